@@ -1,0 +1,437 @@
+"""Performance cases: calls a program makes through the package's public entry
+points, over the range of sizes, measures, directions, key precisions and
+data shapes the library is used for.
+
+A case is a dict of plain values:
+  entry      topl | topl_noalloc | distances | selfjoin | serve
+  data       tiny | text | image | image_bg (the distributions of `synth`, drawn on the GPU)
+  n, B       database histograms, query histograms
+  v, m       vocabulary words and embedding dims (text and tiny; the images use the 28 x 28 grid)
+  method, k, direction, precision, l   the call's options (l: neighbours per query)
+  host       queries and results in host memory instead of device memory
+
+`prepare` makes the data from the seed and loads it; `run` is one call;
+`exact` evaluates the same distances in float64 with plain torch.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_1812_02091_amd import lcemd
+
+SIDE = 28  # image grid
+BACKGROUND = 1.0 / 255.0  # background pixel value of the dense images
+
+
+def listed():
+    return [
+        # one query of a program that calls with host arrays against a small collection
+        dict(name="tiny_one", entry="topl", data="tiny", v=2000, m=64, n=200, B=1, method="act", k=3,
+             direction="sym", precision="fp32", l=5, host=True),
+        # interactive search: a single document against a news-sized collection
+        dict(name="text_one_bf16", entry="topl", data="text", v=70000, m=300, n=18000, B=1, method="act", k=8,
+             direction="sym", precision="bf16", l=16, host=False),
+        # a tight loop that may not allocate: small batches, one direction
+        dict(name="text_noalloc", entry="topl_noalloc", data="text", v=70000, m=300, n=18000, B=16, method="act", k=4,
+             direction="d2q", precision="fp32", l=10, host=False),
+        # offline evaluation of a news-sized collection, float32 keys, deep transfers
+        dict(name="text_batch_act16", entry="topl", data="text", v=70000, m=300, n=18000, B=500, method="act", k=16,
+             direction="sym", precision="fp32", l=16, host=False),
+        # the whole symmetric relaxed-WMD matrix of a small query set (both directions in linear form)
+        dict(name="text_rwmd_matrix", entry="distances", data="text", v=70000, m=300, n=18000, B=61, method="rwmd", k=1,
+             direction="sym", precision="fp32", l=0, host=False),
+        # the tightest measure, one direction
+        dict(name="text_ict_matrix", entry="distances", data="text", v=70000, m=300, n=18000, B=64, method="ict", k=1,
+             direction="d2q", precision="fp32", l=0, host=False),
+        # large vocabulary and collection with bf16 keys (tables far larger than the caches)
+        dict(name="words_large_bf16", entry="topl", data="text", v=500000, m=300, n=100000, B=192, method="act", k=8,
+             direction="sym", precision="bf16", l=16, host=False),
+        # image search: many queries against 60,000 images
+        dict(name="image_act2", entry="topl", data="image", n=60000, B=3000, method="act", k=2,
+             direction="sym", precision="fp32", l=16, host=False),
+        # the full matrix of an image set against a collection, deeper transfers
+        dict(name="image_matrix_act8", entry="distances", data="image", n=20000, B=501, method="act", k=8,
+             direction="sym", precision="fp32", l=0, host=False),
+        # all-pairs neighbours of an image collection
+        dict(name="image_selfjoin", entry="selfjoin", data="image", n=10000, B=0, method="act", k=2,
+             direction="sym", precision="fp32", l=16, host=False),
+        # images with their background: every pixel a coordinate (784 words per histogram)
+        dict(name="image_bg_act16", entry="topl", data="image_bg", n=6000, B=100, method="act", k=16,
+             direction="sym", precision="fp32", l=16, host=False),
+        # a burst of differently long queries to the server
+        dict(name="serve_burst", entry="serve", data="text", v=70000, m=300, n=18000, B=48, method="act", k=8,
+             direction="sym", precision="bf16", l=16, host=True),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["tiny", "text", "text", "text", "words", "image", "image", "image_bg", "selfjoin", "serve"])
+    method = rng.choice(["act", "act", "act", "act", "rwmd", "omr", "ict"])
+    k = rng.choice([1, 2, 3, 4, 5, 8, 12, 16]) if method == "act" else 1
+    c = dict(entry=rng.choice(["topl", "topl", "distances"]), data=kind, method=method, k=k,
+             direction=rng.choice(["d2q", "q2d", "sym", "sym", "sym"]), precision=rng.choice(["fp32", "fp32", "bf16"]),
+             l=rng.choice([1, 5, 10, 16, 32]), host=False)
+    if kind == "tiny":
+        c.update(v=_log_int(rng, 500, 5000), m=rng.choice([16, 50, 64, 100]), n=_log_int(rng, 50, 2000),
+                 B=_log_int(rng, 1, 32), host=True)
+    elif kind in ("text", "serve"):
+        c.update(data="text", v=_log_int(rng, 20000, 70000), m=rng.choice([100, 200, 300]), n=_log_int(rng, 2000, 18000),
+                 B=_log_int(rng, 1, 400))
+        if kind == "serve":
+            c.update(entry="serve", B=_log_int(rng, 1, 48), method="act", k=rng.choice([1, 4, 8]), direction="sym",
+                     host=True)
+        elif c["entry"] == "topl" and c["B"] <= 64 and c["method"] == "act" and rng.random() < 0.4:
+            c.update(entry="topl_noalloc", direction="d2q", k=min(k, 4))
+        elif c["direction"] == "q2d" or (c["direction"] == "sym" and (method == "rwmd" or c["entry"] == "distances")):
+            # the reverse matrix walks every document as a query
+            c["B"] = min(c["B"], 24 if method == "ict" else 61)
+    elif kind == "words":
+        c.update(data="text", entry="topl", direction=rng.choice(["d2q", "sym"]), method="act", k=rng.choice([2, 4, 8]),
+                 v=_log_int(rng, 100000, 500000), m=300, n=_log_int(rng, 20000, 100000), B=_log_int(rng, 16, 192),
+                 precision=rng.choice(["bf16", "bf16", "fp32", "fp8"]))
+        if c["precision"] != "bf16":
+            c["B"] = min(c["B"], 100)
+    elif kind == "image":
+        c.update(n=_log_int(rng, 3000, 60000), B=_log_int(rng, 8, 3000), precision="fp32")
+        if c["entry"] == "distances" or method in ("ict", "rwmd") or k > 8:
+            c["B"] = min(c["B"], 500)
+            c["n"] = min(c["n"], 20000)
+    elif kind == "image_bg":
+        c.update(n=_log_int(rng, 500, 6000), B=_log_int(rng, 4, 100), precision="fp32")
+        if method == "rwmd":  # 0 for every pair of dense images
+            c.update(method="omr")
+        if method == "ict":
+            c["B"] = min(c["B"], 32)
+        if c["direction"] == "q2d" or c["entry"] == "distances":
+            c["n"] = min(c["n"], 1000)
+    else:
+        c.update(data="image", entry="selfjoin", n=_log_int(rng, 1000, 10000), B=0, precision="fp32")
+        if method in ("ict", "rwmd") or k > 8:
+            c["n"] = min(c["n"], 5000)
+    if c["entry"] in ("distances",):
+        c["l"] = 0
+    return c
+
+
+# ---------------------------------------------------------------------------
+# data (the distributions of `synth`, drawn on the GPU)
+# ---------------------------------------------------------------------------
+def _gen(seed, stream):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed) * 16 + stream)
+    return g
+
+
+def _normalise(ptr, raw):
+    """Rows scaled to sum 1 (float64, one rounding)."""
+    lens = ptr[1:] - ptr[:-1]
+    row = torch.repeat_interleave(torch.arange(lens.numel(), device=raw.device), lens)
+    c = torch.zeros(raw.numel() + 1, dtype=torch.float64, device=raw.device)
+    torch.cumsum(raw, 0, out=c[1:])
+    return (raw / (c[ptr[1:]] - c[ptr[:-1]])[row]).float()
+
+
+def _zipf_csr(g, n, v, s, lengths, tf, chunk=16384):
+    """Per row the first `lengths` distinct words of i.i.d. Zipf(s) draws,
+    weights 1 - U[0,1) or (tf) Geometric(1/2)."""
+    dev = "cuda"
+    w = torch.arange(1, v + 1, dtype=torch.float64, device=dev) ** (-s)
+    cdf = torch.cumsum(w, 0)
+    cdf /= cdf[-1].clone()
+    counts, cols = [], []
+    for a in range(0, n, chunk):
+        L = lengths[a:a + chunk]
+        r = L.numel()
+        M = 2 * int(L.max()) + 16
+        t = torch.searchsorted(cdf, torch.rand(r, M, generator=g, dtype=torch.float64, device=dev), right=True)
+        t.clamp_(max=v - 1)
+        st, order = torch.sort(t, dim=1, stable=True)
+        first_sorted = torch.ones_like(st, dtype=torch.bool)
+        first_sorted[:, 1:] = st[:, 1:] != st[:, :-1]
+        first = torch.empty_like(first_sorted).scatter_(1, order, first_sorted)
+        keep = first & (torch.cumsum(first, 1) <= L[:, None])
+        kept_sorted = keep.gather(1, order)
+        counts.append(kept_sorted.sum(1))
+        cols.append(st[kept_sorted])
+    lens = torch.cat(counts)
+    col = torch.cat(cols).to(torch.int32)
+    ptr = torch.zeros(n + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(lens, 0, out=ptr[1:])
+    u = torch.rand(col.numel(), generator=g, dtype=torch.float64, device=dev)
+    raw = torch.floor(torch.log2(1.0 / (1.0 - u))) + 1.0 if tf else 1.0 - u
+    return ptr, col, _normalise(ptr, raw)
+
+
+def _uniform_lengths(g, n, lo, hi):
+    return torch.randint(lo, hi + 1, (n,), generator=g, device="cuda")
+
+
+def _text_lengths(g, n):
+    x = torch.randn(n, generator=g, dtype=torch.float64, device="cuda") * 0.5 + (math.log(120.0) - 0.125)
+    return torch.round(torch.exp(x)).clamp(50, 300).to(torch.int64)
+
+
+def _images(g, n, background, chunk=8192):
+    """Discs of radius U{4..10} with pixel intensities 1 - U[0,1); with a
+    background every pixel carries at least that value."""
+    dev = "cuda"
+    px = torch.arange(SIDE * SIDE, device=dev)
+    yy, xx = px // SIDE, px % SIDE
+    counts, cols, raws = [], [], []
+    for a in range(0, n, chunk):
+        c = min(n, a + chunk) - a
+        r = torch.randint(4, 11, (c,), generator=g, device=dev)
+        span = (SIDE - 2 * r).double()
+        cy = r + (torch.rand(c, generator=g, dtype=torch.float64, device=dev) * span).long()
+        cx = r + (torch.rand(c, generator=g, dtype=torch.float64, device=dev) * span).long()
+        mask = (yy - cy[:, None]) ** 2 + (xx - cx[:, None]) ** 2 <= (r * r)[:, None]
+        val = (1.0 - torch.rand(c, SIDE * SIDE, generator=g, dtype=torch.float64, device=dev)) * mask
+        if background:
+            val += BACKGROUND
+            mask = torch.ones_like(mask)
+        counts.append(mask.sum(1))
+        cols.append(px.expand(c, -1)[mask].to(torch.int32))
+        raws.append(val[mask])
+    ptr = torch.zeros(n + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(torch.cat(counts), 0, out=ptr[1:])
+    return ptr, torch.cat(cols), _normalise(ptr, torch.cat(raws))
+
+
+def _data(case, seed):
+    """(V, database CSR, query CSR or None) on the GPU."""
+    kind, n, B = case["data"], case["n"], case["B"]
+    if kind in ("image", "image_bg"):
+        px = torch.arange(SIDE * SIDE, device="cuda")
+        V = torch.stack([px // SIDE, px % SIDE], 1).float()
+        db = _images(_gen(seed, 1), n, kind == "image_bg")
+        return V, db, _images(_gen(seed, 2), B, kind == "image_bg") if B else None
+    v, m = case["v"], case["m"]
+    V = torch.randn(v, m, generator=_gen(seed, 0), device="cuda")
+    g, gq = _gen(seed, 1), _gen(seed, 2)
+    if kind == "tiny":
+        return (V, _zipf_csr(g, n, v, 1.1, _uniform_lengths(g, n, 10, 40), False),
+                _zipf_csr(gq, B, v, 1.1, _uniform_lengths(gq, B, 10, 40), False))
+    V /= V.norm(dim=1, keepdim=True)
+    db = _zipf_csr(g, n, v, 1.0, _text_lengths(g, n), True)
+    qlen = _uniform_lengths(gq, B, 10, 500) if case["entry"] == "serve" else _text_lengths(gq, B)
+    return V, db, _zipf_csr(gq, B, v, 1.0, qlen, True)
+
+
+def _host(csr):
+    return tuple(x.cpu().numpy() for x in csr)
+
+
+# ---------------------------------------------------------------------------
+# the calls
+# ---------------------------------------------------------------------------
+def prepare(case, seed):
+    V, db, q = _data(case, seed)
+    low = case["precision"]
+    ctx = lcemd.open_context(V, *db, device=0, precisions=() if low == "fp32" else (low,))
+    s = dict(case=case, ctx=ctx)
+    if case["entry"] == "serve":
+        ptr, col, val = _host(q)
+        s["queries"] = [(col[a:b].copy(), val[a:b].copy()) for a, b in zip(ptr[:-1], ptr[1:])]
+        s["server"] = lcemd.Server(ctx, method=case["method"], k=case["k"], precision=low, l=case["l"], max_slots=16)
+    elif q is not None:
+        s["q"] = _host(q) if case["host"] else q
+    if case["entry"] == "topl_noalloc":
+        s["out"] = (torch.empty((case["B"], case["l"]), dtype=torch.int64, device="cuda"),
+                    torch.empty((case["B"], case["l"]), dtype=torch.float32, device="cuda"))
+    return s
+
+
+def run(state):
+    c, ctx = state["case"], state["ctx"]
+    opts = dict(method=c["method"], k=c["k"], precision=c["precision"])
+    if c["entry"] == "topl":
+        return ctx.topl(*state["q"], c["l"], direction=c["direction"], **opts)
+    if c["entry"] == "distances":
+        return ctx.distances(*state["q"], direction=c["direction"], **opts)
+    if c["entry"] == "topl_noalloc":
+        return ctx.topl_noalloc(*state["q"], c["l"], state["out"], **opts)
+    if c["entry"] == "selfjoin":
+        return ctx.selfjoin_topl(c["l"], direction=c["direction"], device=True, **opts)
+    server = state["server"]
+    tickets = [server.submit(col, val) for col, val in state["queries"]]
+    got = [server.wait(t) for t in tickets]
+    return np.stack([g[0] for g in got]), np.stack([g[1] for g in got])
+
+
+# ---------------------------------------------------------------------------
+# work and float64 values
+# ---------------------------------------------------------------------------
+def _mean_words(case):
+    if case["data"] == "image_bg":
+        return SIDE * SIDE
+    return {"tiny": 25.0, "text": 118.5, "image": 166.0}[case["data"]]
+
+
+def _distinct(v, s, tokens):
+    """Expected distinct words of Zipf(s) draws that hit `tokens` (row, word) pairs."""
+    w = np.arange(1, v + 1, dtype=np.float64) ** (-s)
+    return float(np.sum(1.0 - np.exp(-1.3 * tokens * w / w.sum())))
+
+
+def work(case):
+    """Contraction of the table words with the batch's words (2 flops per
+    product), one transfer step and sum (4 flops) per (non-zero, query) and
+    direction; embeddings, histograms and results moved once."""
+    h, n, l = _mean_words(case), case["n"], case["l"]
+    B = case["B"] or n
+    hq = 255.0 if case["entry"] == "serve" else h
+    image = case["data"] in ("image", "image_bg")
+    m = 2 if image else case["m"]
+    zipf = 1.1 if case["data"] == "tiny" else 1.0
+    used = SIDE * SIDE if image else _distinct(case["v"], zipf, n * h)
+    used_q = SIDE * SIDE if image else _distinct(case["v"], zipf, B * hq)
+    d2q = 2.0 * used * B * hq * m + 4.0 * B * n * h
+    q2d = 2.0 * used_q * n * h * m + 4.0 * B * n * hq
+    sym_pairs = 2.0 * B * (l + max(8, l // 2)) * hq * h * m
+    full = case["entry"] == "distances"
+    if case["direction"] == "d2q" or case["entry"] == "selfjoin":
+        flops = d2q
+    elif case["direction"] == "q2d":
+        flops = q2d
+    else:
+        flops = d2q + (q2d if full or case["method"] == "rwmd" else sym_pairs)
+    out = B * n * 4.0 if full else B * l * 12.0
+    return {"bytes": used * m * 4.0 + n * h * 8.0 + 8.0 * n + B * hq * 8.0 + out, "flops": flops}
+
+
+class _Exact:
+    """Float64 distances of queries against a histogram set by Alg. 2-3 of
+    the method, plain torch."""
+
+    def __init__(self, V, method, k):
+        self.V = V.double()
+        self.norm = (self.V * self.V).sum(1)
+        self.method, self.k = method, k
+
+    def depth(self, h):
+        return {"rwmd": 1, "omr": min(2, h), "act": min(self.k, h), "ict": h}[self.method]
+
+    def squared(self, a, b):
+        """|V[a] - V[b]|^2 (..., len a, len b), exactly 0 for equal words."""
+        d2 = self.norm[a][..., :, None] + self.norm[b][..., None, :]
+        d2 = d2 - 2.0 * (self.V[a] @ self.V[b].transpose(-1, -2).contiguous())
+        d2.clamp_(min=0.0)
+        return d2.masked_fill_(a[..., :, None] == b[..., None, :], 0.0)
+
+    def tables(self, d2, w):
+        """Per row the nearest destinations ascending by (distance, position)
+        and their weights, cut at the measure's depth; the last takes the rest."""
+        K = self.depth(d2.shape[-1])
+        if K <= 32 and self.V.shape[1] > 2:  # no ties between different words
+            d2, at = torch.topk(d2, K, dim=-1, largest=False, sorted=True)
+        else:
+            d2, at = torch.sort(d2, dim=-1, stable=True)
+            d2, at = d2[..., :K], at[..., :K]
+        W = w.expand(*d2.shape[:-1], w.shape[-1]).gather(-1, at).clone()
+        W[..., -1] = math.inf
+        if self.method == "omr":
+            W[..., 0] = torch.where(d2[..., 0] == 0.0, W[..., 0], math.inf)
+        return d2.sqrt(), W
+
+    @staticmethod
+    def transfer(x, Z, W, at=None):
+        """Cost of moving masses x down their rows' (Z, W) lists."""
+        rem, cost = x.clone(), torch.zeros_like(x)
+        for i in range(Z.shape[-1]):
+            z, w = (Z[..., i], W[..., i]) if at is None else (Z[:, i][at], W[:, i][at])
+            r = torch.minimum(rem, w)
+            cost += r * z.masked_fill(r == 0.0, 0.0)
+            rem -= r
+            if i % 4 == 3 and not bool((rem > 0).any()):
+                break
+        return cost
+
+    def d2q(self, src, dst):
+        """(rows of dst) x (rows of src): mass of src moved into dst."""
+        ptr, col, val = src
+        used, at = torch.unique(col.long(), return_inverse=True)
+        x = val.double()
+        c = torch.zeros(x.numel() + 1, dtype=torch.float64, device=x.device)
+        out = []
+        qp = dst[0].tolist()
+        for a, b in zip(qp[:-1], qp[1:]):
+            Z, W = self.tables(self.squared(used, dst[1][a:b].long()), dst[2][a:b].double())
+            torch.cumsum(self.transfer(x, Z, W, at), 0, out=c[1:])
+            out.append(c[ptr[1:]] - c[ptr[:-1]])
+        return torch.stack(out)
+
+    def q2d_of(self, qc, qw, db, rows):
+        """Mass of one query moved into each of the database rows `rows`."""
+        ptr, col, val = db
+        a, lens = ptr[rows], ptr[rows + 1] - ptr[rows]
+        H = int(lens.max())
+        j = torch.arange(H, device=col.device)
+        live = j < lens[:, None]
+        at = (a[:, None] + j).clamp(max=col.numel() - 1)
+        words = col[at].long()
+        d2 = self.squared(qc.long().expand(rows.numel(), -1), words).masked_fill_(~live[:, None, :], math.inf)
+        K, d2s, pos = self.depth(H), *torch.sort(d2, dim=-1, stable=True)
+        d2s, pos = d2s[..., :K].contiguous(), pos[..., :K]
+        W = torch.where(live, val[at].double(), 0.0)[:, None, :].expand_as(d2).gather(-1, pos).clone()
+        last = torch.clamp(lens, max=K)[:, None, None] - 1  # the row's own last entry takes the rest
+        i = torch.arange(K, device=col.device)
+        W = torch.where(i == last, math.inf, W)
+        if self.method == "omr":
+            W[..., 0] = torch.where((d2s[..., 0] == 0.0) & (last[..., 0] > 0), W[..., 0], math.inf)
+        Z = d2s.masked_fill(i > last, 0.0).sqrt()
+        return self.transfer(qw.double().expand(rows.numel(), -1), Z, W).sum(-1)
+
+
+def exact(case, seed):
+    if case["precision"] == "fp8":
+        return None  # its statistical selection has no such value
+    B, n = case["B"] or case["n"], case["n"]
+    h = _mean_words(case)
+    V, db, q = _data(case, seed)
+    e = _Exact(V, case["method"], case["k"])
+    l, entry, direction = case["l"], case["entry"], case["direction"]
+    if entry == "selfjoin":
+        D = e.d2q(db, db)
+        if direction == "q2d":
+            D = D.t().contiguous()
+        elif direction == "sym":
+            D = torch.maximum(D, D.t().contiguous())
+        D.fill_diagonal_(math.inf)
+        return None, torch.topk(D, l, dim=1, largest=False, sorted=True).values
+    both = direction == "sym" and (entry == "distances" or case["method"] == "rwmd")
+    if (both or direction == "q2d") and n > 20000:
+        return None
+    if direction == "q2d":
+        D = e.d2q(q, db).t().contiguous()
+    else:
+        D = e.d2q(db, q)
+        if both:
+            D = torch.maximum(D, e.d2q(q, db).t().contiguous())
+    if entry == "distances":
+        return D
+    if direction != "sym" or both:
+        return None, torch.topk(D, l, dim=1, largest=False, sorted=True).values
+    # symmetric top-l: SYM >= D2Q, so the rows of smallest D2Q suffice once
+    # the next D2Q is no smaller than the l-th SYM
+    out = torch.empty(B, l, dtype=torch.float64, device=D.device)
+    qp = q[0].tolist()
+    for b in range(B):
+        take = min(n, max(2 * l, l + 16))
+        while True:
+            d, rows = torch.topk(D[b], min(n, take + 1), largest=False, sorted=True)
+            s = []
+            for a in range(0, min(take, rows.numel()), 64 if h < 400 else 16):
+                part = rows[a:min(take, a + (64 if h < 400 else 16))]
+                s.append(e.q2d_of(q[1][qp[b]:qp[b + 1]], q[2][qp[b]:qp[b + 1]], db, part))
+            s = torch.cat(s)
+            best = torch.topk(torch.maximum(s, d[:s.numel()]), l, largest=False, sorted=True).values
+            if take >= n or bool(d[-1] >= best[-1]):
+                break
+            take = min(n, 4 * take)
+        out[b] = best
+    return None, out
