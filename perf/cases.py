@@ -103,8 +103,8 @@ def draw(rng):
             c["n"] = min(c["n"], 20000)
     elif kind == "image_bg":
         c.update(n=_log_int(rng, 500, 6000), B=_log_int(rng, 4, 100), precision="fp32")
-        if method == "rwmd":  # 0 for every pair of dense images
-            c.update(method="omr")
+        if method == "rwmd" or (method == "act" and k == 1):  # 0 for every pair of dense images
+            c.update(method="omr", k=1)
         if method == "ict":
             c["B"] = min(c["B"], 32)
         if c["direction"] == "q2d" or c["entry"] == "distances":
