@@ -52,48 +52,26 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
 
-// Cost of document u against query q (one lane): the non-zeros in order,
-// kUnroll at a time with their first table pairs loaded together; further
-// pairs are loaded together for every non-zero that still has mass.
-// Entries past a row's sink are never used: the sink leaves no mass.
-// kUni: every lane of the wave is on this document, so its records and the
-// table row offsets are wave-uniform (scalar loads and arithmetic).
-// kGroup: the QL >= 8 lanes from `glane` on share the document: its first
-// lanes load one record each and the group reads them by lane shuffle
-// (every lane of the group runs this with the same e0, e1).  kSolo (QL < 8):
-// every lane loads its document's records itself.
-enum { kUni = 0, kGroup = 1, kSolo = 2 };
-template <int RM>
+// Cost of document u against query q (one lane, 64 consecutive queries a
+// wave): the non-zeros in order, kUnroll at a time with their first table
+// pairs loaded together; further pairs are loaded together for every
+// non-zero that still has mass.  Entries past a row's sink are never used:
+// the sink leaves no mass.  Every lane of the wave is on this document, so
+// its records and the table row offsets are wave-uniform (scalar loads and
+// arithmetic).
 __device__ __forceinline__ float doc_cost(int64_t e0, int64_t e1, const int2* __restrict__ xcv,
-                                          const float4* __restrict__ Zq, int64_t zw_nq, int KP,
-                                          int lane, int glane) {
+                                          const float4* __restrict__ Zq, int64_t zw_nq, int KP) {
   static_assert(kUnroll == 8, "the group sum below is a tree over 8 terms");
-  constexpr bool UNI = RM == kUni;
-  if constexpr (UNI) {
-    e0 = uniform64(e0);
-    e1 = uniform64(e1);
-  }
+  e0 = uniform64(e0);
+  e1 = uniform64(e1);
   const int64_t rstride = (int64_t)KP * zw_nq;  // float4s from one word's run to the next
   float t = 0.f, comp = 0.f;
   for (int64_t e = e0; e < e1; e += kUnroll) {
     const int cnt = (int)min((int64_t)kUnroll, e1 - e);
     int2 cv[kUnroll];
-    if constexpr (UNI) {
-      if (cnt == kUnroll) {
+    if (cnt == kUnroll) {
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) cv[k] = xcv[e + k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) cv[k] = k < cnt ? xcv[e + k] : make_int2(0, 0);
-      }
-    } else if constexpr (RM == kGroup) {
-      const int j = lane - glane;
-      const int2 rec = j < cnt ? xcv[e + j] : make_int2(0, 0);
-#pragma unroll
-      for (int k = 0; k < kUnroll; ++k) {
-        cv[k].x = __shfl(rec.x, glane + k);
-        cv[k].y = __shfl(rec.y, glane + k);
-      }
+      for (int k = 0; k < kUnroll; ++k) cv[k] = xcv[e + k];
     } else {
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k) cv[k] = k < cnt ? xcv[e + k] : make_int2(0, 0);
@@ -102,7 +80,7 @@ __device__ __forceinline__ float doc_cost(int64_t e0, int64_t e1, const int2* __
     float4 f[kUnroll];
 #pragma unroll
     for (int k = 0; k < kUnroll; ++k) {
-      const int w = UNI ? __builtin_amdgcn_readfirstlane(cv[k].x) : cv[k].x;
+      const int w = __builtin_amdgcn_readfirstlane(cv[k].x);
       base[k] = Zq + (int64_t)w * rstride;
       f[k] = k < cnt ? base[k][0] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
@@ -140,28 +118,32 @@ __device__ __forceinline__ float doc_cost(int64_t e0, int64_t e1, const int2* __
   return t;
 }
 
-// Persistent grid: waves pull (query group of QL, 64/QL x kItemSlots
-// documents) items from eight work counters, one per XCD, each walking a
-// contiguous eighth of the items, query group major (an XCD keeps one
-// group's slice of the tables hot in its L2).  For fixed-shape batches the
-// live query count is read from device memory, and the launcher issues one
-// kernel per lane width: the one whose band (QL/2, QL] holds the live count
+// Batches of more than 32 queries.  Persistent grid: waves pull (64
+// queries, `slots` documents) items from eight work counters, one per XCD,
+// each walking a contiguous eighth of the items, query group major (an XCD
+// keeps one group's slice of the tables hot in its L2).  For fixed-shape
+// batches the live query count is read from device memory, and the launcher
+// issues one kernel per lane width: the one whose band holds the live count
 // works, the others return at once (so a batch with few live queries does
 // not pay for the lanes of its empty slots).  Every wave exits once its
 // counter passes the end of its range.
-template <int QL>
+//
+// slots (4, 8 or kItemSlots consecutive documents) is the host's: a lane's
+// results leave as 16-byte stores, so long items write whole sectors, but
+// one 64-query group of 18,000 documents is only 1,125 items of 16 -- about
+// one wave per SIMD, each alone with its loads' latency.  The launcher
+// shortens items until the chip holds about 16 waves per CU (ICT, 64
+// queries: 1,355 -> 520 us).
 __global__ __launch_bounds__(kThreads) void k_phase2_persistent(
     const int64_t* __restrict__ xptr, const int2* __restrict__ xcv, int64_t n,
-    const int32_t* __restrict__ perm, const float4* __restrict__ ZP, int64_t zw_nq, int KP,
-    int64_t nq_arg, const int* __restrict__ nq_dev, float* __restrict__ out, int64_t ld,
-    unsigned long long* __restrict__ counters) {
-  constexpr int S = 64 / QL;  // documents side by side
-  constexpr int64_t kDocs = (int64_t)S * kItemSlots;
-  const int lane = threadIdx.x & 63, qs = lane % QL, ds = lane / QL;
+    const float4* __restrict__ ZP, int64_t zw_nq, int KP, int64_t nq_arg, const int* __restrict__ nq_dev,
+    int slots, float* __restrict__ out, int64_t ld, unsigned long long* __restrict__ counters) {
+  constexpr int QL = 64;
+  const int lane = threadIdx.x & 63;
   const int xcd = blockIdx.x & 7;
   const int64_t nq = nq_dev ? (int64_t)*nq_dev : nq_arg;
-  if (nq_dev && (nq > nq_arg || (QL > 1 && 2 * nq <= QL))) return;  // another width's band
-  const int64_t nd = (n + kDocs - 1) / kDocs;
+  if (nq_dev && (nq > nq_arg || 2 * nq <= QL)) return;  // another width's band
+  const int64_t nd = (n + slots - 1) / slots;
   const int64_t total = (nq + QL - 1) / QL * nd;
   const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
   while (true) {
@@ -169,46 +151,146 @@ __global__ __launch_bounds__(kThreads) void k_phase2_persistent(
     if (lane == 0) it = atomicAdd(&counters[xcd], 1ull);
     const int64_t item = uniform64(lo + (int64_t)__shfl((long long)it, 0));
     if (item >= hi) break;
-    // lanes past the batch walk the last query's table (so every lane of a
-    // document group takes part in its record shuffles) and write nothing
-    const int64_t q = (item / nd) * QL + qs;
+    // lanes past the batch walk the last query's table and write nothing
+    const int64_t q = (item / nd) * QL + lane;
     const bool qok = q < nq;
     const float4* Zq = ZP + (qok ? q : nq - 1);
-    const int64_t d0 = (item % nd) * kDocs + ds;
-    if constexpr (S == 1) {
-      // one document at a time for all 64 lanes: each lane's kItemSlots
-      // results are consecutive in its query's row, so they are staged in
-      // the wave's own LDS rows (lane-private slots: no barrier) and written
-      // together, 16-byte stores where aligned
-      __shared__ float st[kThreads / 64][kItemSlots][64];
-      float(*sw)[64] = st[threadIdx.x >> 6];
-      int cnt = 0;
-      for (int j = 0; j < kItemSlots; ++j) {
-        const int64_t i = d0 + j;
-        if (i >= n) break;
-        sw[j][lane] = doc_cost<kUni>(xptr[i], xptr[i + 1], xcv, Zq, zw_nq, KP, lane, 0);
-        ++cnt;
-      }
-      if (qok && cnt > 0) {
-        float* o = out + q * ld + d0;
-        if (cnt == kItemSlots && (reinterpret_cast<uintptr_t>(o) & 15) == 0) {
-#pragma unroll
-          for (int t = 0; t < kItemSlots; t += 4)
-            *reinterpret_cast<float4*>(o + t) = make_float4(sw[t][lane], sw[t + 1][lane], sw[t + 2][lane], sw[t + 3][lane]);
-        } else {
-          for (int t = 0; t < cnt; ++t) o[t] = sw[t][lane];
-        }
-      }
-    } else {
-      for (int j = 0; j < kItemSlots; ++j) {
-        const int64_t i = d0 + (int64_t)j * S;
-        if (i >= n) break;
-        const int64_t u = (int64_t)perm[i];
-        const float c = doc_cost<(QL >= kUnroll ? kGroup : kSolo)>(xptr[u], xptr[u + 1], xcv, Zq, zw_nq, KP,
-                                                                   lane, ds * QL);
-        if (qok) out[q * ld + u] = c;
+    const int64_t d0 = (item % nd) * slots;
+    // one document at a time for all 64 lanes: each lane's results are
+    // consecutive in its query's row, so they are staged in the wave's own
+    // LDS rows (lane-private slots: no barrier) and written together,
+    // 16-byte stores where aligned
+    __shared__ float st[kThreads / 64][kItemSlots][64];
+    float(*sw)[64] = st[threadIdx.x >> 6];
+    int cnt = 0;
+    for (int j = 0; j < slots; ++j) {
+      const int64_t i = d0 + j;
+      if (i >= n) break;
+      sw[j][lane] = doc_cost(xptr[i], xptr[i + 1], xcv, Zq, zw_nq, KP);
+      ++cnt;
+    }
+    if (qok && cnt > 0) {
+      float* o = out + q * ld + d0;
+      if (cnt == slots && (reinterpret_cast<uintptr_t>(o) & 15) == 0) {
+        for (int t = 0; t < slots; t += 4)
+          *reinterpret_cast<float4*>(o + t) = make_float4(sw[t][lane], sw[t + 1][lane], sw[t + 2][lane], sw[t + 3][lane]);
+      } else {
+        for (int t = 0; t < cnt; ++t) o[t] = sw[t][lane];
       }
     }
+  }
+}
+
+// Batches of up to 32 queries: a wave's lanes are QL queries (fastest, so a
+// non-zero's table run is one contiguous read) x NL non-zeros of one group
+// of eight x S documents (S > 1 only below 8 queries; then taken in order of
+// length within windows of 128).  Lane j of a document's NL holds non-zeros
+// j, j + NL, ... of every group, NL groups a step, so a lane has eight table
+// loads in flight as in doc_cost; the group sums cross the lanes as the same
+// eight-term tree and every lane of the document runs the same Kahan chain:
+// the bits of doc_cost.
+//
+// Bound: the table gather's latency and the L1/L2 request rate.  The former
+// split (documents side by side, 16 slots each, work counters) put 18,000
+// documents x 1 query on 18 waves: 1,813 us, and x 16 queries on 281:
+// 1,043 us.  Spreading a document's non-zeros over lanes gives 8x the waves
+// and coalesced record reads: 35 us and 133 us (ACT, k = 8 and 4, 2.1 M
+// non-zeros, 70,000 words).
+// Waves take documents at a fixed stride (a counter's atomics, about 0.2 us
+// each on one address, cost more than the walk of a short document).
+template <int QL>
+__global__ __launch_bounds__(kThreads) void k_phase2_small(
+    const int64_t* __restrict__ xptr, const int2* __restrict__ xcv, int64_t n,
+    const int32_t* __restrict__ perm, const float4* __restrict__ ZP, int64_t zw_nq, int KP,
+    int64_t nq_arg, const int* __restrict__ nq_dev, float* __restrict__ out, int64_t ld) {
+  constexpr int NL = QL >= 8 ? 64 / QL : 8;  // lanes of a group of eight non-zeros
+  constexpr int S = 64 / (QL * NL);          // documents side by side
+  constexpr int PER = kUnroll / NL;          // non-zeros of a group per lane
+  constexpr int G = NL;                      // groups a step: PER * G = 8 loads in flight
+  const int64_t nq = nq_dev ? (int64_t)*nq_dev : nq_arg;
+  if (nq_dev && (nq > nq_arg || (QL > 1 ? 2 * nq <= QL : nq < 1))) return;  // another width's band
+  const int lane = threadIdx.x & 63, qs = lane % QL, j = lane / QL % NL, ds = lane / (QL * NL);
+  // lanes past the batch walk the last query's table and write nothing
+  const bool qok = qs < nq;
+  const float4* Zq = ZP + (qok ? qs : nq - 1);
+  const int64_t rstride = (int64_t)KP * zw_nq;  // float4s from one word's run to the next
+  const int64_t wave = (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t items = (n + S - 1) / S, nw = (int64_t)gridDim.x * (kThreads / 64);
+  for (int64_t item = wave; item < items; item += nw) {
+    const int64_t i = min(item * S + ds, n - 1);  // past the end: the last document again, not written
+    const int64_t u = S > 1 ? (int64_t)perm[i] : i;
+    int64_t e0 = xptr[u], e1 = xptr[u + 1];
+    if constexpr (S == 1) {
+      e0 = uniform64(e0);
+      e1 = uniform64(e1);
+    }
+    float t = 0.f, comp = 0.f;
+    for (int64_t e = e0; e < e1; e += kUnroll * G) {
+      const int left = (int)min((int64_t)(kUnroll * G), e1 - e);
+      float rem[kUnroll], acc[kUnroll];
+      const float4* base[kUnroll];
+      int2 cv[kUnroll];
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) {  // k = PER * group + non-zero of the lane
+        const int at = kUnroll * (k / PER) + j + NL * (k % PER);
+        cv[k] = at < left ? xcv[e + at] : make_int2(0, 0);
+      }
+      float4 f[kUnroll];
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) {
+        const int at = kUnroll * (k / PER) + j + NL * (k % PER);
+        base[k] = Zq + (int64_t)cv[k].x * rstride;
+        f[k] = at < left ? base[k][0] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      bool any = false;
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) {
+        rem[k] = __int_as_float(cv[k].y);  // 0 for the padding slots
+        acc[k] = 0.f;
+        step(rem[k], acc[k], f[k].x, f[k].y);
+        step(rem[k], acc[k], f[k].z, f[k].w);
+        any = any || rem[k] > 0.f;
+      }
+      for (int p = 1; any && p < KP; ++p) {
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+          if (rem[k] > 0.f) f[k] = base[k][p * zw_nq];
+        any = false;
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k) {
+          if (rem[k] > 0.f) {
+            step(rem[k], acc[k], f[k].x, f[k].y);
+            if (rem[k] > 0.f) step(rem[k], acc[k], f[k].z, f[k].w);
+            any = any || rem[k] > 0.f;
+          }
+        }
+      }
+      // group sums: ((a0 + a1) + (a2 + a3)) + ((a4 + a5) + (a6 + a7)), the
+      // terms of one lane NL apart, the others across lanes (a sum of two is
+      // the same bits either way round); groups past the document add +0
+      // to a state they leave unchanged, so they are skipped
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        float a[PER];
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+          a[r] = acc[PER * g + r];
+#pragma unroll
+          for (int o = 1; o < NL; o <<= 1) a[r] += __shfl_xor(a[r], o * QL);
+        }
+        float s;
+        if constexpr (PER == 1) s = a[0];
+        else if constexpr (PER == 2) s = a[0] + a[1];
+        else s = (a[0] + a[1]) + (a[2] + a[3]);
+        if (kUnroll * g < left) {
+          const float y = s - comp;
+          const float tt = t + y;
+          comp = (tt - t) - y;
+          t = tt;
+        }
+      }
+    }
+    if (j == 0 && qok && item * S + ds < n) out[(int64_t)qs * ld + u] = t;
   }
 }
 
@@ -260,16 +342,32 @@ int persistent_grid(const void* fn, int threads, size_t shmem, int64_t items) {
   return (int)grid;
 }
 
-template <int QL>
-static hipError_t launch_p2(const int64_t* xptr, const int2* xcv, int64_t n, const int32_t* perm,
-                            const float2* ZW, int64_t zw_nq, int KT, int64_t nq, const int* nq_dev,
-                            float* out, int64_t ld, unsigned long long* counters, hipStream_t s) {
+static hipError_t launch_p2_wide(const int64_t* xptr, const int2* xcv, int64_t n, const float2* ZW, int64_t zw_nq,
+                                 int KT, int64_t nq, const int* nq_dev, float* out, int64_t ld,
+                                 unsigned long long* counters, hipStream_t s) {
+  // documents per item: the longest of 16, 8, 4 that leaves about 16 waves
+  // per CU (256 CUs)
+  int slots = kItemSlots;
+  while (slots > 4 && (nq + 63) / 64 * ((n + slots - 1) / slots) < 4096) slots /= 2;
   // waves needed at most (bounds the grid)
-  const int64_t items = (nq + QL - 1) / QL * ((n + (64 / QL) * kItemSlots - 1) / ((64 / QL) * kItemSlots));
-  const int grid = persistent_grid((const void*)k_phase2_persistent<QL>, kThreads, 0, (items + 3) / 4);
+  const int64_t items = (nq + 63) / 64 * ((n + slots - 1) / slots);
+  const int grid = persistent_grid((const void*)k_phase2_persistent, kThreads, 0, (items + 3) / 4);
   if (grid <= 0) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(k_phase2_persistent<QL>, dim3(grid), dim3(kThreads), 0, s, xptr, xcv, n, perm,
-                     (const float4*)ZW, zw_nq, (int)zw_pairs(KT), nq, nq_dev, out, ld, counters);
+  hipLaunchKernelGGL(k_phase2_persistent, dim3(grid), dim3(kThreads), 0, s, xptr, xcv, n, (const float4*)ZW, zw_nq,
+                     (int)zw_pairs(KT), nq, nq_dev, slots, out, ld, counters);
+  return hipGetLastError();
+}
+
+template <int QL>
+static hipError_t launch_p2_small(const int64_t* xptr, const int2* xcv, int64_t n, const int32_t* perm,
+                                  const float2* ZW, int64_t zw_nq, int KT, int64_t nq, const int* nq_dev,
+                                  float* out, int64_t ld, hipStream_t s) {
+  constexpr int kDocs = QL >= 8 ? 1 : 8 / QL;  // documents of a wave
+  const int64_t items = (n + kDocs - 1) / kDocs;
+  const int grid = persistent_grid((const void*)k_phase2_small<QL>, kThreads, 0, (items + 3) / 4);
+  if (grid <= 0) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(k_phase2_small<QL>, dim3(grid), dim3(kThreads), 0, s, xptr, xcv, n, perm, (const float4*)ZW,
+                     zw_nq, (int)zw_pairs(KT), nq, nq_dev, out, ld);
   return hipGetLastError();
 }
 
@@ -279,24 +377,27 @@ hipError_t launch_phase2_persistent(const int64_t* xptr, const int2* xcv, int64_
                                     unsigned long long* counters, hipStream_t s) {
   // nq: the batch size, or with nq_dev the largest live count
   if (n <= 0 || nq <= 0) return hipSuccess;
-  hipError_t e = launch_zero_ints((int*)counters, 16, s);
-  if (e != hipSuccess) return e;
   if (nq <= 32 && !perm) return hipErrorInvalidValue;
   // lane width: the smallest power of two >= the queries (at most 64); with
   // a device-side live count, every width up to that one (each works only
   // for live counts in its band)
   int top = 1;
   while (top < 64 && top < nq) top *= 2;
+  hipError_t e;
+  if (top == 64) {
+    e = launch_zero_ints((int*)counters, 16, s);
+    if (e != hipSuccess) return e;
+  }
   for (int ql = top; ql >= (nq_dev ? 1 : top); ql /= 2) {
     const int64_t qmax = ql == top ? nq : std::min<int64_t>(nq, ql);  // the most queries this width takes
     switch (ql) {
-      case 64: e = launch_p2<64>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
-      case 32: e = launch_p2<32>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
-      case 16: e = launch_p2<16>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
-      case 8: e = launch_p2<8>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
-      case 4: e = launch_p2<4>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
-      case 2: e = launch_p2<2>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
-      default: e = launch_p2<1>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
+      case 64: e = launch_p2_wide(xptr, xcv, n, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
+      case 32: e = launch_p2_small<32>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
+      case 16: e = launch_p2_small<16>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
+      case 8: e = launch_p2_small<8>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
+      case 4: e = launch_p2_small<4>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
+      case 2: e = launch_p2_small<2>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
+      default: e = launch_p2_small<1>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
     }
     if (e != hipSuccess) return e;
   }
