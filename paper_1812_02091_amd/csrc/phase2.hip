@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "phase2_step.h"
 
 namespace lcemd {
 
@@ -31,80 +32,85 @@ constexpr int kUnroll = 8;       // non-zeros whose table loads are in flight to
 constexpr int kItemSlots = 16;   // document slots per lane and work item
 static_assert(kItemSlots % 4 == 0, "results are stored four at a time");
 
-// One transfer step of Eq. (6)-(8) against table entry (z, w).  rem >= +0
-// (never -0: rem - rem is +0) and w > 0 (or +inf), so the smaller float is
-// the smaller bit pattern: one integer minimum (fminf would first
-// canonicalise both operands).  A step with rem = +0 changes nothing
-// (r = +0, acc + 0 z = acc for finite z >= 0): so the second entry of a
-// table row's first 16-byte pair, which is always written (as (0, 0) when
-// the row has one entry), is stepped without testing rem; later pairs are
-// read only while some mass remains (their entries past the row's sink are
-// never written).
-__device__ __forceinline__ void step(float& rem, float& acc, float z, float w) {
-  const float r = __uint_as_float(min(__float_as_uint(rem), __float_as_uint(w)));
-  rem -= r;
-  acc = fmaf(r, z, acc);
-}
-
-__device__ __forceinline__ int64_t uniform64(int64_t x) {
-  const int lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-  const int hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
-  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-}
-
-// Cost of document u against query q (one lane, 64 consecutive queries a
+// Cost of document [e0, e1) against a lane's query (64 consecutive queries a
 // wave): the non-zeros in order, kUnroll at a time with their first table
-// pairs loaded together; further pairs are loaded together for every
-// non-zero that still has mass.  Entries past a row's sink are never used:
-// the sink leaves no mass.  Every lane of the wave is on this document, so
-// its records and the table row offsets are wave-uniform (scalar loads and
-// arithmetic).
+// pairs loaded together.  Every lane of the wave is on this document, so its
+// records and the table rows' addresses are wave-uniform: ZP (the tables)
+// plus the word's row in scalar registers, `lane` (the query's byte offset)
+// in one vector register.  rbytes / pbytes: from one word's / pair's run to
+// the next.
+//
+// DEEP (KT > 2): the second pairs are loaded with the first ones (some lane
+// goes on for four of five non-zeros, and the walk then waits once, not
+// twice).  Their values count only for lanes with mass left -- a row that
+// ended in its first pair has no second one written.  Further pairs are
+// loaded for the lanes that need them; the others step over the pair they
+// hold, which changes nothing without mass.
+// Bound: the vector-memory path (2.6 loads of 16 bytes per non-zero and
+// query for image tables at KT = 8) beside as much scalar work, which is why
+// a row's address is one 64-bit product and sum and nothing but the further
+// pairs' loads branches.  Against the walk that loaded pair by pair and
+// tested the mass before every step: 20,000 images x 501 queries, KT = 8,
+// 3.47 -> 2.36 ms; 6,000 x 100 with background, KT = 16, 8.2 -> 1.32 ms, ICT
+// 56.6 -> 9.6 ms; text 18,000 x 500, KT = 16, 4.01 -> 3.50 ms.
+template <bool DEEP>
 __device__ __forceinline__ float doc_cost(int64_t e0, int64_t e1, const int2* __restrict__ xcv,
-                                          const float4* __restrict__ Zq, int64_t zw_nq, int KP) {
+                                          const char* __restrict__ ZP, uint32_t lane, uint32_t rbytes,
+                                          uint32_t pbytes, int KP) {
   static_assert(kUnroll == 8, "the group sum below is a tree over 8 terms");
   e0 = uniform64(e0);
   e1 = uniform64(e1);
-  const int64_t rstride = (int64_t)KP * zw_nq;  // float4s from one word's run to the next
   float t = 0.f, comp = 0.f;
-  for (int64_t e = e0; e < e1; e += kUnroll) {
-    const int cnt = (int)min((int64_t)kUnroll, e1 - e);
-    int2 cv[kUnroll];
-    if (cnt == kUnroll) {
+  auto records = [&](int64_t e, int2(&cv)[kUnroll]) {
+    if (e + kUnroll <= e1) {
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k) cv[k] = xcv[e + k];
     } else {
 #pragma unroll
-      for (int k = 0; k < kUnroll; ++k) cv[k] = k < cnt ? xcv[e + k] : make_int2(0, 0);
+      for (int k = 0; k < kUnroll; ++k) cv[k] = e + k < e1 ? xcv[e + k] : make_int2(0, 0);
     }
-    const float4* base[kUnroll];
-    float4 f[kUnroll];
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k) {
-      const int w = __builtin_amdgcn_readfirstlane(cv[k].x);
-      base[k] = Zq + (int64_t)w * rstride;
-      f[k] = k < cnt ? base[k][0] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+  };
+  int2 nx[kUnroll];
+  records(e0, nx);
+  for (int64_t e = e0; e < e1; e += kUnroll) {
+    const char* base[kUnroll];
+    float4 f[kUnroll], f2[DEEP ? kUnroll : 1];
     float rem[kUnroll], acc[kUnroll];
-    bool any = false;
 #pragma unroll
     for (int k = 0; k < kUnroll; ++k) {
-      rem[k] = __int_as_float(cv[k].y);  // 0 for the padding slots
+      // padding slots read word 0's run: their mass is 0
+      base[k] = ZP + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(nx[k].x) * rbytes;
+      rem[k] = __int_as_float(nx[k].y);
+      f[k] = *(const float4*)(base[k] + lane);
+      if constexpr (DEEP) f2[k] = *(const float4*)(base[k] + (lane + pbytes));
+    }
+    records(e + kUnroll, nx);  // the next group's, in flight through this one
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) {
       acc[k] = 0.f;
       step(rem[k], acc[k], f[k].x, f[k].y);
       step(rem[k], acc[k], f[k].z, f[k].w);
-      any = any || rem[k] > 0.f;
     }
-    for (int p = 1; any && p < KP; ++p) {
-#pragma unroll
-      for (int k = 0; k < kUnroll; ++k)
-        if (rem[k] > 0.f) f[k] = base[k][p * zw_nq];
-      any = false;
+    if constexpr (DEEP) {
+      float left = 0.f;
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k) {
-        if (rem[k] > 0.f) {
+        const bool on = rem[k] > 0.f;
+        f[k] = make_float4(on ? f2[k].x : 0.f, f2[k].y, on ? f2[k].z : 0.f, f2[k].w);
+        step(rem[k], acc[k], f[k].x, f[k].y);
+        step(rem[k], acc[k], f[k].z, f[k].w);
+        left = fmaxf(left, rem[k]);
+      }
+      for (int p = 2; p < KP && __any(left > 0.f); ++p) {
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+          if (rem[k] > 0.f) f[k] = *(const float4*)(base[k] + (lane + p * pbytes));
+        left = 0.f;
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k) {
           step(rem[k], acc[k], f[k].x, f[k].y);
-          if (rem[k] > 0.f) step(rem[k], acc[k], f[k].z, f[k].w);
-          any = any || rem[k] > 0.f;
+          step(rem[k], acc[k], f[k].z, f[k].w);
+          left = fmaxf(left, rem[k]);
         }
       }
     }
@@ -133,7 +139,9 @@ __device__ __forceinline__ float doc_cost(int64_t e0, int64_t e1, const int2* __
 // one 64-query group of 18,000 documents is only 1,125 items of 16 -- about
 // one wave per SIMD, each alone with its loads' latency.  The launcher
 // shortens items until the chip holds about 16 waves per CU (ICT, 64
-// queries: 1,355 -> 520 us).
+// queries: 1,355 -> 520 us) and an XCD's waves stay with one group's tables
+// (501 documents x 20,000 queries, KT = 8: 5.7 -> 3.6 ms).
+template <bool DEEP>
 __global__ __launch_bounds__(kThreads) void k_phase2_persistent(
     const int64_t* __restrict__ xptr, const int2* __restrict__ xcv, int64_t n,
     const float4* __restrict__ ZP, int64_t zw_nq, int KP, int64_t nq_arg, const int* __restrict__ nq_dev,
@@ -146,6 +154,7 @@ __global__ __launch_bounds__(kThreads) void k_phase2_persistent(
   const int64_t nd = (n + slots - 1) / slots;
   const int64_t total = (nq + QL - 1) / QL * nd;
   const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
+  const uint32_t pbytes = (uint32_t)zw_nq * 16u, rbytes = (uint32_t)KP * pbytes;  // (the launcher checks)
   while (true) {
     unsigned long long it = 0;
     if (lane == 0) it = atomicAdd(&counters[xcd], 1ull);
@@ -154,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void k_phase2_persistent(
     // lanes past the batch walk the last query's table and write nothing
     const int64_t q = (item / nd) * QL + lane;
     const bool qok = q < nq;
-    const float4* Zq = ZP + (qok ? q : nq - 1);
+    const uint32_t zq = (uint32_t)(qok ? q : nq - 1) * 16u;
     const int64_t d0 = (item % nd) * slots;
     // one document at a time for all 64 lanes: each lane's results are
     // consecutive in its query's row, so they are staged in the wave's own
@@ -166,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void k_phase2_persistent(
     for (int j = 0; j < slots; ++j) {
       const int64_t i = d0 + j;
       if (i >= n) break;
-      sw[j][lane] = doc_cost(xptr[i], xptr[i + 1], xcv, Zq, zw_nq, KP);
+      sw[j][lane] = doc_cost<DEEP>(xptr[i], xptr[i + 1], xcv, (const char*)ZP, zq, rbytes, pbytes, KP);
       ++cnt;
     }
     if (qok && cnt > 0) {
@@ -342,18 +351,22 @@ int persistent_grid(const void* fn, int threads, size_t shmem, int64_t items) {
   return (int)grid;
 }
 
+template <bool DEEP>
 static hipError_t launch_p2_wide(const int64_t* xptr, const int2* xcv, int64_t n, const float2* ZW, int64_t zw_nq,
                                  int KT, int64_t nq, const int* nq_dev, float* out, int64_t ld,
                                  unsigned long long* counters, hipStream_t s) {
+  // the kernel's 32-bit offsets (tiles hold at most 16,384 queries and 512 pairs)
+  if (zw_pairs(KT) * zw_nq * 16 >= (int64_t(1) << 32)) return hipErrorInvalidValue;
   // documents per item: the longest of 16, 8, 4 that leaves about 16 waves
-  // per CU (256 CUs)
+  // per CU (256 CUs), and, an XCD holding about 512 waves, no more than one
+  // query group's tables in use on an XCD at a time
   int slots = kItemSlots;
-  while (slots > 4 && (nq + 63) / 64 * ((n + slots - 1) / slots) < 4096) slots /= 2;
+  while (slots > 4 && ((nq + 63) / 64 * ((n + slots - 1) / slots) < 4096 || (n + slots - 1) / slots < 512)) slots /= 2;
   // waves needed at most (bounds the grid)
   const int64_t items = (nq + 63) / 64 * ((n + slots - 1) / slots);
-  const int grid = persistent_grid((const void*)k_phase2_persistent, kThreads, 0, (items + 3) / 4);
+  const int grid = persistent_grid((const void*)k_phase2_persistent<DEEP>, kThreads, 0, (items + 3) / 4);
   if (grid <= 0) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(k_phase2_persistent, dim3(grid), dim3(kThreads), 0, s, xptr, xcv, n, (const float4*)ZW, zw_nq,
+  hipLaunchKernelGGL(k_phase2_persistent<DEEP>, dim3(grid), dim3(kThreads), 0, s, xptr, xcv, n, (const float4*)ZW, zw_nq,
                      (int)zw_pairs(KT), nq, nq_dev, slots, out, ld, counters);
   return hipGetLastError();
 }
@@ -391,7 +404,10 @@ hipError_t launch_phase2_persistent(const int64_t* xptr, const int2* xcv, int64_
   for (int ql = top; ql >= (nq_dev ? 1 : top); ql /= 2) {
     const int64_t qmax = ql == top ? nq : std::min<int64_t>(nq, ql);  // the most queries this width takes
     switch (ql) {
-      case 64: e = launch_p2_wide(xptr, xcv, n, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s); break;
+      case 64:
+        e = KT > 2 ? launch_p2_wide<true>(xptr, xcv, n, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s)
+                   : launch_p2_wide<false>(xptr, xcv, n, ZW, zw_nq, KT, qmax, nq_dev, out, ld, counters, s);
+        break;
       case 32: e = launch_p2_small<32>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
       case 16: e = launch_p2_small<16>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
       case 8: e = launch_p2_small<8>(xptr, xcv, n, perm, ZW, zw_nq, KT, qmax, nq_dev, out, ld, s); break;
