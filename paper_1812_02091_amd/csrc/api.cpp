@@ -515,7 +515,10 @@ int d2q_phase2(lcemd_ctx* c, const DbView& db, int64_t q0, int64_t nq, int KT, c
                                         ZW + 2 * 64 * g, zw_nq, KT, cost, out + (q0 + 64 * g) * ld, ld, p2c,
                                         c->stream));
   }
-  if (nq > 64 * ng)
+  if (ng == 0 && c->p2_mode != 2 && phase2_lds_fits(db.n, db.v_used, KT, nq))
+    HIPCHK(c, launch_phase2_lds(db.xptr, db.xcv, db.n, db.perm, db.v_used, ZW, zw_nq, KT, nq, out + q0 * ld, ld,
+                                c->stream));
+  else if (nq > 64 * ng)
     HIPCHK(c, launch_phase2_persistent(db.xptr, db.xcv, db.n, db.perm, ZW + 2 * 64 * ng, zw_nq, KT, nq - 64 * ng,
                                        nullptr, out + (q0 + 64 * ng) * ld, ld, p2c, c->stream));
   if ((rc = prof_end(c))) return rc;

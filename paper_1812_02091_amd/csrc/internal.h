@@ -212,6 +212,14 @@ hipError_t launch_phase2_wordmajor(const int64_t* xptr, int64_t n, const int64_t
                                    const uint32_t* winv, int64_t nnz, int64_t v_used, const float2* ZW,
                                    int64_t zw_nq, int KT, float* cost, float* out, int64_t ld,
                                    unsigned long long* counters, hipStream_t s);
+// Phase 2 with the tables of 8 or 16 queries in LDS (phase2_lds.hip): small
+// vocabularies, batches of more than 32 queries with enough windows of 128
+// documents to fill the chip.  perm: the documents in order of length within
+// windows of 128.
+bool phase2_lds_fits(int64_t n, int64_t v_used, int KT, int64_t nq);
+hipError_t launch_phase2_lds(const int64_t* xptr, const int2* xcv, int64_t n, const int32_t* perm, int64_t v_used,
+                             const float2* ZW, int64_t zw_nq, int KT, int64_t nq, float* out, int64_t ld,
+                             hipStream_t s);
 hipError_t launch_phase2_persistent(const int64_t* xptr, const int2* xcv, int64_t n, const int32_t* perm,
                                     const float2* ZW, int64_t zw_nq, int KT, int64_t nq,
                                     const int* nq_dev, float* out, int64_t ld,
