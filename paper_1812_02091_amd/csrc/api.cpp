@@ -320,13 +320,15 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
     HIPCHK(c, launch_phase1_bf16(a, mode, depth, c->stream));
     return LCEMD_OK;
   }
-  // float32 with at most 28 dims (image coordinates): the 64-row kernel,
-  // whose row blocks waste less of ~160-word histograms and whose exact keys
-  // need no redo of rows with tied grid distances.  Not for ICT tables: the
-  // 128-row kernel redoes rows deeper than their list one by one, where the
-  // 64-row kernel can only report overflow (and the tables are rebuilt at
-  // full depth)
-  const bool small_m = prec == LCEMD_FP32 && a.m4 <= 7 && !(mode == P1_TABLE && a.method == LCEMD_ICT);
+  if (prec == LCEMD_FP32 && mode != P1_PAIR && depth <= 32 && !c->force_kernel) {
+    a.KT_margin = 0;
+    a.rb_max = 0;
+    HIPCHK(c, launch_phase1_rows(a, mode, depth, c->stream));
+    return LCEMD_OK;
+  }
+  // pairs with at most 28 dims (image coordinates): the 64-row kernel, whose
+  // row blocks waste less of ~160-word histograms
+  const bool small_m = prec == LCEMD_FP32 && a.m4 <= 7;
   if (depth + margin <= 32 && !c->force_kernel && !small_m) {
     const int KL = pow2ceil(depth + margin);
     a.KT_margin = margin;

@@ -150,6 +150,9 @@ __device__ __forceinline__ void zw_write_row(float2* ZW, int64_t zw_nq, int KT, 
 hipError_t launch_phase1_deep(const P1Args& a, int mode, int hmax, int prec, hipStream_t s);
 hipError_t launch_phase1_fast(const P1Args& a, int mode, int KT, int prec, hipStream_t s);
 hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, int prec, int seg_hmax, hipStream_t s);
+// float32 table modes, lists of up to 32 entries, segments of up to
+// LCEMD_MAX_HIST words
+hipError_t launch_phase1_rows(const P1Args& a, int mode, int depth, hipStream_t s);
 // bfloat16 table modes (lists of depth + 8 <= 32, segments <= kSegShort words,
 // rows of at most kBf16MaxDims dims)
 bool phase1_bf16_fits(int mb, int seg_hmax, int depth);

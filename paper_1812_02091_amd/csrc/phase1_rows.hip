@@ -1,0 +1,487 @@
+// Phase 1 of LC-ACT (Sec. 4, Phase 1) with float32 keys, table modes, lists
+// of up to 32 entries: per (vocabulary row, query) the nearest query words of
+// Alg. 3 and their capacities.
+//
+// Bound: the float32 MFMA (157 TFLOP/s; 134-150 in a loop of nothing but
+// MFMAs and their LDS reads; here the pipe is busy 74 % of the time at 128
+// words).  Float32 MFMAs and vector instructions hardly run side by side on a
+// SIMD, so every vector instruction adds to the contraction's time, and
+// keeping them few is what this kernel is about.
+//
+// Contraction: a workgroup of four waves takes 128 vocabulary rows against
+// one query; wave w owns rows 32w .. 32w + 31.  The rows are the MFMA's N
+// operand (each lane reads its row's dims straight from global memory, a
+// 32-dim slice ahead), the query's words its M operand (a slice of 128 words
+// staged in LDS for the four waves), so that after a pass a lane holds 64
+// keys of its own row -- words 32 t + 8 (r / 4) + 4 (lane / 32) + r % 4 -- in
+// its accumulators.
+//
+// Selection: in registers.  A key and its word's position make one 64-bit
+// number that orders by (key, position), compared as float64 (the key's bits
+// on top; positions complemented under negative keys): a compare-exchange is
+// v_min_f64 + v_max_f64.  Each 16 keys go through a sorting network and are
+// merged into the lane's sorted list, the two lanes of a row merge theirs at
+// the end.  No branch, no LDS, and the list is exactly the row's LK smallest:
+// nothing has to be certified or redone but ICT rows deeper than the list.
+// The kernel this replaced put every key through LDS (two barriers per 64
+// words) and merged lists held there entry by entry with a band for quantised
+// keys.  62,000 words x 300 dims x 250 queries of ~118 words: RWMD 17.0 ->
+// 13.6 ms, k = 8 20.5 -> 14.6, k = 16 22.4 -> 15.0; 784 grid words x 20,000
+// images, k = 8, 7.7 -> 2.9 ms.
+//
+// Distances: |v|^2 + key unless cancellation could bite (below a quarter of
+// |v|^2 + |c|^2), where it is recomputed by direct differences (identical
+// words give exactly 0).
+#include <algorithm>
+
+#include "internal.h"
+
+namespace lcemd {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+namespace {
+
+constexpr int kFR = 128;        // rows per workgroup
+constexpr int kFC = 128;        // words per pass
+constexpr int kFStride = 144;   // bytes per staged word slice (128 + 16 pad: conflict-free 16-byte reads)
+constexpr int kFSeg = LCEMD_MAX_HIST;
+constexpr float kFGuard = 0.25f;
+constexpr uint32_t kNoKey = 0x7f800000u;  // +inf: above every key
+
+struct F32Smem {
+  unsigned char st[2][kFC * kFStride];  // word slices, double-buffered
+  int cid[kFSeg + kFC];   // word 0 past the query's words, up to a pass's end
+  float cap[kFSeg + kFC];
+  float qn[kFSeg + kFC];  // +inf there: those keys are above every key
+};
+
+// queries per item group: 8, or 32 over vocabularies of at least 2^18 used
+// words, where a row block's vectors are reused by more items before they
+// leave L2 (1M words: phase 1 -2 %; 70,000 words: 8 keeps a group's query
+// vectors within an XCD's L2)
+__host__ __device__ inline int f32_group_log2(int64_t v_used) { return v_used >= (int64_t(1) << 18) ? 5 : 3; }
+
+__device__ __forceinline__ double dmin(double a, double b) {
+  double d;
+  asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ double dmax(double a, double b) {
+  double d;
+  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ void cas(double& a, double& b) {
+  const double x = a, y = b;
+  a = dmin(x, y);
+  b = dmax(x, y);
+}
+
+// Batcher's odd-even merge sort of N (a power of two) keys at k[0 .. N)
+template <int N>
+__device__ __forceinline__ void net_sort(double* k) {
+#pragma unroll
+  for (int p = 1; p < N; p <<= 1)
+#pragma unroll
+    for (int q = p; q >= 1; q >>= 1)
+#pragma unroll
+      for (int j = q % p; j + q < N; j += 2 * q)
+#pragma unroll
+        for (int i = 0; i < q; ++i)
+          if (i + j + q < N && (i + j) / (2 * p) == (i + j + q) / (2 * p)) cas(k[i + j], k[i + j + q]);
+}
+
+// a (ascending, LK) := the LK smallest of a and b (ascending, NB <= LK)
+template <int LK, int NB>
+__device__ __forceinline__ void net_merge(double* a, const double* b) {
+#pragma unroll
+  for (int i = 0; i < NB; ++i) a[LK - 1 - i] = dmin(a[LK - 1 - i], b[i]);
+  // bitonic now
+#pragma unroll
+  for (int h = LK >> 1; h > 0; h >>= 1)
+#pragma unroll
+    for (int i = 0; i < LK; ++i)
+      if ((i & h) == 0) cas(a[i], a[i + h]);
+}
+
+// The tile's 16 keys into the lane's list.
+template <int LK>
+__device__ __forceinline__ void take16(double (&lst)[LK], double (&k)[16]) {
+  if constexpr (LK == 1) {
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+      for (int i = 0; i < h; ++i) k[i] = dmin(k[i], k[i + h]);
+    lst[0] = dmin(lst[0], k[0]);
+  } else if constexpr (LK >= 16) {
+    net_sort<16>(k);
+    net_merge<LK, 16>(lst, k);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; i += LK) net_sort<LK>(k + i);
+#pragma unroll
+    for (int w = LK; w < 16; w <<= 1)
+#pragma unroll
+      for (int i = 0; i < 16; i += 2 * w) net_merge<LK, LK>(k + i, k + i + w);
+    net_merge<LK, LK>(lst, k);
+  }
+}
+
+// Squared distance by direct differences over the m4 float4 groups that
+// hold the real dims.  FOUR: four partial sums over pairs of groups (at most
+// 28 dims), else one sum.
+template <bool FOUR>
+__device__ __forceinline__ float f32_exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b) {
+  const float4* x = (const float4*)(V + (size_t)a * m_pad);
+  const float4* y = (const float4*)(V + (size_t)b * m_pad);
+  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+  const int n4 = FOUR ? (m4 + 1) & ~1 : m4;  // (m_pad / 4 is even; the padding adds exact zeros)
+  for (int d = 0; d < n4; ++d) {
+    const float4 p = x[d], q = y[d];
+    const float e0 = p.x - q.x, e1 = p.y - q.y, e2 = p.z - q.z, e3 = p.w - q.w;
+    if constexpr (FOUR) {
+      s0 = fmaf(e0, e0, s0);
+      s1 = fmaf(e1, e1, s1);
+      s2 = fmaf(e2, e2, s2);
+      s3 = fmaf(e3, e3, s3);
+    } else {
+      s0 = fmaf(e0, e0, s0);
+      s0 = fmaf(e1, e1, s0);
+      s0 = fmaf(e2, e2, s0);
+      s0 = fmaf(e3, e3, s0);
+    }
+  }
+  return FOUR ? (s0 + s1) + (s2 + s3) : s0;
+}
+
+// One staged slice on NT 32-word tiles (NT fixed at compile time so the
+// MFMAs issue back to back without branches); the first njq of its four
+// groups of MFMAs (the others hold no real dims and would add exact zeros).
+template <int NT, bool FULL>
+__device__ __forceinline__ void f32_slice(floatx16 (&acc)[NT], const float4 (&rows)[4], const unsigned char* st, int li,
+                                          int lh, int njq) {
+  // lane half lh supplies dims [16 lh, 16 lh + 16) of the 32-dim slice
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (!FULL && j >= njq) break;
+    float4 wv[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      wv[t] = *(const float4*)(st + (32 * t + li) * kFStride + lh * 64 + j * 16);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[t].x, rows[j].x, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[t].y, rows[j].y, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[t].z, rows[j].z, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[t].w, rows[j].w, acc[t], 0, 0, 0);
+  }
+}
+
+// What a thread has in flight: the lane's row's next slice, and the pieces of
+// the words' next slice that it stages (word 32 it + tid / 8, piece tid % 8).
+struct Flight {
+  const unsigned char* rptr;
+  const unsigned char* wptr[4];
+  float4 r[4];
+  float4 w[4];
+  template <int NT>
+  __device__ __forceinline__ void words(const unsigned char* vb, size_t rowbytes, const int* cid, int tid) {
+#pragma unroll
+    for (int it = 0; it < NT; ++it) wptr[it] = vb + (size_t)cid[32 * it + (tid >> 3)] * rowbytes + (tid & 7) * 16;
+  }
+  __device__ __forceinline__ void load_rows(int sl) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = *(const float4*)(rptr + sl * 128 + i * 16);
+  }
+  template <int NT>
+  __device__ __forceinline__ void load_words(int sl) {
+#pragma unroll
+    for (int it = 0; it < NT; ++it) w[it] = *(const float4*)(wptr[it] + sl * 128);
+  }
+  template <int NT>
+  __device__ __forceinline__ void load(int sl) {
+    load_rows(sl);
+    load_words<NT>(sl);
+  }
+};
+
+// One pass: NT tiles of words from c0 on, all slices, then their keys into
+// the list.  A pass is a function of its own tile count so that the
+// accumulators stay in the same registers throughout (a switch inside the
+// slice loop had them copied, 200 moves a slice).
+template <int NT, int LK, bool SMALL>
+__device__ __forceinline__ void f32_pass(F32Smem& sm, Flight& fl, double (&lst)[LK], int c0, bool more, int nsl,
+                                         int last_njq, const unsigned char* vb, size_t rowbytes, int tid) {
+  const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  floatx16 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+  float4 rows[4];
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int it = 0; it < NT; ++it)
+      *(float4*)(sm.st[buf] + (32 * it + (tid >> 3)) * kFStride + (tid & 7) * 16) = fl.w[it];
+  };
+  auto take_rows = [&]() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rows[i] = fl.r[i];
+  };
+  // (one barrier a slice; two, with one buffer, took the same time)
+  __syncthreads();  // the previous pass's slices are consumed
+  stage(0);
+  take_rows();
+  if constexpr (!SMALL) {
+    if (nsl > 1) fl.load<NT>(1);
+    __syncthreads();
+    for (int sl = 0; sl < nsl - 1; ++sl) {
+      stage((sl + 1) & 1);  // (last read a slice ago, before the barrier)
+      if (sl + 2 < nsl) fl.load_words<NT>(sl + 2);
+      f32_slice<NT, true>(acc, rows, sm.st[sl & 1], li, lh, 4);
+      take_rows();
+      if (sl + 2 < nsl) fl.load_rows(sl + 2);
+      __syncthreads();
+    }
+  } else {
+    __syncthreads();
+  }
+  if (more) {  // the next pass's first slice (it has at most NT tiles)
+    fl.words<NT>(vb, rowbytes, sm.cid + c0 + 32 * NT, tid);
+    fl.load<NT>(0);
+  }
+  f32_slice<NT, false>(acc, rows, sm.st[SMALL ? 0 : (nsl - 1) & 1], li, lh, last_njq);
+
+  // ---- selection: 16 keys of the lane's row per tile ----
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int pbase = (c0 + 32 * t) | (lh << 2);  // position bits that the 16 keys share
+    double k[16];
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      const float4 qn = *(const float4*)(sm.qn + c0 + 32 * t + 8 * rq + 4 * lh);
+      const float qv[4] = {qn.x, qn.y, qn.z, qn.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int bits = __float_as_int(qv[i] - 2.f * acc[t][4 * rq + i]);
+        k[4 * rq + i] = __hiloint2double(bits, (bits >> 31) ^ (pbase | (8 * rq + i)));
+      }
+    }
+    take16<LK>(lst, k);
+  }
+}
+
+// One work item: (query, 128-row block).  Returns early (uniformly) for
+// empty items.
+template <int MODE, int LK, bool SMALL>
+__device__ __forceinline__ void f32_task(const P1Args& a, F32Smem& sm, int64_t item) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 31, lh = lane >> 5;
+  constexpr bool kCapStop = MODE != P1_TABLE_FULL;
+
+  // items run query-fastest within a group of queries, then row block, then
+  // group: an XCD's contiguous range of items keeps a group's query vectors
+  // and a row block's vectors in its L2
+  const int64_t nrb = (a.v_used + kFR - 1) / kFR;
+  const int lg = f32_group_log2(a.v_used);
+  const int64_t t0 = item >> lg;
+  const int64_t rblk = t0 % nrb, qi = ((t0 / nrb) << lg) + (item & ((int64_t(1) << lg) - 1));
+  if (qi >= a.nq) return;
+  const int64_t r0 = rblk * kFR;
+  const int64_t s0 = a.qptr[a.q0 + qi];
+  const int h = (int)(a.qptr[a.q0 + qi + 1] - s0);
+  if (h <= 0) return;  // padding slot of a fixed-size batch
+  const int64_t r = r0 + 32 * wave + li;  // the lane's row (both halves)
+  const bool row_ok = r < a.v_used;
+  const int rid = row_ok ? a.used[r] : a.used[r0];
+  for (int c = tid; c < h + kFC; c += kThreads) {
+    const int w = c < h ? a.qcol[s0 + c] : 0;
+    sm.cid[c] = w;
+    sm.cap[c] = c < h ? a.qval[s0 + c] : 0.f;
+    sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
+  }
+  const float rvn = a.vnorm[rid];
+  const float bound = MODE == P1_TABLE ? (row_ok ? a.xmax[r] : 0.f) : INFINITY;
+  __syncthreads();
+
+  int kef;
+  if constexpr (MODE == P1_TABLE_FULL) {
+    kef = min(a.k, h);
+  } else {
+    if (a.method == LCEMD_ICT) kef = h;
+    else if (a.method == LCEMD_OMR) kef = min(2, h);
+    else if (a.method == LCEMD_RWMD) kef = 1;
+    else kef = min(a.k, h);
+  }
+
+  // ---------------- contraction ----------------
+  const size_t rowbytes = (size_t)a.m_pad * 4;
+  const int nsl = SMALL ? 1 : (a.m4 + 7) >> 3;  // 32-dim slices that hold real dims
+  const int last_njq = min(4, a.m4 - 8 * (nsl - 1));
+  const unsigned char* vb = (const unsigned char*)a.V;
+  double lst[LK];
+#pragma unroll
+  for (int i = 0; i < LK; ++i) lst[i] = __hiloint2double((int)kNoKey, 0);
+  // passes of at most four tiles, as even as they come (a pass of one tile
+  // costs its barriers and latencies like one of four), longer ones first
+  const int nt = (h + 31) >> 5, npass = (nt + 3) >> 2, base = nt / npass, extra = nt % npass;
+  Flight fl;
+  fl.rptr = vb + (size_t)rid * rowbytes + lh * 64;
+  fl.words<4>(vb, rowbytes, sm.cid, tid);
+  fl.load<4>(0);
+  int c0 = 0;
+  for (int p = 0; p < npass; ++p) {
+    const int n = base + (p < extra ? 1 : 0);
+    const bool more = p + 1 < npass;
+    switch (n) {
+      case 1: f32_pass<1, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
+      case 2: f32_pass<2, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
+      case 3: f32_pass<3, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
+      default: f32_pass<4, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
+    }
+    c0 += 32 * n;
+  }
+
+  // ---------------- the row's list: merge of its two lanes ----------------
+  {
+    double other[LK];
+#pragma unroll
+    for (int i = 0; i < LK; ++i)
+      other[i] = __hiloint2double(__shfl_xor(__double2hiint(lst[i]), 32), __shfl_xor(__double2loint(lst[i]), 32));
+    net_merge<LK, LK>(lst, other);
+  }
+
+  // ---------------- distances, cut, outputs ----------------
+  // both lanes of a row do the same arithmetic and share the stores
+  float z[LK], w[LK];
+  int pos[LK];
+  int D = 0;
+  bool covered = false;
+  float Pc = 0.f;
+#pragma unroll
+  for (int l = 0; l < LK; ++l) {
+    z[l] = 0.f;
+    w[l] = 0.f;
+    pos[l] = 0;
+    const int bits = __double2hiint(lst[l]);
+    const bool live = row_ok && !covered && bits != (int)kNoKey;
+    if (!__any(live)) continue;
+    if (live) {
+      pos[l] = __double2loint(lst[l]) ^ (bits >> 31);
+      const float qn = sm.qn[pos[l]];
+      float d2 = rvn + __int_as_float(bits);
+      bool need = !(d2 >= kFGuard * (rvn + qn));
+      if (kCapStop && a.method == LCEMD_OMR && l == 0) need = true;
+      if (need) d2 = f32_exact_d2<SMALL>(a.V, a.m_pad, a.m4, rid, sm.cid[pos[l]]);
+      z[l] = sqrtf(fmaxf(d2, 0.f));
+      w[l] = sm.cap[pos[l]];
+      ++D;
+      Pc += w[l];
+      covered = D >= kef;
+      if (kCapStop) covered = covered || Pc >= bound || (a.method == LCEMD_OMR && l == 0 && d2 != 0.f);
+    }
+  }
+  if (!row_ok) return;  // (no barrier past this point)
+  // an ICT row deeper than the list: redone exactly by k_fix_rows while the
+  // redo list has room, else the launch reports overflow
+  if (!covered && D < h && lh == 0) {
+    if (a.fix_list) {
+      const int slot = atomicAdd(a.fix_count, 1);
+      if (slot < a.fix_cap) a.fix_list[slot] = qi * a.v_used + r;
+      else if (a.overflow) a.overflow[0] = 1;
+    } else if (a.overflow) {
+      a.overflow[0] = 1;
+    }
+  }
+  if constexpr (MODE == P1_TABLE) {
+    if (D > a.KT && a.overflow) a.overflow[0] = 1;
+#pragma unroll
+    for (int l = 0; l < LK; l += 2) {
+      if (((l >> 1) & 1) == lh && l < D && l < a.KT) {
+        constexpr int kOdd = LK > 1 ? 1 : 0;  // (LK = 1: a row has one entry)
+        const bool two = kOdd && l + 1 < D && l + 1 < a.KT;
+        *zw_pair(a.ZW, a.zw_nq, a.KT, qi, r, l >> 1) =
+            make_float4(z[l], l == D - 1 ? INFINITY : w[l], two ? z[l + kOdd] : 0.f,
+                        two ? (l + 1 == D - 1 ? INFINITY : w[l + kOdd]) : 0.f);
+      }
+    }
+  } else {
+    const int64_t o0 = (qi * a.v_used + r) * (int64_t)a.k;
+#pragma unroll
+    for (int l = 0; l < LK; ++l) {
+      if ((l & 1) == lh && l < a.k) {
+        const bool in = l < D;
+        a.S[o0 + l] = in ? pos[l] : -1;
+        a.Z[o0 + l] = in ? z[l] : 0.f;
+        a.W[o0 + l] = in ? w[l] : 0.f;
+      }
+    }
+  }
+}
+
+// Persistent grid: as many workgroups as stay resident, each pulling items
+// from the counter of its XCD (workgroup i runs on XCD i % 8), which walks a
+// contiguous eighth of the items; the counter is read one item ahead.  Every
+// workgroup exits once its counter passes the end of its range.
+template <int MODE, int LK, bool SMALL>
+__global__ __launch_bounds__(kThreads, 2) void k_phase1_rows(P1Args a, int64_t total) {
+  __shared__ F32Smem sm;
+  __shared__ int64_t s_item;
+  const int xcd = blockIdx.x & 7;
+  const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
+  unsigned long long nxt = 0;
+  if (threadIdx.x == 0) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+  while (true) {
+    __syncthreads();  // the previous item is done with LDS and s_item
+    if (threadIdx.x == 0) {
+      s_item = lo + (int64_t)nxt;
+      if (lo + (int64_t)nxt < hi) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+    }
+    __syncthreads();
+    const int64_t item = s_item;
+    if (item >= hi) break;
+    f32_task<MODE, LK, SMALL>(a, sm, item);
+  }
+}
+
+template <int MODE, int LK, bool SMALL>
+hipError_t launch_f32_one(const P1Args& a, hipStream_t s) {
+  const int64_t nrb = (a.v_used + kFR - 1) / kFR;
+  const int64_t gw = int64_t(1) << f32_group_log2(a.v_used);
+  const int64_t total = (a.nq + gw - 1) / gw * nrb * gw;
+  if (total <= 0) return hipSuccess;
+  if (!a.work_ctr) return hipErrorInvalidValue;
+  hipError_t e = launch_zero_ints((int*)a.work_ctr, 16, s);
+  if (e != hipSuccess) return e;
+  const int grid = persistent_grid((const void*)k_phase1_rows<MODE, LK, SMALL>, kThreads, 0, total);
+  if (grid <= 0) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL((k_phase1_rows<MODE, LK, SMALL>), dim3(grid), dim3(kThreads), 0, s, a, total);
+  return hipGetLastError();
+}
+
+template <int MODE, bool SMALL>
+hipError_t launch_f32_list(const P1Args& a, int depth, hipStream_t s) {
+  if (depth <= 1) return launch_f32_one<MODE, 1, SMALL>(a, s);
+  if (depth <= 2) return launch_f32_one<MODE, 2, SMALL>(a, s);
+  if (depth <= 4) return launch_f32_one<MODE, 4, SMALL>(a, s);
+  if (depth <= 8) return launch_f32_one<MODE, 8, SMALL>(a, s);
+  if (depth <= 16) return launch_f32_one<MODE, 16, SMALL>(a, s);
+  if (depth <= 32) return launch_f32_one<MODE, 32, SMALL>(a, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_phase1_rows(const P1Args& a, int mode, int depth, hipStream_t s) {
+  const bool small = a.m4 <= 7;  // at most 28 dims: one slice
+  if (mode == P1_TABLE)
+    return small ? launch_f32_list<P1_TABLE, true>(a, depth, s) : launch_f32_list<P1_TABLE, false>(a, depth, s);
+  if (mode == P1_TABLE_FULL)
+    return small ? launch_f32_list<P1_TABLE_FULL, true>(a, depth, s) : launch_f32_list<P1_TABLE_FULL, false>(a, depth, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace lcemd

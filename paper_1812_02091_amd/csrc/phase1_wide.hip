@@ -20,13 +20,9 @@
 //
 // Exact distances: float32 keys -- the list distance is |v|^2 + key unless
 // cancellation could bite (below a quarter of |v|^2 + |c|^2), where it is
-// recomputed by direct differences.  bfloat16 keys -- every bf16-rounded
-// product is within 2^-8 of the exact one, so a key is off by at most
-// 2^-7 * 1.0625 * |v||c| (float32 accumulation included for m <= 4096);
-// the list therefore keeps, past the cut, every candidate whose key is
-// within 2^-6 * 1.07 * |v| * max|c| of the cut key: in exact order nothing
-// outside that band can precede the cut.  All listed candidates then get
-// float32 distances -- |v|^2 + |c|^2 - 2<v, c> with the dot product
+// recomputed by direct differences.  fp8 keys -- the list keeps, past the
+// cut, every candidate within a statistical band of the cut key.  All listed
+// candidates then get float32 distances -- |v|^2 + |c|^2 - 2<v, c> with the dot product
 // accumulated in float32 over the original vectors (staged through LDS a
 // chunk of dims at a time), or by direct differences where cancellation
 // could bite, as for float32 keys -- and are re-sorted and cut again.
@@ -37,7 +33,6 @@
 namespace lcemd {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 namespace {
 
@@ -48,24 +43,12 @@ constexpr int kCK = 66;         // floats per key row (64 columns + 2 pad)
 constexpr int kQSCap = kWR * kCK;  // floats of the staging area (the key buffer's size)
 constexpr int kSeg = kSegShort;            // segment words held in LDS (short variant)
 constexpr int kSegLong = LCEMD_MAX_HIST;   // long variant (float32 keys)
-// queries per tile group (table modes): 8, or 32 with float32 keys over
-// vocabularies of at least 2^18 used words, where a row block's vectors are
-// reused by more items before they leave L2 (1M words: phase 1 -2 %; with
-// fp8 keys 32 was 3 % slower; 70,000 words: 8 keeps a group's query vectors
-// within an XCD's L2)
-__host__ __device__ inline int wide_group_log2(int64_t v_used, int prec) {
-  return prec == PREC_F32 && v_used >= (int64_t(1) << 18) ? 5 : 3;
-}
+constexpr int kWGroupLog2 = 3;  // queries per item group (table modes; 32 was 3 % slower at 1M words)
 constexpr float kGuardW = 0.25f;
-constexpr float kBandBF16 = 0.015625f * 1.07f;  // 2^-6 * 1.07
 // fp8 (e4m3, 3 mantissa bits): a statistical band, not a worst-case one --
 // about six standard deviations of the key error of a few-hundred-term dot
 // product with independent relative rounding errors of at most 2^-4
 constexpr float kBandFP8 = 0.04f;
-template <int PREC>
-__device__ __forceinline__ float band_coef() {
-  return PREC == PREC_F32 ? 0.f : (PREC == PREC_BF16 ? kBandBF16 : kBandFP8);
-}
 
 __device__ __forceinline__ uint32_t w_bits(float f) {
   const uint32_t u = __float_as_uint(f);
@@ -86,13 +69,12 @@ __device__ __forceinline__ uint64_t w_shfl1(uint64_t v) {
 }
 
 // Selection keys.  Exact keys: (order-preserving key bits, position) in 64
-// bits (float32 pair mode).  Quantised keys (the table modes): the key's PB
-// low bits give way to the position (9 bits for segments of up to 512
-// words, 10 up to 1024), one 32-bit word, rounded down in value by at most
+// bits (float32 pair mode).  Quantised keys (fp8 tables): the key's PB low
+// bits give way to the position (9 bits: segments of up to 512 words), one
+// 32-bit word, rounded down in value by at most
 // 2^(PB-23) of the key's magnitude; lists keep every entry within twice
 // that band past their cut and are re-sorted afterwards by the exact keys
-// (float32: the contraction's key, kept beside the list; bf16/fp8: the
-// recomputed distances).
+// (the recomputed distances).
 template <bool QK, int PB = 9>
 struct KeyOps {
   using T = uint32_t;
@@ -162,21 +144,6 @@ __device__ __forceinline__ void slice_f32(floatx16 (&acc)[4], const uint4 (&a_cu
 }
 
 template <int NT>
-__device__ __forceinline__ void slice_bf16(floatx16 (&acc)[4], const uint4 (&a_cur)[4],
-                                           const unsigned char* st, int li, int lh) {
-  // lane half lh supplies dims [32 lh + 8 s, +8) of the 64-dim slice
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const bf16x8 av = *reinterpret_cast<const bf16x8*>(&a_cur[s]);
-    bf16x8 bv[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) bv[t] = *(const bf16x8*)(st + (32 * t + li) * kStride + lh * 64 + s * 16);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv[t], acc[t], 0, 0, 0);
-  }
-}
-
-template <int NT>
 __device__ __forceinline__ void slice_fp8(floatx16 (&acc)[4], const uint4 (&a_cur)[4],
                                           const unsigned char* st, int li, int lh) {
   // lane half lh supplies dims [64 lh + 8 s, +8) of the 128-dim slice
@@ -201,13 +168,6 @@ __device__ __forceinline__ void slice_mfma(int ntile, floatx16 (&acc)[4], const 
       case 3: slice_f32<3>(acc, a_cur, st, li, lh); break;
       default: slice_f32<4>(acc, a_cur, st, li, lh); break;
     }
-  } else if constexpr (PREC == PREC_BF16) {
-    switch (ntile) {
-      case 1: slice_bf16<1>(acc, a_cur, st, li, lh); break;
-      case 2: slice_bf16<2>(acc, a_cur, st, li, lh); break;
-      case 3: slice_bf16<3>(acc, a_cur, st, li, lh); break;
-      default: slice_bf16<4>(acc, a_cur, st, li, lh); break;
-    }
   } else {
     switch (ntile) {
       case 1: slice_fp8<1>(acc, a_cur, st, li, lh); break;
@@ -218,9 +178,9 @@ __device__ __forceinline__ void slice_mfma(int ntile, floatx16 (&acc)[4], const 
   }
 }
 
-template <int KL, int PREC, bool QK, bool EX, int SEG = kSeg>
+template <int KL, int PREC, bool QK, int SEG = kSeg>
 struct WideSmem {
-  static constexpr int KLS = KL + 1 + (EX ? 1 : 0);  // list row stride (odd or +1: spreads rows over banks)
+  static constexpr int KLS = KL + 1;  // list row stride (spreads rows over banks)
   union {
     unsigned char st[kWC * kStride];  // staged column slice
     float ck[kWR * kCK];              // keys of 64 columns of a pass
@@ -228,7 +188,6 @@ struct WideSmem {
     float zb[kWR * KLS];              // exact squared distances of the lists
   } u;
   typename KeyOps<QK>::T lst[2][kWR * KLS];
-  float lkx[EX ? 2 : 1][EX ? kWR * KLS : 1];  // float32 quantised keys: the exact keys beside the list
   int cid[SEG];
   float cap[SEG];
   float qn[SEG];
@@ -291,15 +250,13 @@ __device__ __forceinline__ void wide_dots(float (&ex)[KH], const int (&ps)[KH], 
 // block) in pair mode.  Returns early (uniformly) for empty items.
 template <int MODE, int KL, int PREC, bool LONG>
 __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_raw, int64_t item) {
-  // quantised keys everywhere but in the float32 pair mode; EX: float32
-  // with quantised keys keeps the exact keys and one more list slot.
-  // LONG: segments of up to kSegLong words (float32 only, 10 position bits)
+  // float32 pairs: exact keys; fp8 tables: quantised keys.  LONG: segments of
+  // up to kSegLong words (float32 only)
   static_assert(!LONG || PREC == PREC_F32, "long segments run with float32 keys");
-  constexpr bool QK = PREC != PREC_F32 || MODE != P1_PAIR;
-  constexpr bool EX = PREC == PREC_F32 && QK;
-  constexpr int KLC = KL + (EX ? 1 : 0);  // list capacity
-  constexpr int PB = LONG ? 10 : 9;
-  using Sm = WideSmem<KL, PREC, QK, EX, LONG ? kSegLong : kSeg>;
+  static_assert((PREC == PREC_F32) == (MODE == P1_PAIR), "float32 tables: k_phase1_rows");
+  constexpr bool QK = PREC != PREC_F32;
+  constexpr int PB = 9;
+  using Sm = WideSmem<KL, PREC, QK, LONG ? kSegLong : kSeg>;
   constexpr int KLS = Sm::KLS;
   Sm& sm = *reinterpret_cast<Sm*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -355,7 +312,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
     // query vectors and a row block's vectors in its L2
     const int64_t nrb = (a.v_used + kWR - 1) / kWR;
     const int64_t work = item;
-    const int lg = wide_group_log2(a.v_used, PREC);
+    constexpr int lg = kWGroupLog2;
     const int64_t qin = work & ((int64_t(1) << lg) - 1), t = work >> lg;
     const int64_t rblk = t % nrb, g = t / nrb;
     const int64_t qi = (g << lg) + qin;
@@ -407,12 +364,11 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
 
   // ---------------- contraction ----------------
   const unsigned char* base = PREC == PREC_F32    ? (const unsigned char*)a.V
-                              : PREC == PREC_BF16 ? (const unsigned char*)a.Vb
                                                   : (const unsigned char*)a.V8;
-  const size_t rowbytes = PREC == PREC_FP8 ? (size_t)a.m8 : (size_t)a.m_pad * (PREC == PREC_F32 ? 4 : 2);
+  const size_t rowbytes = PREC == PREC_FP8 ? (size_t)a.m8 : (size_t)a.m_pad * 4;
   // 128-byte slices that hold real dims (the zero padding past them would
   // add exact zeros): 4 * m4 dims of 4, 2 or 1 bytes
-  const int realbytes = 4 * a.m4 * (PREC == PREC_F32 ? 4 : PREC == PREC_BF16 ? 2 : 1);
+  const int realbytes = 4 * a.m4 * (PREC == PREC_F32 ? 4 : 1);
   const int nsl = min((int)(rowbytes / 128), (realbytes + 127) / 128);
   const int li = lane & 31, lh = lane >> 5;
   const int arow = 32 * wave + li;
@@ -540,12 +496,10 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
       }
       const KT_* cur = &sm.lst[par][row * KLS];
       KT_* nxt = &sm.lst[par ^ 1][row * KLS];
-      const float* curx = &sm.lkx[EX ? par : 0][EX ? row * KLS : 0];
-      float* nxtx = &sm.lkx[EX ? (par ^ 1) : 0][EX ? row * KLS : 0];
       const int len = row_ok ? sm.rlen[row] : 0;
       // approximate keys: the error band plus the rounding of 32-bit keys
       const float band = !QK ? 0.f
-                             : band_coef<PREC>() * sqrtf(sm.rvn[row]) * sm.qmax +
+                             : kBandFP8 * sqrtf(sm.rvn[row]) * sm.qmax +
                                    KO::kRound * (sm.qmax * sm.qmax + 2.f * sqrtf(sm.rvn[row]) * sm.qmax);
       int ptr = 0, w = 0;
       float P = 0.f, K0 = 0.f;
@@ -575,15 +529,12 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
             act = false;
           } else if (cut && (!QK || KO::key(take) > K0 + band)) {
             act = false;
-          } else if (w >= KLC) {
+          } else if (w >= KL) {
             // the list is full: remember the smallest key left out; the
             // final lists are certified against it after the exact re-sort
             act = false;
             if (sub == 0) sm.rdrop[row] = fminf(sm.rdrop[row], KO::key(take));
           } else {
-            if constexpr (EX) {
-              if (sub == 0) nxtx[w] = lc < best ? curx[ptr] : sm.u.ck[row * kCK + (int)(KO::pos(take)) - cb];
-            }
             if (lc < best) {
               ++ptr;
             } else {
@@ -625,7 +576,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
     for (int l = sub; l < len; l += 2) {
       const auto e = L[l];
       const int pos = (int)KeyOps<QK, PB>::pos(e);
-      float d2 = sm.rvn[row] + (EX ? sm.lkx[EX ? par : 0][EX ? row * KLS + l : 0] : KeyOps<QK, PB>::key(e));
+      float d2 = sm.rvn[row] + KeyOps<QK, PB>::key(e);
       bool need = !(d2 >= kGuardW * (sm.rvn[row] + sm.qn[pos]));
       if (MODE != P1_TABLE_FULL && a.method == LCEMD_OMR && l == 0) need = true;
       if (need) d2 = w_exact_d2(a.V, a.m_pad, a.m4, sm.rid[row], sm.cid[pos]);
@@ -675,26 +626,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
   if (sub == 0 && row_ok) {
     auto* Lw = &sm.lst[par][row * KLS];
     float* Z2 = &sm.u.zb[row * KLS];
-    float* Lx = &sm.lkx[EX ? par : 0][EX ? row * KLS : 0];
-    if constexpr (EX) {
-      // exact re-sort by (contraction key, position), distances moving
-      // along; the list then holds positions
-      for (int i = 0; i < len; ++i) Lw[i] = KeyOps<QK, PB>::pos(Lw[i]);
-      for (int i = 1; i < len; ++i) {
-        const uint64_t e = w_pack(Lx[i], (uint32_t)Lw[i]);
-        const float z = Z2[i];
-        int j = i - 1;
-        while (j >= 0 && w_pack(Lx[j], (uint32_t)Lw[j]) > e) {
-          Lw[j + 1] = Lw[j];
-          Lx[j + 1] = Lx[j];
-          Z2[j + 1] = Z2[j];
-          --j;
-        }
-        Lw[j + 1] = (uint32_t)e;
-        Lx[j + 1] = w_unpack(e);
-        Z2[j + 1] = z;
-      }
-    } else if constexpr (PREC != PREC_F32) {
+    if constexpr (PREC != PREC_F32) {
       // exact re-sort by (squared distance, position); the list then holds
       // positions
       for (int i = 0; i < len; ++i) Lw[i] = KeyOps<QK, PB>::pos(Lw[i]);
@@ -739,17 +671,11 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
       else if (a.overflow) a.overflow[0] = 1;
     }
     // a candidate left out of a full list has a key >= rdrop - half a band
-    // (bf16; exact keys for float32): the used entries must all be nearer
+    // (fp8 keys): the used entries must all be nearer
     if (QK && D > 0 && sm.rdrop[row] < INFINITY && a.overflow) {
-      bool certified;
-      if constexpr (EX) {
-        // exact keys left out are at least their quantised value
-        certified = Lx[D - 1] < sm.rdrop[row];
-      } else {
-        const float half_band = 0.5f * band_coef<PREC>() * sqrtf(sm.rvn[row]) * sm.qmax;
-        const float last_key = Z2[D - 1] - sm.rvn[row];
-        certified = last_key < sm.rdrop[row] - half_band - 1e-6f * (sm.rvn[row] + sm.qmax * sm.qmax);
-      }
+      const float half_band = 0.5f * kBandFP8 * sqrtf(sm.rvn[row]) * sm.qmax;
+      const float last_key = Z2[D - 1] - sm.rvn[row];
+      const bool certified = last_key < sm.rdrop[row] - half_band - 1e-6f * (sm.rvn[row] + sm.qmax * sm.qmax);
       if (!certified) {
         if (can_redo) redo = true;
         else a.overflow[0] = 1;
@@ -823,8 +749,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_phase1_wide(P1Args a, int64_t t
 
 template <int MODE, int KL, int PREC, bool LONG>
 static hipError_t launch_wide_one(const P1Args& a, hipStream_t s) {
-  constexpr bool QK = PREC != PREC_F32 || MODE != P1_PAIR;
-  const size_t shmem = sizeof(WideSmem<KL, PREC, QK, PREC == PREC_F32 && QK, LONG ? kSegLong : kSeg>);
+  constexpr bool QK = PREC != PREC_F32;
+  const size_t shmem = sizeof(WideSmem<KL, PREC, QK, LONG ? kSegLong : kSeg>);
   const void* fn = (const void*)k_phase1_wide<MODE, KL, PREC, LONG>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
@@ -833,7 +759,7 @@ static hipError_t launch_wide_one(const P1Args& a, hipStream_t s) {
     total = a.npairs * (int64_t)a.rb_max;
   } else {
     const int64_t nrb = (a.v_used + kWR - 1) / kWR;
-    const int64_t gw = int64_t(1) << wide_group_log2(a.v_used, PREC);
+    const int64_t gw = int64_t(1) << kWGroupLog2;
     total = (a.nq + gw - 1) / gw * nrb * gw;
   }
   if (total <= 0) return hipSuccess;
@@ -856,15 +782,6 @@ static hipError_t launch_wide_mode(const P1Args& a, int KL, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-template <int PREC, bool LONG = false>
-static hipError_t launch_wide_prec(const P1Args& a, int mode, int KL, hipStream_t s) {
-  switch (mode) {
-    case P1_TABLE: return launch_wide_mode<P1_TABLE, PREC, LONG>(a, KL, s);
-    case P1_TABLE_FULL: return launch_wide_mode<P1_TABLE_FULL, PREC, LONG>(a, KL, s);
-    case P1_PAIR: return launch_wide_mode<P1_PAIR, PREC, LONG>(a, KL, s);
-  }
-  return hipErrorInvalidValue;
-}
 
 // Exact redo of single table rows (rows whose selection certificate
 // failed): one wave per row computes float32 squared distances to all of the
@@ -1004,14 +921,17 @@ int phase1_wide_rows() { return kWR; }
 
 hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, int prec, int seg_hmax, hipStream_t s) {
   if (seg_hmax > kSegLong) return hipErrorInvalidValue;
-  if (seg_hmax > kSeg) return prec == PREC_F32 ? launch_wide_prec<PREC_F32, true>(a, mode, KL, s) : hipErrorInvalidValue;
-  if (prec == PREC_F32) return launch_wide_prec<PREC_F32>(a, mode, KL, s);
-  if (prec == PREC_BF16) return hipErrorInvalidValue;  // bf16 keys: launch_phase1_bf16
-  if (prec == PREC_FP8) {
-    if (!a.V8 || !a.vscale || a.m8 % 128 != 0) return hipErrorInvalidValue;
-    return launch_wide_prec<PREC_FP8>(a, mode, KL, s);
+  if (prec == PREC_F32) {  // float32 table modes: launch_phase1_rows
+    if (mode != P1_PAIR) return hipErrorInvalidValue;
+    return seg_hmax > kSeg ? launch_wide_mode<P1_PAIR, PREC_F32, true>(a, KL, s)
+                           : launch_wide_mode<P1_PAIR, PREC_F32, false>(a, KL, s);
   }
-  return hipErrorInvalidValue;
+  if (prec == PREC_FP8) {
+    if (seg_hmax > kSeg || !a.V8 || !a.vscale || a.m8 % 128 != 0) return hipErrorInvalidValue;
+    if (mode == P1_TABLE) return launch_wide_mode<P1_TABLE, PREC_FP8, false>(a, KL, s);
+    if (mode == P1_TABLE_FULL) return launch_wide_mode<P1_TABLE_FULL, PREC_FP8, false>(a, KL, s);
+  }
+  return hipErrorInvalidValue;  // bf16 keys: launch_phase1_bf16; reduced-precision pairs use float32 keys
 }
 
 }  // namespace lcemd
