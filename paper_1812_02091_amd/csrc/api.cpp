@@ -272,10 +272,9 @@ int ensure_precision(lcemd_ctx* c, int prec) {
 }
 
 // Launch phase 1: rows of `a` may need up to `depth` list entries.  Lists of
-// up to 32 entries (with the bf16 margin) run on the 128-row kernel, up to
-// 64 (and float32 embeddings of at most 28 dims at any depth up to 64) on
-// the 64-row streaming kernel, deeper rows on the kernel that keeps a
-// whole row of keys in LDS (float32 keys).  Pair mode: a.rb_max is set to
+// up to 32 entries (with the reduced-precision margin) run on the kernel of
+// their precision, up to 64 on the 64-row streaming kernel, deeper rows on
+// the kernel that keeps a whole row of keys in LDS (both float32 keys).  Pair mode: a.rb_max is set to
 // the row-block count of the chosen kernel for queries of up to row_hmax
 // words (callers size `partial` for 64-row blocks, the largest count).
 int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hmax,
@@ -320,20 +319,15 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
     HIPCHK(c, launch_phase1_bf16(a, mode, depth, c->stream));
     return LCEMD_OK;
   }
-  if (prec == LCEMD_FP32 && mode != P1_PAIR && depth <= 32 && !c->force_kernel) {
+  if (prec == LCEMD_FP32 && depth <= 32 && !c->force_kernel) {
     a.KT_margin = 0;
-    a.rb_max = 0;
+    a.rb_max = phase1_rows_partials(a, row_hmax);
     HIPCHK(c, launch_phase1_rows(a, mode, depth, c->stream));
-    return LCEMD_OK;
-  }
-  // pairs with at most 28 dims (image coordinates): the 64-row kernel, whose
-  // row blocks waste less of ~160-word histograms
-  const bool small_m = prec == LCEMD_FP32 && a.m4 <= 7;
-  if (depth + margin <= 32 && !c->force_kernel && !small_m) {
+  } else if (prec == LCEMD_FP8) {  // tables, lists of up to 32 entries
     const int KL = pow2ceil(depth + margin);
     a.KT_margin = margin;
-    a.rb_max = (row_hmax + phase1_wide_rows() - 1) / phase1_wide_rows();
-    HIPCHK(c, launch_phase1_wide(a, mode, KL, prec, seg_hmax, c->stream));
+    a.rb_max = 0;
+    HIPCHK(c, launch_phase1_wide(a, mode, KL, c->stream));
   } else if (depth <= 64 && c->force_kernel != 2) {
     const int KL = pow2ceil(std::min(depth + margin, 64));
     a.KT_margin = margin;

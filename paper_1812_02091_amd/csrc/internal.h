@@ -149,15 +149,17 @@ __device__ __forceinline__ void zw_write_row(float2* ZW, int64_t zw_nq, int KT, 
 // kernel launchers (each in the translation unit of its kernel)
 hipError_t launch_phase1_deep(const P1Args& a, int mode, int hmax, int prec, hipStream_t s);
 hipError_t launch_phase1_fast(const P1Args& a, int mode, int KT, int prec, hipStream_t s);
-hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, int prec, int seg_hmax, hipStream_t s);
-// float32 table modes, lists of up to 32 entries, segments of up to
-// LCEMD_MAX_HIST words
+// fp8 table modes (lists of up to 32 entries, segments <= kSegShort words)
+hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, hipStream_t s);
+// float32 keys, lists of up to 32 entries, segments of up to LCEMD_MAX_HIST
+// words; pair mode takes candidate lists, its partial sums (P1Args::rb_max
+// per pair) cover phase1_rows_partials' row blocks
+int phase1_rows_partials(const P1Args& a, int row_hmax);
 hipError_t launch_phase1_rows(const P1Args& a, int mode, int depth, hipStream_t s);
 // bfloat16 table modes (lists of depth + 8 <= 32, segments <= kSegShort words,
 // rows of at most kBf16MaxDims dims)
 bool phase1_bf16_fits(int mb, int seg_hmax, int depth);
 hipError_t launch_phase1_bf16(const P1Args& a, int mode, int depth, hipStream_t s);
-int phase1_wide_rows();
 hipError_t launch_fix_rows(const P1Args& a, int mode, int count, hipStream_t s);
 hipError_t launch_pair_reduce(const float* partial, int64_t npairs, int rb_max, float* out,
                               int64_t out_ld, int64_t per_row, hipStream_t s);

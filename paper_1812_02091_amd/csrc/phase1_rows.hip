@@ -1,6 +1,8 @@
-// Phase 1 of LC-ACT (Sec. 4, Phase 1) with float32 keys, table modes, lists
-// of up to 32 entries: per (vocabulary row, query) the nearest query words of
-// Alg. 3 and their capacities.
+// Phase 1 of LC-ACT (Sec. 4, Phase 1) with float32 keys, lists of up to 32
+// entries.  Table modes: per (vocabulary row, query) the nearest query words
+// of Alg. 3 and their capacities.  Pair mode (Q2D of a candidate pair): the
+// query's words as rows against the database row's words, and the transfers
+// of the query's mass summed per block of rows.
 //
 // Bound: the float32 MFMA (157 TFLOP/s; 134-150 in a loop of nothing but
 // MFMAs and their LDS reads; here the pipe is busy 74 % of the time at 128
@@ -33,6 +35,7 @@
 // |v|^2 + |c|^2), where it is recomputed by direct differences (identical
 // words give exactly 0).
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -49,8 +52,21 @@ constexpr int kFSeg = LCEMD_MAX_HIST;
 constexpr float kFGuard = 0.25f;
 constexpr uint32_t kNoKey = 0x7f800000u;  // +inf: above every key
 
+// Tiles per pass at most.  Embeddings of at most 28 dims (SMALL) have one
+// slice and little to contract, so what counts there is how many waves hide
+// the set-up and the selection: with two tiles a wave of lists of up to 8
+// entries fits 168 registers, three workgroups per CU instead of two (four,
+// at 128 registers, spill: 20,000 images x 784 words, k = 8, 2.9 against 2.6
+// ms).
+template <bool SMALL>
+constexpr int max_tiles() { return SMALL ? 2 : 4; }
+template <int LK, bool SMALL>
+constexpr int groups_per_cu() { return SMALL && LK <= 8 ? 3 : 2; }
+
+template <bool SMALL>
 struct F32Smem {
-  unsigned char st[2][kFC * kFStride];  // word slices, double-buffered
+  unsigned char st[SMALL ? 1 : 2][32 * max_tiles<SMALL>() * kFStride];  // word slices, double-buffered
+  float rcost[kFR];       // pair mode: the rows' costs
   int cid[kFSeg + kFC];   // word 0 past the query's words, up to a pass's end
   float cap[kFSeg + kFC];
   float qn[kFSeg + kFC];  // +inf there: those keys are above every key
@@ -209,12 +225,13 @@ struct Flight {
 };
 
 // One pass: NT tiles of words from c0 on, all slices, then their keys into
-// the list.  A pass is a function of its own tile count so that the
+// the list (live: the wave has rows; it stages words either way).  A pass is a function of its own tile count so that the
 // accumulators stay in the same registers throughout (a switch inside the
 // slice loop had them copied, 200 moves a slice).
 template <int NT, int LK, bool SMALL>
-__device__ __forceinline__ void f32_pass(F32Smem& sm, Flight& fl, double (&lst)[LK], int c0, bool more, int nsl,
-                                         int last_njq, const unsigned char* vb, size_t rowbytes, int tid) {
+__device__ __forceinline__ void f32_pass(F32Smem<SMALL>& sm, Flight& fl, double (&lst)[LK], int c0, bool more,
+                                         bool live, int nsl, int last_njq, const unsigned char* vb, size_t rowbytes,
+                                         int tid) {
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
   floatx16 acc[NT];
 #pragma unroll
@@ -241,7 +258,7 @@ __device__ __forceinline__ void f32_pass(F32Smem& sm, Flight& fl, double (&lst)[
     for (int sl = 0; sl < nsl - 1; ++sl) {
       stage((sl + 1) & 1);  // (last read a slice ago, before the barrier)
       if (sl + 2 < nsl) fl.load_words<NT>(sl + 2);
-      f32_slice<NT, true>(acc, rows, sm.st[sl & 1], li, lh, 4);
+      if (live) f32_slice<NT, true>(acc, rows, sm.st[sl & 1], li, lh, 4);
       take_rows();
       if (sl + 2 < nsl) fl.load_rows(sl + 2);
       __syncthreads();
@@ -253,6 +270,7 @@ __device__ __forceinline__ void f32_pass(F32Smem& sm, Flight& fl, double (&lst)[
     fl.words<NT>(vb, rowbytes, sm.cid + c0 + 32 * NT, tid);
     fl.load<NT>(0);
   }
+  if (!live) return;
   f32_slice<NT, false>(acc, rows, sm.st[SMALL ? 0 : (nsl - 1) & 1], li, lh, last_njq);
 
   // ---- selection: 16 keys of the lane's row per tile ----
@@ -274,37 +292,76 @@ __device__ __forceinline__ void f32_pass(F32Smem& sm, Flight& fl, double (&lst)[
   }
 }
 
-// One work item: (query, 128-row block).  Returns early (uniformly) for
-// empty items.
+// One work item: (query, 128-row block) in the table modes, (candidate pair,
+// 128-row block of the query's words) in pair mode.  Returns early
+// (uniformly) for empty items.
 template <int MODE, int LK, bool SMALL>
-__device__ __forceinline__ void f32_task(const P1Args& a, F32Smem& sm, int64_t item) {
+__device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<SMALL>& sm, int64_t item) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 31, lh = lane >> 5;
   constexpr bool kCapStop = MODE != P1_TABLE_FULL;
 
-  // items run query-fastest within a group of queries, then row block, then
-  // group: an XCD's contiguous range of items keeps a group's query vectors
-  // and a row block's vectors in its L2
-  const int64_t nrb = (a.v_used + kFR - 1) / kFR;
-  const int lg = f32_group_log2(a.v_used);
-  const int64_t t0 = item >> lg;
-  const int64_t rblk = t0 % nrb, qi = ((t0 / nrb) << lg) + (item & ((int64_t(1) << lg) - 1));
-  if (qi >= a.nq) return;
-  const int64_t r0 = rblk * kFR;
-  const int64_t s0 = a.qptr[a.q0 + qi];
-  const int h = (int)(a.qptr[a.q0 + qi + 1] - s0);
-  if (h <= 0) return;  // padding slot of a fixed-size batch
-  const int64_t r = r0 + 32 * wave + li;  // the lane's row (both halves)
-  const bool row_ok = r < a.v_used;
-  const int rid = row_ok ? a.used[r] : a.used[r0];
-  for (int c = tid; c < h + kFC; c += kThreads) {
-    const int w = c < h ? a.qcol[s0 + c] : 0;
-    sm.cid[c] = w;
-    sm.cap[c] = c < h ? a.qval[s0 + c] : 0.f;
-    sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
+  int64_t qi = 0, r = 0;  // table modes: query of the launch, table row
+  int64_t pair = 0;       // pair mode: pair and the first of its partial sums here
+  int part = 0, nrows = kFR;
+  int64_t s0;             // the segment
+  int h, rid;
+  float bound;
+  bool row_ok;
+  if constexpr (MODE == P1_PAIR) {
+    // partial sums of 128 rows, or 64 (SMALL: two per item)
+    const int nblk = SMALL ? (a.rb_max + 1) >> 1 : a.rb_max;
+    pair = item / nblk;
+    const int blk = (int)(item % nblk);
+    part = SMALL ? 2 * blk : blk;
+    const int64_t qr = pair / a.cand_use, b = a.qlist ? (int64_t)a.qlist[qr] : qr;
+    const int64_t u = (int64_t)(uint32_t)a.cand[qr * a.cand_ld + pair % a.cand_use];
+    const int64_t q0 = a.qptr[b] + blk * kFR;
+    nrows = (int)min((int64_t)kFR, a.qptr[b + 1] - q0);
+    if (nrows <= 0 || u >= a.n) {
+      if (tid == 0) a.partial[pair * a.rb_max + part] = 0.f;
+      if (SMALL && tid == 0 && part + 1 < a.rb_max) a.partial[pair * a.rb_max + part + 1] = 0.f;
+      return;
+    }
+    row_ok = 32 * wave + li < nrows;
+    const int64_t i = q0 + (row_ok ? 32 * wave + li : 0);
+    rid = a.qcol[i];
+    bound = row_ok ? a.qval[i] : 0.f;
+    s0 = a.xptr[u];
+    h = (int)(a.xptr[u + 1] - s0);
+    for (int c = tid; c < h + kFC; c += kThreads) {
+      const int w = c < h ? a.xcol[s0 + c] : 0;
+      sm.cid[c] = w;
+      sm.cap[c] = c < h ? __int_as_float(a.xcv[s0 + c].y) : 0.f;
+      sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
+    }
+  } else {
+    // items run query-fastest within a group of queries, then row block, then
+    // group: an XCD's contiguous range of items keeps a group's query vectors
+    // and a row block's vectors in its L2
+    const int64_t nrb = (a.v_used + kFR - 1) / kFR;
+    const int lg = f32_group_log2(a.v_used);
+    const int64_t t0 = item >> lg;
+    const int64_t rblk = t0 % nrb;
+    qi = ((t0 / nrb) << lg) + (item & ((int64_t(1) << lg) - 1));
+    if (qi >= a.nq) return;
+    const int64_t r0 = rblk * kFR;
+    s0 = a.qptr[a.q0 + qi];
+    h = (int)(a.qptr[a.q0 + qi + 1] - s0);
+    if (h <= 0) return;  // padding slot of a fixed-size batch
+    r = r0 + 32 * wave + li;  // the lane's row (both halves)
+    row_ok = r < a.v_used;
+    rid = row_ok ? a.used[r] : a.used[r0];
+    bound = MODE == P1_TABLE ? (row_ok ? a.xmax[r] : 0.f) : INFINITY;
+    for (int c = tid; c < h + kFC; c += kThreads) {
+      const int w = c < h ? a.qcol[s0 + c] : 0;
+      sm.cid[c] = w;
+      sm.cap[c] = c < h ? a.qval[s0 + c] : 0.f;
+      sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
+    }
   }
   const float rvn = a.vnorm[rid];
-  const float bound = MODE == P1_TABLE ? (row_ok ? a.xmax[r] : 0.f) : INFINITY;
+  const bool live = __any(row_ok);  // the wave has rows
   __syncthreads();
 
   int kef;
@@ -325,22 +382,31 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem& sm, int64_t i
   double lst[LK];
 #pragma unroll
   for (int i = 0; i < LK; ++i) lst[i] = __hiloint2double((int)kNoKey, 0);
-  // passes of at most four tiles, as even as they come (a pass of one tile
+  // passes of at most kNT tiles, as even as they come (a pass of one tile
   // costs its barriers and latencies like one of four), longer ones first
-  const int nt = (h + 31) >> 5, npass = (nt + 3) >> 2, base = nt / npass, extra = nt % npass;
+  constexpr int kNT = max_tiles<SMALL>();
+  const int nt = (h + 31) >> 5, npass = (nt + kNT - 1) / kNT, base = nt / npass, extra = nt % npass;
   Flight fl;
   fl.rptr = vb + (size_t)rid * rowbytes + lh * 64;
-  fl.words<4>(vb, rowbytes, sm.cid, tid);
-  fl.load<4>(0);
+  fl.words<kNT>(vb, rowbytes, sm.cid, tid);
+  fl.load<kNT>(0);
   int c0 = 0;
   for (int p = 0; p < npass; ++p) {
     const int n = base + (p < extra ? 1 : 0);
     const bool more = p + 1 < npass;
-    switch (n) {
-      case 1: f32_pass<1, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
-      case 2: f32_pass<2, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
-      case 3: f32_pass<3, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
-      default: f32_pass<4, LK, SMALL>(sm, fl, lst, c0, more, nsl, last_njq, vb, rowbytes, tid); break;
+    auto pass = [&](auto tiles) {
+      f32_pass<decltype(tiles)::value, LK, SMALL>(sm, fl, lst, c0, more, live, nsl, last_njq, vb, rowbytes, tid);
+    };
+    if constexpr (SMALL) {
+      if (n == 1) pass(std::integral_constant<int, 1>());
+      else pass(std::integral_constant<int, 2>());
+    } else {
+      switch (n) {
+        case 1: pass(std::integral_constant<int, 1>()); break;
+        case 2: pass(std::integral_constant<int, 2>()); break;
+        case 3: pass(std::integral_constant<int, 3>()); break;
+        default: pass(std::integral_constant<int, 4>()); break;
+      }
     }
     c0 += 32 * n;
   }
@@ -384,6 +450,31 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem& sm, int64_t i
       if (kCapStop) covered = covered || Pc >= bound || (a.method == LCEMD_OMR && l == 0 && d2 != 0.f);
     }
   }
+  if constexpr (MODE == P1_PAIR) {
+    // the transfers of the row's mass (the last entry takes the rest), then
+    // the rows' sum in order
+    if (!covered && D < h && row_ok && a.overflow) a.overflow[0] = 1;  // a list too short
+    if (lh == 0) {
+      float rem = bound, cost = 0.f;
+#pragma unroll
+      for (int l = 0; l < LK; ++l) {
+        if (l < D) {
+          const float t = l == D - 1 ? rem : fminf(rem, w[l]);
+          rem -= t;
+          cost = fmaf(t, z[l], cost);
+        }
+      }
+      sm.rcost[32 * wave + li] = cost;
+    }
+    __syncthreads();
+    constexpr int kPart = SMALL ? 64 : kFR;
+    if (tid % kPart == 0 && tid < kFR && part + tid / kPart < a.rb_max) {
+      float tot = 0.f;
+      for (int i = tid; i < min(tid + kPart, nrows); ++i) tot += sm.rcost[i];
+      a.partial[pair * a.rb_max + part + tid / kPart] = tot;
+    }
+    return;
+  }
   if (!row_ok) return;  // (no barrier past this point)
   // an ICT row deeper than the list: redone exactly by k_fix_rows while the
   // redo list has room, else the launch reports overflow
@@ -408,7 +499,7 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem& sm, int64_t i
                         two ? (l + 1 == D - 1 ? INFINITY : w[l + kOdd]) : 0.f);
       }
     }
-  } else {
+  } else if constexpr (MODE == P1_TABLE_FULL) {
     const int64_t o0 = (qi * a.v_used + r) * (int64_t)a.k;
 #pragma unroll
     for (int l = 0; l < LK; ++l) {
@@ -427,8 +518,8 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem& sm, int64_t i
 // contiguous eighth of the items; the counter is read one item ahead.  Every
 // workgroup exits once its counter passes the end of its range.
 template <int MODE, int LK, bool SMALL>
-__global__ __launch_bounds__(kThreads, 2) void k_phase1_rows(P1Args a, int64_t total) {
-  __shared__ F32Smem sm;
+__global__ __launch_bounds__(kThreads, (groups_per_cu<LK, SMALL>())) void k_phase1_rows(P1Args a, int64_t total) {
+  __shared__ F32Smem<SMALL> sm;
   __shared__ int64_t s_item;
   const int xcd = blockIdx.x & 7;
   const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
@@ -449,9 +540,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_phase1_rows(P1Args a, int64_t t
 
 template <int MODE, int LK, bool SMALL>
 hipError_t launch_f32_one(const P1Args& a, hipStream_t s) {
-  const int64_t nrb = (a.v_used + kFR - 1) / kFR;
-  const int64_t gw = int64_t(1) << f32_group_log2(a.v_used);
-  const int64_t total = (a.nq + gw - 1) / gw * nrb * gw;
+  int64_t total;
+  if (MODE == P1_PAIR) {
+    total = a.npairs * (SMALL ? (a.rb_max + 1) / 2 : a.rb_max);
+  } else {
+    const int64_t nrb = (a.v_used + kFR - 1) / kFR;
+    const int64_t gw = int64_t(1) << f32_group_log2(a.v_used);
+    total = (a.nq + gw - 1) / gw * nrb * gw;
+  }
   if (total <= 0) return hipSuccess;
   if (!a.work_ctr) return hipErrorInvalidValue;
   hipError_t e = launch_zero_ints((int*)a.work_ctr, 16, s);
@@ -473,14 +569,25 @@ hipError_t launch_f32_list(const P1Args& a, int depth, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// embeddings of at most 28 dims: one slice
+bool phase1_rows_small(const P1Args& a) { return a.m4 <= 7; }
+
+template <int MODE>
+hipError_t launch_f32_mode(const P1Args& a, int depth, hipStream_t s) {
+  return phase1_rows_small(a) ? launch_f32_list<MODE, true>(a, depth, s) : launch_f32_list<MODE, false>(a, depth, s);
+}
+
 }  // namespace
 
+int phase1_rows_partials(const P1Args& a, int row_hmax) {
+  const int rows = phase1_rows_small(a) ? 64 : kFR;
+  return (row_hmax + rows - 1) / rows;
+}
+
 hipError_t launch_phase1_rows(const P1Args& a, int mode, int depth, hipStream_t s) {
-  const bool small = a.m4 <= 7;  // at most 28 dims: one slice
-  if (mode == P1_TABLE)
-    return small ? launch_f32_list<P1_TABLE, true>(a, depth, s) : launch_f32_list<P1_TABLE, false>(a, depth, s);
-  if (mode == P1_TABLE_FULL)
-    return small ? launch_f32_list<P1_TABLE_FULL, true>(a, depth, s) : launch_f32_list<P1_TABLE_FULL, false>(a, depth, s);
+  if (mode == P1_TABLE) return launch_f32_mode<P1_TABLE>(a, depth, s);
+  if (mode == P1_TABLE_FULL) return launch_f32_mode<P1_TABLE_FULL>(a, depth, s);
+  if (mode == P1_PAIR && a.cand) return launch_f32_mode<P1_PAIR>(a, depth, s);
   return hipErrorInvalidValue;
 }
 

@@ -1,5 +1,6 @@
-// Phase 1 of LC-ACT (Sec. 4, Phase 1), wide variant: 128 rows per
-// workgroup and up to 128 columns per MFMA pass.
+// Phase 1 of LC-ACT (Sec. 4, Phase 1) with fp8 keys, table modes, lists of up
+// to 32 entries: 128 rows per workgroup and up to 128 columns per MFMA pass;
+// and the exact redo of single table rows (every precision).
 //
 // Contraction: wave w owns rows [32w, 32w+32).  Its row operand (32 rows x
 // one 128-byte slice of dims) is read straight from global memory into
@@ -11,21 +12,18 @@
 //
 // Selection: after a pass the keys |c|^2 - 2 <v, c> go to LDS 64 columns at
 // a time and two lanes per row merge them into the row's sorted candidate
-// list (packed (key, position); position breaks ties; for lists of 8 or more
-// entries each lane first sorts its 32 keys in registers and the merge takes
-// from their heads, else it scans them for the next), cut at k_eff = min(k,
-// h) (Alg. 3; 1 for RWMD, 2 for OMR) or as soon as the listed capacities
-// reach the row's bound (Lemma 1/2: no transfer of at most that much mass
-// passes this point).
+// list (packed key | position; position breaks ties; each lane first sorts
+// its 32 keys in registers and the merge takes from their heads), cut at
+// k_eff = min(k, h) (Alg. 3; 1 for RWMD, 2 for OMR) or as soon as the listed
+// capacities reach the row's bound (Lemma 1/2: no transfer of at most that
+// much mass passes this point).
 //
-// Exact distances: float32 keys -- the list distance is |v|^2 + key unless
-// cancellation could bite (below a quarter of |v|^2 + |c|^2), where it is
-// recomputed by direct differences.  fp8 keys -- the list keeps, past the
-// cut, every candidate within a statistical band of the cut key.  All listed
-// candidates then get float32 distances -- |v|^2 + |c|^2 - 2<v, c> with the dot product
-// accumulated in float32 over the original vectors (staged through LDS a
-// chunk of dims at a time), or by direct differences where cancellation
-// could bite, as for float32 keys -- and are re-sorted and cut again.
+// Exact distances: the list keeps, past the cut, every candidate within a
+// statistical band of the cut key.  All listed candidates then get float32
+// distances -- |v|^2 + |c|^2 - 2<v, c> with the dot product accumulated in
+// float32 over the original vectors (staged through LDS a chunk of dims at a
+// time), or by direct differences where cancellation could bite -- and are
+// re-sorted and cut again.
 #include <algorithm>
 
 #include "internal.h"
@@ -41,8 +39,8 @@ constexpr int kWC = 128;        // columns per MFMA pass
 constexpr int kStride = 144;    // bytes per staged column slice (128 + 16 pad)
 constexpr int kCK = 66;         // floats per key row (64 columns + 2 pad)
 constexpr int kQSCap = kWR * kCK;  // floats of the staging area (the key buffer's size)
-constexpr int kSeg = kSegShort;            // segment words held in LDS (short variant)
-constexpr int kSegLong = LCEMD_MAX_HIST;   // long variant (float32 keys)
+constexpr int kSeg = kSegShort;            // segment words held in LDS
+constexpr int kSegLong = LCEMD_MAX_HIST;   // longest segment of the exact redo
 constexpr int kWGroupLog2 = 3;  // queries per item group (table modes; 32 was 3 % slower at 1M words)
 constexpr float kGuardW = 0.25f;
 // fp8 (e4m3, 3 mantissa bits): a statistical band, not a worst-case one --
@@ -61,45 +59,19 @@ __device__ __forceinline__ float w_unpack(uint64_t k) {
   const uint32_t o = (uint32_t)(k >> 32);
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
-__device__ __forceinline__ uint64_t w_shfl1(uint64_t v) {
-  int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
-  lo = __shfl_xor(lo, 1);
-  hi = __shfl_xor(hi, 1);
-  return ((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo;
+// Selection keys: the key's 9 low bits give way to the position (segments of
+// up to 512 words), one 32-bit word, rounded down in value by at most 2^-14
+// of the key's magnitude; lists keep every entry within twice that band past
+// their cut and are re-sorted afterwards by the recomputed distances.
+constexpr uint32_t kWNone = 0xffffffffu;
+constexpr uint32_t kWPos = 511u;
+constexpr float kWRound = 1.f / 8192.f;  // twice the largest relative rounding of a key
+__device__ __forceinline__ uint32_t wk_pack(float f, uint32_t pos) { return (w_bits(f) & ~kWPos) | pos; }
+__device__ __forceinline__ float wk_key(uint32_t k) {
+  const uint32_t o = k & ~kWPos;
+  return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
-
-// Selection keys.  Exact keys: (order-preserving key bits, position) in 64
-// bits (float32 pair mode).  Quantised keys (fp8 tables): the key's PB low
-// bits give way to the position (9 bits: segments of up to 512 words), one
-// 32-bit word, rounded down in value by at most
-// 2^(PB-23) of the key's magnitude; lists keep every entry within twice
-// that band past their cut and are re-sorted afterwards by the exact keys
-// (the recomputed distances).
-template <bool QK, int PB = 9>
-struct KeyOps {
-  using T = uint32_t;
-  static constexpr T kNone = 0xffffffffu;
-  static constexpr uint32_t kPos = (1u << PB) - 1u;
-  // twice the largest relative rounding of a key, 2 * 2^(PB-23)
-  static constexpr float kRound = (float)(1u << PB) / (float)(1u << 22);
-  __device__ static T pack(float f, uint32_t pos) { return (w_bits(f) & ~kPos) | pos; }
-  __device__ static float key(T k) {
-    const uint32_t o = k & ~kPos;
-    return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
-  }
-  __device__ static uint32_t pos(T k) { return k & kPos; }
-  __device__ static T shfl1(T v) { return (T)__shfl_xor((int)v, 1); }
-};
-template <int PB>
-struct KeyOps<false, PB> {
-  using T = uint64_t;
-  static constexpr T kNone = ~0ull;
-  static constexpr float kRound = 0.f;  // exact keys
-  __device__ static T pack(float f, uint32_t pos) { return w_pack(f, pos); }
-  __device__ static float key(T k) { return w_unpack(k); }
-  __device__ static uint32_t pos(T k) { return (uint32_t)k; }
-  __device__ static T shfl1(T v) { return w_shfl1(v); }
-};
+__device__ __forceinline__ uint32_t wk_pos(uint32_t k) { return k & kWPos; }
 
 // Squared distance by direct differences over the m4 float4 groups that
 // hold the real dims (the zero padding would add exact zeros).
@@ -122,28 +94,6 @@ __device__ __forceinline__ float w_exact_d2(const float* __restrict__ V, int m_p
 // One staged slice on NT 32-column tiles (NT fixed at compile time so the
 // MFMAs issue back to back without branches).
 template <int NT>
-__device__ __forceinline__ void slice_f32(floatx16 (&acc)[4], const uint4 (&a_cur)[4],
-                                          const unsigned char* st, int li, int lh) {
-  // lane half lh supplies dims [16 lh, 16 lh + 16) of the 32-dim slice
-  const float* af = (const float*)a_cur;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float4 bv[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-      bv[t] = *(const float4*)(st + (32 * t + li) * kStride + lh * 64 + j * 16);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[4 * j + 0], bv[t].x, acc[t], 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[4 * j + 1], bv[t].y, acc[t], 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[4 * j + 2], bv[t].z, acc[t], 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[4 * j + 3], bv[t].w, acc[t], 0, 0, 0);
-  }
-}
-
-template <int NT>
 __device__ __forceinline__ void slice_fp8(floatx16 (&acc)[4], const uint4 (&a_cur)[4],
                                           const unsigned char* st, int li, int lh) {
   // lane half lh supplies dims [64 lh + 8 s, +8) of the 128-dim slice
@@ -158,49 +108,38 @@ __device__ __forceinline__ void slice_fp8(floatx16 (&acc)[4], const uint4 (&a_cu
   }
 }
 
-template <int PREC>
 __device__ __forceinline__ void slice_mfma(int ntile, floatx16 (&acc)[4], const uint4 (&a_cur)[4],
                                            const unsigned char* st, int li, int lh) {
-  if constexpr (PREC == PREC_F32) {
-    switch (ntile) {
-      case 1: slice_f32<1>(acc, a_cur, st, li, lh); break;
-      case 2: slice_f32<2>(acc, a_cur, st, li, lh); break;
-      case 3: slice_f32<3>(acc, a_cur, st, li, lh); break;
-      default: slice_f32<4>(acc, a_cur, st, li, lh); break;
-    }
-  } else {
-    switch (ntile) {
-      case 1: slice_fp8<1>(acc, a_cur, st, li, lh); break;
-      case 2: slice_fp8<2>(acc, a_cur, st, li, lh); break;
-      case 3: slice_fp8<3>(acc, a_cur, st, li, lh); break;
-      default: slice_fp8<4>(acc, a_cur, st, li, lh); break;
-    }
+  switch (ntile) {
+    case 1: slice_fp8<1>(acc, a_cur, st, li, lh); break;
+    case 2: slice_fp8<2>(acc, a_cur, st, li, lh); break;
+    case 3: slice_fp8<3>(acc, a_cur, st, li, lh); break;
+    default: slice_fp8<4>(acc, a_cur, st, li, lh); break;
   }
 }
 
-template <int KL, int PREC, bool QK, int SEG = kSeg>
+template <int KL>
 struct WideSmem {
   static constexpr int KLS = KL + 1;  // list row stride (spreads rows over banks)
   union {
     unsigned char st[kWC * kStride];  // staged column slice
     float ck[kWR * kCK];              // keys of 64 columns of a pass
-    float qs[PREC == PREC_F32 ? 1 : kQSCap];  // segment vectors, a chunk of dims (exact recompute)
+    float qs[kQSCap];  // segment vectors, a chunk of dims (exact recompute)
     float zb[kWR * KLS];              // exact squared distances of the lists
   } u;
-  typename KeyOps<QK>::T lst[2][kWR * KLS];
-  int cid[SEG];
-  float cap[SEG];
-  float qn[SEG];
+  uint32_t lst[2][kWR * KLS];
+  int cid[kSeg];
+  float cap[kSeg];
+  float qn[kSeg];
   int rid[kWR];
   float rbound[kWR];
   float rvn[kWR];
   int rlen[kWR];
-  float rcost[kWR];
   float rdrop[kWR];  // smallest key dropped because the list was full
   int rcut[kWR];     // the last merge reached k_eff or the row's bound
   float qmax;
-  float rsc[PREC == PREC_FP8 ? kWR : 1];   // fp8 row scales
-  float csc[PREC == PREC_FP8 ? SEG : 1];  // fp8 column scales
+  float rsc[kWR];   // fp8 row scales
+  float csc[kSeg];  // fp8 column scales
 };
 
 // Float32 dot products <v_row, c_pos> of a thread's listed candidates
@@ -246,67 +185,19 @@ __device__ __forceinline__ void wide_dots(float (&ex)[KH], const int (&ps)[KH], 
 
 }  // namespace
 
-// One work item: (query, 128-row block) in the table modes, (pair, row
-// block) in pair mode.  Returns early (uniformly) for empty items.
-template <int MODE, int KL, int PREC, bool LONG>
+// One work item: (query, 128-row block).  Returns early (uniformly) for empty
+// items.
+template <int MODE, int KL>
 __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_raw, int64_t item) {
-  // float32 pairs: exact keys; fp8 tables: quantised keys.  LONG: segments of
-  // up to kSegLong words (float32 only)
-  static_assert(!LONG || PREC == PREC_F32, "long segments run with float32 keys");
-  static_assert((PREC == PREC_F32) == (MODE == P1_PAIR), "float32 tables: k_phase1_rows");
-  constexpr bool QK = PREC != PREC_F32;
-  constexpr int PB = 9;
-  using Sm = WideSmem<KL, PREC, QK, LONG ? kSegLong : kSeg>;
+  using Sm = WideSmem<KL>;
   constexpr int KLS = Sm::KLS;
   Sm& sm = *reinterpret_cast<Sm*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
   // ---------------- task decode ----------------
   int nrows = 0, h = 0;
-  int64_t out_row0 = 0, pidx = 0;
-  int rb = 0;
-  if constexpr (MODE == P1_PAIR) {
-    pidx = item / a.rb_max;
-    rb = (int)(item % a.rb_max);
-    int64_t b, u;
-    if (a.cand) {
-      const int64_t qi = pidx / a.cand_use, c = pidx % a.cand_use;
-      b = a.qlist ? (int64_t)a.qlist[qi] : qi;
-      u = (int64_t)(uint32_t)a.cand[qi * a.cand_ld + c];
-    } else if (a.pair_q) {
-      b = a.pair_q[pidx];
-      u = a.pair_u[pidx];
-    } else {
-      b = a.q0 + pidx / a.n;
-      u = pidx % a.n;
-    }
-    const int64_t qs0 = a.qptr[b];
-    const int hq = (int)(a.qptr[b + 1] - qs0);
-    nrows = min(kWR, hq - rb * kWR);
-    if (nrows <= 0 || u < 0 || u >= a.n) {
-      if (tid == 0) a.partial[pidx * a.rb_max + rb] = 0.f;
-      return;
-    }
-    if (tid < kWR) {
-      const bool ok = tid < nrows;
-      const int w = ok ? a.qcol[qs0 + rb * kWR + tid] : 0;
-      sm.rid[tid] = w;
-      sm.rbound[tid] = ok ? a.qval[qs0 + rb * kWR + tid] : 0.f;
-      sm.rvn[tid] = a.vnorm[w];
-      if constexpr (PREC == PREC_FP8) sm.rsc[tid] = a.vscale[w];
-      sm.rlen[tid] = 0;
-      sm.rdrop[tid] = INFINITY;
-    }
-    const int64_t s0 = a.xptr[u];
-    h = (int)(a.xptr[u + 1] - s0);
-    for (int c = tid; c < h; c += kThreads) {
-      const int w = a.xcol[s0 + c];
-      sm.cid[c] = w;
-      sm.cap[c] = __int_as_float(a.xcv[s0 + c].y);
-      sm.qn[c] = a.vnorm[w];
-      if constexpr (PREC == PREC_FP8) sm.csc[c] = a.vscale[w];
-    }
-  } else {
+  int64_t out_row0 = 0;
+  {
     // items run query-fastest within a group of queries, then row
     // block, then group: an XCD's contiguous range of items keeps a group's
     // query vectors and a row block's vectors in its L2
@@ -327,7 +218,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
       sm.rid[tid] = w;
       sm.rbound[tid] = ok ? (MODE == P1_TABLE ? a.xmax[r0 + tid] : INFINITY) : 0.f;
       sm.rvn[tid] = a.vnorm[w];
-      if constexpr (PREC == PREC_FP8) sm.rsc[tid] = a.vscale[w];
+      sm.rsc[tid] = a.vscale[w];
       sm.rlen[tid] = 0;
       sm.rdrop[tid] = INFINITY;
     }
@@ -339,12 +230,12 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
       sm.cid[c] = w;
       sm.cap[c] = a.qval[s0 + c];
       sm.qn[c] = a.vnorm[w];
-      if constexpr (PREC == PREC_FP8) sm.csc[c] = a.vscale[w];
+      sm.csc[c] = a.vscale[w];
     }
   }
   if (tid == 0) sm.qmax = 0.f;
   __syncthreads();
-  if (QK && tid < 64) {
+  if (tid < 64) {
     float mx = 0.f;
     for (int c = tid; c < h; c += 64) mx = fmaxf(mx, sm.qn[c]);
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -363,13 +254,11 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
   constexpr bool kCapStop = MODE != P1_TABLE_FULL;
 
   // ---------------- contraction ----------------
-  const unsigned char* base = PREC == PREC_F32    ? (const unsigned char*)a.V
-                                                  : (const unsigned char*)a.V8;
-  const size_t rowbytes = PREC == PREC_FP8 ? (size_t)a.m8 : (size_t)a.m_pad * 4;
+  const unsigned char* base = a.V8;
+  const size_t rowbytes = (size_t)a.m8;
   // 128-byte slices that hold real dims (the zero padding past them would
-  // add exact zeros): 4 * m4 dims of 4, 2 or 1 bytes
-  const int realbytes = 4 * a.m4 * (PREC == PREC_F32 ? 4 : 1);
-  const int nsl = min((int)(rowbytes / 128), (realbytes + 127) / 128);
+  // add exact zeros)
+  const int nsl = min((int)(rowbytes / 128), (4 * a.m4 + 127) / 128);
   const int li = lane & 31, lh = lane >> 5;
   const int arow = 32 * wave + li;
   const bool arow_ok = arow < nrows;
@@ -431,7 +320,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
         set_b(c0 + kWC);
         load_b(0);
       }
-      slice_mfma<PREC>(ntile, acc, a_cur, sm.u.st, li, lh);
+      slice_mfma(ntile, acc, a_cur, sm.u.st, li, lh);
     }
 
     // ---- selection: 64 columns at a time ----
@@ -445,115 +334,87 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
         const int t = 2 * half + tt;
         const int c = cb + 32 * tt + li;
         const float qc = c < h ? sm.qn[c] : 0.f;
-        const float csc = PREC == PREC_FP8 && c < h ? sm.csc[PREC == PREC_FP8 ? c : 0] : 1.f;
+        const float csc = c < h ? sm.csc[c] : 1.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int i = 32 * wave + 8 * (r >> 2) + 4 * lh + (r & 3);
-          if constexpr (PREC == PREC_FP8)
-            sm.u.ck[i * kCK + 32 * tt + li] = qc - 2.f * (sm.rsc[i] * csc) * acc[t][r];
-          else
-            sm.u.ck[i * kCK + 32 * tt + li] = qc - 2.f * acc[t][r];
+          sm.u.ck[i * kCK + 32 * tt + li] = qc - 2.f * (sm.rsc[i] * csc) * acc[t][r];
         }
       }
       __syncthreads();
       // this thread's 32 contiguous columns, read without branches (the
       // buffer is fully allocated; columns past h are masked afterwards)
-      using KO = KeyOps<QK, PB>;
-      using KT_ = typename KO::T;
-      KT_ kk[32];
+      uint32_t kk[32];
       const float2* krow = (const float2*)&sm.u.ck[row * kCK + 32 * sub];
 #pragma unroll
       for (int j2 = 0; j2 < 16; ++j2) {
         const float2 kv = krow[j2];
         const int c = cb + 32 * sub + 2 * j2;
-        const KT_ m0 = (row_ok && c < h) ? (KT_)0 : KO::kNone;
-        const KT_ m1 = (row_ok && c + 1 < h) ? (KT_)0 : KO::kNone;
-        kk[2 * j2] = KO::pack(kv.x, (uint32_t)c) | m0;
-        kk[2 * j2 + 1] = KO::pack(kv.y, (uint32_t)(c + 1)) | m1;
+        const uint32_t m0 = (row_ok && c < h) ? 0u : kWNone;
+        const uint32_t m1 = (row_ok && c + 1 < h) ? 0u : kWNone;
+        kk[2 * j2] = wk_pack(kv.x, (uint32_t)c) | m0;
+        kk[2 * j2 + 1] = wk_pack(kv.y, (uint32_t)(c + 1)) | m1;
       }
-      // lists of 8 or more entries: the thread's 32 keys are sorted once
-      // (bitonic network in registers) and the merge takes from their head;
-      // shorter lists scan the keys for the next one instead
-      constexpr bool kSorted = QK && KL >= 8;
-      if constexpr (kSorted) {
+      // the thread's 32 keys are sorted once (bitonic network in registers)
+      // and the merge takes from their head
 #pragma unroll
-        for (int kb = 2; kb <= 32; kb <<= 1) {
+      for (int kb = 2; kb <= 32; kb <<= 1) {
 #pragma unroll
-          for (int jb = kb >> 1; jb > 0; jb >>= 1) {
+        for (int jb = kb >> 1; jb > 0; jb >>= 1) {
 #pragma unroll
-            for (int i = 0; i < 32; ++i) {
-              const int l2 = i ^ jb;
-              if (l2 > i) {
-                const KT_ x = kk[i], y = kk[l2];
-                const KT_ lo = x < y ? x : y, hi = x < y ? y : x;
-                const bool up = (i & kb) == 0;
-                kk[i] = up ? lo : hi;
-                kk[l2] = up ? hi : lo;
-              }
+          for (int i = 0; i < 32; ++i) {
+            const int l2 = i ^ jb;
+            if (l2 > i) {
+              const uint32_t x = kk[i], y = kk[l2];
+              const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
+              const bool up = (i & kb) == 0;
+              kk[i] = up ? lo : hi;
+              kk[l2] = up ? hi : lo;
             }
           }
         }
       }
-      const KT_* cur = &sm.lst[par][row * KLS];
-      KT_* nxt = &sm.lst[par ^ 1][row * KLS];
+      const uint32_t* cur = &sm.lst[par][row * KLS];
+      uint32_t* nxt = &sm.lst[par ^ 1][row * KLS];
       const int len = row_ok ? sm.rlen[row] : 0;
       // approximate keys: the error band plus the rounding of 32-bit keys
-      const float band = !QK ? 0.f
-                             : kBandFP8 * sqrtf(sm.rvn[row]) * sm.qmax +
-                                   KO::kRound * (sm.qmax * sm.qmax + 2.f * sqrtf(sm.rvn[row]) * sm.qmax);
+      const float band = kBandFP8 * sqrtf(sm.rvn[row]) * sm.qmax +
+                         kWRound * (sm.qmax * sm.qmax + 2.f * sqrtf(sm.rvn[row]) * sm.qmax);
       int ptr = 0, w = 0;
       float P = 0.f, K0 = 0.f;
       bool cut = false;
-      KT_ last = 0;
       bool act = row_ok;
       while (__any(act)) {
-        KT_ best = KO::kNone;
+        const uint32_t mine = act ? kk[0] : kWNone;
+        const uint32_t o = (uint32_t)__shfl_xor((int)mine, 1);
+        const uint32_t best = o < mine ? o : mine;
         if (act) {
-          if constexpr (kSorted) {
-            best = kk[0];
-          } else {
-#pragma unroll
-            for (int j = 0; j < 32; ++j) {
-              const KT_ cand = kk[j] > last ? kk[j] : KO::kNone;
-              best = cand < best ? cand : best;
-            }
-          }
-        }
-        const KT_ mine = best;
-        const KT_ o = KO::shfl1(best);
-        best = o < best ? o : best;
-        if (act) {
-          const KT_ lc = ptr < len ? cur[ptr] : KO::kNone;
-          const KT_ take = lc < best ? lc : best;
-          if (take == KO::kNone) {
+          const uint32_t lc = ptr < len ? cur[ptr] : kWNone;
+          const uint32_t take = lc < best ? lc : best;
+          if (take == kWNone) {
             act = false;
-          } else if (cut && (!QK || KO::key(take) > K0 + band)) {
+          } else if (cut && wk_key(take) > K0 + band) {
             act = false;
           } else if (w >= KL) {
             // the list is full: remember the smallest key left out; the
             // final lists are certified against it after the exact re-sort
             act = false;
-            if (sub == 0) sm.rdrop[row] = fminf(sm.rdrop[row], KO::key(take));
+            if (sub == 0) sm.rdrop[row] = fminf(sm.rdrop[row], wk_key(take));
           } else {
             if (lc < best) {
               ++ptr;
-            } else {
-              last = best;
-              if constexpr (kSorted) {
-                if (mine == best) {  // this thread's head was taken
+            } else if (mine == best) {  // this thread's head was taken
 #pragma unroll
-                  for (int j = 0; j < 31; ++j) kk[j] = kk[j + 1];
-                  kk[31] = KO::kNone;
-                }
-              }
+              for (int j = 0; j < 31; ++j) kk[j] = kk[j + 1];
+              kk[31] = kWNone;
             }
             if (sub == 0) nxt[w] = take;
             ++w;
             if (!cut) {
-              P += sm.cap[KO::pos(take)];
+              P += sm.cap[wk_pos(take)];
               if (w >= kef || (kCapStop && P >= bound)) {
                 cut = true;
-                K0 = KO::key(take);
+                K0 = wk_key(take);
               }
             }
           }
@@ -572,17 +433,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
   // ---------------- exact distances of the final lists ----------------
   const int len = row_ok ? sm.rlen[row] : 0;
   const auto* L = &sm.lst[par][row * KLS];
-  if constexpr (PREC == PREC_F32) {
-    for (int l = sub; l < len; l += 2) {
-      const auto e = L[l];
-      const int pos = (int)KeyOps<QK, PB>::pos(e);
-      float d2 = sm.rvn[row] + KeyOps<QK, PB>::key(e);
-      bool need = !(d2 >= kGuardW * (sm.rvn[row] + sm.qn[pos]));
-      if (MODE != P1_TABLE_FULL && a.method == LCEMD_OMR && l == 0) need = true;
-      if (need) d2 = w_exact_d2(a.V, a.m_pad, a.m4, sm.rid[row], sm.cid[pos]);
-      sm.u.zb[row * KLS + l] = d2;
-    }
-  } else {
+  {
     constexpr int KH = (KL + 1) / 2;
     float ex[KH];
     int ps[KH];
@@ -590,7 +441,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
     for (int e = 0; e < KH; ++e) {
       ex[e] = 0.f;
       const int l = sub + 2 * e;
-      ps[e] = l < len ? (int)KeyOps<QK, PB>::pos(L[l]) : 0;
+      ps[e] = l < len ? (int)wk_pos(L[l]) : 0;
     }
     const float* vr = a.V + (size_t)sm.rid[row] * a.m_pad;
     // chunks of D dims of all h segment vectors per LDS pass, as wide as
@@ -626,10 +477,10 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
   if (sub == 0 && row_ok) {
     auto* Lw = &sm.lst[par][row * KLS];
     float* Z2 = &sm.u.zb[row * KLS];
-    if constexpr (PREC != PREC_F32) {
+    {
       // exact re-sort by (squared distance, position); the list then holds
       // positions
-      for (int i = 0; i < len; ++i) Lw[i] = KeyOps<QK, PB>::pos(Lw[i]);
+      for (int i = 0; i < len; ++i) Lw[i] = wk_pos(Lw[i]);
       for (int i = 1; i < len; ++i) {
         const uint64_t e = w_pack(Z2[i], (uint32_t)Lw[i]);
         int j = i - 1;
@@ -660,11 +511,11 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
     // shortfall after the exact re-sort is a rounding residue of the
     // capacity sum, which the last entry absorbs
     if (!covered && sm.rcut[row]) covered = true;
-    // rows redone exactly by k_fix_rows (table modes, while their list has
+    // rows redone exactly by k_fix_rows (while their list has
     // room; otherwise the launch reports overflow): a list that ran out
     // before the row's bound was covered (an ICT row deeper than the list;
     // the table may hold up to KT entries), or a cut that is not certified
-    const bool can_redo = MODE != P1_PAIR && a.fix_list != nullptr;
+    const bool can_redo = a.fix_list != nullptr;
     bool redo = false;
     if (!covered && D < h) {
       if (can_redo) redo = true;
@@ -672,7 +523,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
     }
     // a candidate left out of a full list has a key >= rdrop - half a band
     // (fp8 keys): the used entries must all be nearer
-    if (QK && D > 0 && sm.rdrop[row] < INFINITY && a.overflow) {
+    if (D > 0 && sm.rdrop[row] < INFINITY && a.overflow) {
       const float half_band = 0.5f * kBandFP8 * sqrtf(sm.rvn[row]) * sm.qmax;
       const float last_key = Z2[D - 1] - sm.rvn[row];
       const bool certified = last_key < sm.rdrop[row] - half_band - 1e-6f * (sm.rvn[row] + sm.qmax * sm.qmax);
@@ -692,7 +543,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
                    [&](int l) { return sqrtf(fmaxf(Z2[l], 0.f)); },
                    [&](int l) { return l == D - 1 ? INFINITY : sm.cap[(uint32_t)Lw[l]]; });
       if (D > a.KT && a.overflow) a.overflow[0] = 1;
-    } else if constexpr (MODE == P1_TABLE_FULL) {
+    } else {
       const int64_t o0 = (out_row0 + row) * (int64_t)a.k;
       for (int l = 0; l < a.k; ++l) {
         if (l < D) {
@@ -706,23 +557,6 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
           a.W[o0 + l] = 0.f;
         }
       }
-    } else {
-      float rem = bound, cost = 0.f;
-      for (int l = 0; l < D; ++l) {
-        const float w = sm.cap[(uint32_t)Lw[l]];
-        const float r = l == D - 1 ? rem : fminf(rem, w);
-        rem -= r;
-        cost = fmaf(r, sqrtf(fmaxf(Z2[l], 0.f)), cost);
-      }
-      sm.rcost[row] = cost;
-    }
-  }
-  if constexpr (MODE == P1_PAIR) {
-    __syncthreads();
-    if (tid == 0) {
-      float tot = 0.f;
-      for (int r = 0; r < nrows; ++r) tot += sm.rcost[r];
-      a.partial[pidx * a.rb_max + rb] = tot;
     }
   }
 }
@@ -731,7 +565,7 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
 // from the counter of its XCD (workgroup i runs on XCD i % 8), which walks a
 // contiguous eighth of the items.  No workgroup waits on another; each
 // exits once its counter passes the end of its range.
-template <int MODE, int KL, int PREC, bool LONG>
+template <int MODE, int KL>
 __global__ __launch_bounds__(kThreads, 2) void k_phase1_wide(P1Args a, int64_t total) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ int64_t s_item;
@@ -743,45 +577,35 @@ __global__ __launch_bounds__(kThreads, 2) void k_phase1_wide(P1Args a, int64_t t
     __syncthreads();
     const int64_t item = s_item;
     if (item >= hi) break;
-    wide_task<MODE, KL, PREC, LONG>(a, smem_raw, item);
+    wide_task<MODE, KL>(a, smem_raw, item);
   }
 }
 
-template <int MODE, int KL, int PREC, bool LONG>
+template <int MODE, int KL>
 static hipError_t launch_wide_one(const P1Args& a, hipStream_t s) {
-  constexpr bool QK = PREC != PREC_F32;
-  const size_t shmem = sizeof(WideSmem<KL, PREC, QK, LONG ? kSegLong : kSeg>);
-  const void* fn = (const void*)k_phase1_wide<MODE, KL, PREC, LONG>;
+  const size_t shmem = sizeof(WideSmem<KL>);
+  const void* fn = (const void*)k_phase1_wide<MODE, KL>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
-  int64_t total;
-  if (MODE == P1_PAIR) {
-    total = a.npairs * (int64_t)a.rb_max;
-  } else {
-    const int64_t nrb = (a.v_used + kWR - 1) / kWR;
-    const int64_t gw = int64_t(1) << kWGroupLog2;
-    total = (a.nq + gw - 1) / gw * nrb * gw;
-  }
+  const int64_t nrb = (a.v_used + kWR - 1) / kWR;
+  const int64_t gw = int64_t(1) << kWGroupLog2;
+  const int64_t total = (a.nq + gw - 1) / gw * nrb * gw;
   if (total <= 0) return hipSuccess;
   if (!a.work_ctr) return hipErrorInvalidValue;
   e = launch_zero_ints((int*)a.work_ctr, 16, s);
   if (e != hipSuccess) return e;
   const int grid = persistent_grid(fn, kThreads, shmem, total);
   if (grid <= 0) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_phase1_wide<MODE, KL, PREC, LONG>), dim3(grid), dim3(kThreads), shmem, s, a, total);
+  hipLaunchKernelGGL((k_phase1_wide<MODE, KL>), dim3(grid), dim3(kThreads), shmem, s, a, total);
   return hipGetLastError();
 }
 
-template <int MODE, int PREC, bool LONG>
+template <int MODE>
 static hipError_t launch_wide_mode(const P1Args& a, int KL, hipStream_t s) {
-  if (KL <= 2) return launch_wide_one<MODE, 2, PREC, LONG>(a, s);
-  if (KL <= 4) return launch_wide_one<MODE, 4, PREC, LONG>(a, s);
-  if (KL <= 8) return launch_wide_one<MODE, 8, PREC, LONG>(a, s);
-  if (KL <= 16) return launch_wide_one<MODE, 16, PREC, LONG>(a, s);
-  if (KL <= 32) return launch_wide_one<MODE, 32, PREC, LONG>(a, s);
+  if (KL <= 16) return launch_wide_one<MODE, 16>(a, s);  // (depth + 8 entries)
+  if (KL <= 32) return launch_wide_one<MODE, 32>(a, s);
   return hipErrorInvalidValue;
 }
-
 
 // Exact redo of single table rows (rows whose selection certificate
 // failed): one wave per row computes float32 squared distances to all of the
@@ -917,21 +741,11 @@ hipError_t launch_fix_rows(const P1Args& a, int mode, int count, hipStream_t s) 
   return hipGetLastError();
 }
 
-int phase1_wide_rows() { return kWR; }
-
-hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, int prec, int seg_hmax, hipStream_t s) {
-  if (seg_hmax > kSegLong) return hipErrorInvalidValue;
-  if (prec == PREC_F32) {  // float32 table modes: launch_phase1_rows
-    if (mode != P1_PAIR) return hipErrorInvalidValue;
-    return seg_hmax > kSeg ? launch_wide_mode<P1_PAIR, PREC_F32, true>(a, KL, s)
-                           : launch_wide_mode<P1_PAIR, PREC_F32, false>(a, KL, s);
-  }
-  if (prec == PREC_FP8) {
-    if (seg_hmax > kSeg || !a.V8 || !a.vscale || a.m8 % 128 != 0) return hipErrorInvalidValue;
-    if (mode == P1_TABLE) return launch_wide_mode<P1_TABLE, PREC_FP8, false>(a, KL, s);
-    if (mode == P1_TABLE_FULL) return launch_wide_mode<P1_TABLE_FULL, PREC_FP8, false>(a, KL, s);
-  }
-  return hipErrorInvalidValue;  // bf16 keys: launch_phase1_bf16; reduced-precision pairs use float32 keys
+hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, hipStream_t s) {
+  if (!a.V8 || !a.vscale || a.m8 % 128 != 0) return hipErrorInvalidValue;
+  if (mode == P1_TABLE) return launch_wide_mode<P1_TABLE>(a, KL, s);
+  if (mode == P1_TABLE_FULL) return launch_wide_mode<P1_TABLE_FULL>(a, KL, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace lcemd

@@ -87,3 +87,23 @@ def test_distances(L, method, k, m):
         got = ctx.distances(q.rowptr, q.col, q.val, method=method, k=k, direction=d)
         P.assert_distances(got, orc.matrix(q.rowptr, q.col, q.val, method, k, d), f"{method} {d}")
     ctx.close()
+
+
+@pytest.mark.parametrize("method,k", [("omr", 1), ("act", 2), ("act", 7), ("act", 30)])
+@pytest.mark.parametrize("m", [2, 27, 60])
+def test_candidate_pairs(L, method, k, m):
+    """Q2D of candidate pairs: row blocks of 128 query words (partial sums of
+    64 at up to 28 dims), segments around the tile and pass edges."""
+    rng = np.random.default_rng(44)
+    v = 600
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    db = _queries(rng, v, [1, 2, 31, 32, 33, 64, 65, 127, 128, 129, 300, 513, 40, 90])
+    q = _queries(rng, v, [1, 31, 33, 63, 64, 65, 127, 128, 129, 192, 193, 300, 520])
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    orc = O.Oracle(V, db.rowptr, db.col, db.val)
+    print(f"[gpu] pairs {method} k={k} m={m}", flush=True)
+    idx, dist = ctx.topl(q.rowptr, q.col, q.val, 5, method=method, k=k, direction="sym")
+    want = orc.matrix(q.rowptr, q.col, q.val, method, k, "sym")
+    off = sum(P.check_topl(idx[b], dist[b], want[b], 5, f"{method} query {b}") for b in range(q.n))
+    assert off <= 2
+    ctx.close()
