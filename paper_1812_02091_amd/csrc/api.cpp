@@ -316,7 +316,7 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
       int rc = wsget(c, "bf16_qmax", (size_t)std::max<int64_t>(a.nq, 1), a.qmx);
       if (rc) return rc;
     }
-    HIPCHK(c, launch_phase1_bf16(a, mode, depth, c->stream));
+    HIPCHK(c, launch_phase1_bf16(a, mode, depth, seg_hmax, c->stream));
     return LCEMD_OK;
   }
   if (prec == LCEMD_FP32 && depth <= 32 && !c->force_kernel) {

@@ -159,7 +159,7 @@ hipError_t launch_phase1_rows(const P1Args& a, int mode, int depth, hipStream_t 
 // bfloat16 table modes (lists of depth + 8 <= 32, segments <= kSegShort words,
 // rows of at most kBf16MaxDims dims)
 bool phase1_bf16_fits(int mb, int seg_hmax, int depth);
-hipError_t launch_phase1_bf16(const P1Args& a, int mode, int depth, hipStream_t s);
+hipError_t launch_phase1_bf16(const P1Args& a, int mode, int depth, int seg_hmax, hipStream_t s);
 hipError_t launch_fix_rows(const P1Args& a, int mode, int count, hipStream_t s);
 hipError_t launch_pair_reduce(const float* partial, int64_t npairs, int rb_max, float* out,
                               int64_t out_ld, int64_t per_row, hipStream_t s);

@@ -3,14 +3,14 @@
 // capacities), selected on bfloat16 contractions and finished with float32
 // distances recomputed from the float32 embeddings.
 //
-// Work item: one query against a block of 256 used vocabulary rows; a
-// workgroup of 8 waves, wave w owning rows 32w..32w+31.  The contraction
-// runs on the 32x32x16 bf16 MFMA with the vocabulary rows as its N operand
-// -- each lane holds all K steps of its row in registers for the whole item
-// -- and the query's words as its M operand, staged in LDS 128 words at a
-// time and read by every wave.  After a 32-word tile, lane l therefore
-// holds 16 keys of its own row l % 32: words 8(r/4) + 4(l/32) + (r%4) of the
-// tile, r = 0..15.
+// Work item: one query against a block of 256 used vocabulary rows, a
+// workgroup of eight waves, wave w owning rows 32w .. 32w + 31.  The
+// contraction runs on the 32x32x16 bf16 MFMA with the vocabulary rows as its
+// N operand (each lane reads its row's dims straight from global memory, a
+// 64-dim slice ahead) and the query's words as its M operand (a slice of 64
+// words staged in LDS for the eight waves, double-buffered), so that after a
+// pass a lane holds 32 keys of its own row in its accumulators: words 32 t +
+// 8 (r / 4) + 4 (lane / 32) + r % 4.
 //
 // Keys are approximate squared distances.  The bf16 rows (built at load)
 // hold -2 v in their first m dims, 1 in the next three and a three-piece
@@ -27,22 +27,37 @@
 // the packed keys) of its cut key: a word outside that band is farther,
 // exactly, than every word up to the cut, so it can never be needed.
 //
-// Selection.  Each lane keeps the smallest keys it has seen for its row in
-// a sorted register list (packed key | word position; a bitonic sort makes
-// the list from the first tile, later tiles insert their candidates by a
-// min/max network).  A key above the row's threshold (cut key + band,
-// from the lanes' own lists, which bound the row's) is no candidate.
-// After the last tile the two lanes of a row merge their lists; keys pushed
-// out of a full list are remembered (the smallest of them) and the row is
-// redone exactly unless every used entry is provably nearer.
+// Selection, in registers: packed keys (position in the 9 low bits) go 16 at
+// a time through a sorting network and into the lane's sorted list, the two
+// lanes of a row merge theirs at the end.  The list is the row's LK smallest
+// keys; what it leaves out is no nearer than its last entry, and the row is
+// redone exactly unless every used entry is provably nearer than that.
 //
 // Exact distances.  Every listed candidate gets a float32 dot product with
-// the float32 row: the query's float32 vectors are staged through LDS a
-// chunk of dims at a time, each of a row's two lanes takes half of every
-// chunk's dims for all the row's entries, and the halves are added in a
-// fixed order.  Where cancellation could bite the distance is taken by
-// direct differences (identical words: exactly 0).  The list is re-sorted
-// by (distance, position) and cut as Alg. 3 / the capacity bound say.
+// the float32 row: the query's float32 vectors are staged through LDS W dims
+// at a time, and of every RD = 64 dims (32 for queries of more than 256
+// words) each of a row's two lanes sums one half over all chunks; the halves
+// are added in a fixed order.  Where cancellation could bite the distance is
+// taken by direct differences (identical words: exactly 0).  The list is
+// re-sorted by (distance, position) and cut as Alg. 3 / the capacity bound
+// say.
+//
+// Bound: the recompute, about three fifths of an item's time, whose LDS reads
+// (a dot product reads the whole float32 word, 1.2 KB at 300 dims, from rows
+// that no order makes conflict-free: about twice the conflict-free time) take
+// half of a CU's cycles; the rest is the phases of a workgroup waiting on
+// each other through barriers.
+//
+// Measured on ACT k = 8 tables of 300-dim words, CU cycles per query x 256
+// rows.  The form before this one (rows and words both staged in LDS, keys
+// inserted into LDS lists one at a time, queue merges): 76 k at 32 words,
+// 88 k at 64, 110 k at 128; this one: 63 k, 68 k, 89 k (256 queries of about
+// 118 words over 72 k rows: 69 ms, now 55 ms).  Workgroups of four waves and
+// passes of up to 128 words, three to a CU: 64 k, 72 k, 95 k, and 0.30 ms
+// instead of 0.22 ms for one query (an item of half the rows stages the same
+// words).  The row's dims all in registers and a tile of 32 words at a time:
+// 68 ms; the words of the next list entry read ahead of the sums: 99 k against
+// 75 k cycles for that phase (registers spill).
 #include <algorithm>
 
 #include "internal.h"
@@ -54,82 +69,124 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 namespace {
 
-constexpr int kBT = 512;              // threads per workgroup (one workgroup per CU)
+constexpr int kBT = 512;              // threads per workgroup
 constexpr int kBR = 256;              // rows per item (8 waves x 32)
-constexpr int kBW = 128;              // query words per staged chunk
-constexpr int kBMaxMb = kBf16MaxDims; // bf16 row width held in registers
-constexpr int kBKS = kBMaxMb / 16;    // K steps held in registers
-constexpr int kBQa = 2 * kBMaxMb + 16; // bytes per staged word (16 bytes of padding)
+constexpr int kBW = 64;               // query words per pass
+constexpr int kBStride = 144;         // bytes per staged word slice (128 + 16 pad: conflict-free 16-byte reads)
+constexpr int kBMaxMb = kBf16MaxDims; // bf16 row width
 constexpr int kBSeg = kSegShort;      // query words per item
-constexpr int kBStg = 34;             // u32 per row: candidate staging [2][17] / final list
 constexpr int kBGroup = 32;           // queries per item group (query-fastest): a row block stays in L2 for 32 items
 constexpr uint32_t kNone = 0xffffffffu;
 constexpr uint32_t kPosMask = 511u;   // 9 position bits (words < 512)
 // twice the largest relative rounding of a packed key: 2 * 2^(9 - 23)
 constexpr float kQuant = 1.f / 8192.f;
 constexpr float kGuard = 0.25f;       // cancellation guard of the float32 form
+constexpr uint32_t kNoD2 = 0x7f800000u;
 
-struct BfSmem {
-  union {
-    unsigned char qa[kBW * kBQa];   // bf16 query words (M operand), one chunk
-    float qf[kBSeg * 36];           // float32 query vectors, a chunk of dims (h (RD + 4) floats)
-    float zb[kBR * 32];             // exact squared distances of the lists
-  } u;
-  uint32_t lst[kBR * kBStg];        // candidate staging, then the final lists
-  int cid[kBSeg];
-  float cap[kBSeg];
-  float qn[kBSeg];
-  int rid[kBR];
-  float rbound[kBR];
-  float rvn[kBR];
-  float reps[kBR];
-  float rband[kBR];
-  int rlen[kBR];
-  uint32_t rdrop[kBR];
-  int rflag[kBR];  // 2: the merged list has its cut; 1: full without a cut; 0: neither
-  int rorder[kBR];  // rows by list length (the recompute's row of each lane pair)
-  int lhist[34];    // rows per list length, then the next free rank of each length
-  float qmax;
-  float eqmax;
+// LDS of a workgroup: a union of the contraction's word slice, the lists
+// on their way to the recompute's lanes and its staged float32 words; then
+// the query's words and the rows.
+struct BfLds {
+  unsigned char* st;   // [2][kBW][kBStride]
+  uint32_t* lst;       // [kBR][LK + 1]
+  float* qf;           // [h][W + 4]
+  int* cid;            // [hp]
+  float* cap;
+  float* qn;
+  int* rid;            // [kBR] each
+  float* rbound;
+  float* rvn;
+  float* reps;
+  uint32_t* rdrop;
+  int* rkey;           // length and row, for the order of length
+  int* rflag;          // the merged list has its cut
+  int* rorder;         // rows by list length (the recompute's row of each lane pair)
 };
-
-__device__ __forceinline__ uint32_t pk(float d2, int j) {
-  // d2 >= 0: its bits order like the values; the 9 low bits give way to j
-  return (__float_as_uint(d2) & ~kPosMask) | (uint32_t)j;
+// dims staged at a time for the recompute: what four pieces a thread hold
+__host__ __device__ inline int bf_stage(int h) { return h <= 256 ? 32 : 16; }
+__host__ __device__ inline int bf_words(int hmax) { return hmax + kBW; }
+__host__ __device__ inline size_t bf_union(int hmax, int LK) {
+  const size_t a = 2 * (size_t)kBW * kBStride, b = sizeof(uint32_t) * kBR * (LK + 1);
+  const int h32 = hmax < 256 ? hmax : 256;
+  const size_t c = sizeof(float) * (h32 * 36 > hmax * 20 ? h32 * 36 : hmax * 20);
+  const size_t m = a > b ? (a > c ? a : c) : (b > c ? b : c);
+  return (m + 15) / 16 * 16;
 }
+__host__ __device__ inline size_t bf_bytes(int hmax, int LK) {
+  return bf_union(hmax, LK) + 12 * (size_t)bf_words(hmax) + 4 * (size_t)kBR * 8;
+}
+__device__ __forceinline__ BfLds bf_lds(unsigned char* base, int hmax, int LK) {
+  BfLds s;
+  s.st = base;
+  s.lst = (uint32_t*)base;
+  s.qf = (float*)base;
+  // (the rows first: rkey is read 16 bytes at a time)
+  int* p = (int*)(base + bf_union(hmax, LK));
+  s.rid = p;
+  s.rbound = (float*)(p + kBR);
+  s.rvn = (float*)(p + 2 * kBR);
+  s.reps = (float*)(p + 3 * kBR);
+  s.rdrop = (uint32_t*)(p + 4 * kBR);
+  s.rkey = p + 5 * kBR;
+  s.rflag = p + 6 * kBR;
+  s.rorder = p + 7 * kBR;
+  p += 8 * kBR;
+  const int hp = bf_words(hmax);
+  s.cid = p;
+  s.cap = (float*)(p + hp);
+  s.qn = (float*)(p + 2 * hp);
+  return s;
+}
+
 __device__ __forceinline__ float pk_key(uint32_t k) { return __uint_as_float(k & ~kPosMask); }
 __device__ __forceinline__ int pk_pos(uint32_t k) { return (int)(k & kPosMask); }
-__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
-__device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a < b ? b : a; }
 
-// ascending bitonic sort of 16 packed keys
-__device__ __forceinline__ void sort16(uint32_t (&k)[16]) {
-#pragma unroll
-  for (int kb = 2; kb <= 16; kb <<= 1) {
-#pragma unroll
-    for (int jb = kb >> 1; jb > 0; jb >>= 1) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int l = i ^ jb;
-        if (l > i) {
-          const uint32_t x = k[i], y = k[l];
-          const bool up = (i & kb) == 0;
-          k[i] = up ? umin(x, y) : umax(x, y);
-          k[l] = up ? umax(x, y) : umin(x, y);
-        }
-      }
-    }
-  }
+// compare-exchange of packed keys and of exact (distance, position) pairs:
+// both order as unsigned 32 / 64-bit numbers, the latter (never negative)
+// also as float64
+__device__ __forceinline__ uint32_t kmin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t kmax(uint32_t a, uint32_t b) { return a < b ? b : a; }
+__device__ __forceinline__ double kmin(double a, double b) {
+  double d;
+  asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ double kmax(double a, double b) {
+  double d;
+  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+template <typename T>
+__device__ __forceinline__ void cas(T& a, T& b) {
+  const T x = a, y = b;
+  a = kmin(x, y);
+  b = kmax(x, y);
 }
 
-// insert c into the ascending list a; returns what fell off the end
-template <int LK>
-__device__ __forceinline__ uint32_t insert(uint32_t (&a)[LK], uint32_t c) {
-  const uint32_t out = umax(a[LK - 1], c);
+// Batcher's odd-even merge sort of N (a power of two) keys
+template <int N, typename T>
+__device__ __forceinline__ void net_sort(T* k) {
 #pragma unroll
-  for (int i = LK - 1; i > 0; --i) a[i] = umax(a[i - 1], umin(a[i], c));
-  a[0] = umin(a[0], c);
-  return out;
+  for (int p = 1; p < N; p <<= 1)
+#pragma unroll
+    for (int q = p; q >= 1; q >>= 1)
+#pragma unroll
+      for (int j = q % p; j + q < N; j += 2 * q)
+#pragma unroll
+        for (int i = 0; i < q; ++i)
+          if (i + j + q < N && (i + j) / (2 * p) == (i + j + q) / (2 * p)) cas(k[i + j], k[i + j + q]);
+}
+
+// a (ascending, LK) := the LK smallest of a and b (ascending, NB <= LK)
+template <int LK, int NB>
+__device__ __forceinline__ void net_merge(uint32_t* a, const uint32_t* b) {
+#pragma unroll
+  for (int i = 0; i < NB; ++i) a[LK - 1 - i] = kmin(a[LK - 1 - i], b[i]);
+#pragma unroll
+  for (int h = LK >> 1; h > 0; h >>= 1)
+#pragma unroll
+    for (int i = 0; i < LK; ++i)
+      if ((i & h) == 0) cas(a[i], a[i + h]);
 }
 
 // Cut of an ascending list (Alg. 3 / Lemma 1-2): the first entry where
@@ -172,79 +229,136 @@ __device__ __forceinline__ float exact_d2(const float* __restrict__ V, int m_pad
   return s;
 }
 
-// Stage words [c0, c0 + cw) of the query in LDS as the M operand (their
-// query-form bf16 rows).  Wave w takes words c0 + w, c0 + w + 8, ...; a
-// lane copies one 16-byte piece (mb <= 512: at most 64 pieces).
-__device__ __forceinline__ void stage_words(const P1Args& a, BfSmem& sm, int c0, int cw, int mb) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int npc = mb / 8;
-  for (int c = wave; c < cw; c += kBT / 64)
-    if (lane < npc)
-      *(uint4*)(sm.u.qa + c * kBQa + 16 * lane) = *(const uint4*)(a.Vbq + (size_t)sm.cid[c0 + c] * mb + 8 * lane);
-}
-
-// Float32 squared distances of row xr's listed words (lane pair xr, sub):
-// the query's float32 vectors are staged RD dims at a time; lane sub takes
-// dims [sub RD/2, (sub+1) RD/2) of every chunk for all the row's entries,
-// its row dims loaded one chunk ahead, and the halves are added in a fixed
-// order.  Results (by direct differences where cancellation could bite) go
-// to zb.  m4dims: the real dims rounded up to 4.
-template <int RD, int LK>
-__device__ __forceinline__ void recompute(const P1Args& a, BfSmem& sm, int h, int m4dims, int xr, int sub) {
-  constexpr int RS = RD + 4;      // floats per staged word
-  constexpr int HALF = RD / 2;
-  constexpr int Q = HALF / 4;     // float4 of a lane's half chunk
-  constexpr int N4 = RD / 4;      // float4 per staged word and chunk
-  const int tid = threadIdx.x;
-  const int xlen = sm.rlen[xr];
-  const int xw = sm.rid[xr];
-  int pos[LK];
-  float dot[LK];
-#pragma unroll
-  for (int e = 0; e < LK; ++e) {
-    pos[e] = e < xlen ? pk_pos(sm.lst[xr * kBStg + e]) : 0;
-    dot[e] = 0.f;
+// What a thread has in flight for the contraction: the lane's row's next
+// slice, and the pieces of the words' next slice that it stages.
+struct BfFlight {
+  const unsigned char* rptr;
+  const unsigned char* wptr;
+  uint4 r[4];
+  uint4 w;
+  __device__ __forceinline__ void words(const uint16_t* vbq, size_t rowbytes, const int* cid, int tid) {
+    wptr = (const unsigned char*)vbq + (size_t)cid[tid >> 3] * rowbytes + (tid & 7) * 16;
   }
-  // the longest list of the wave bounds its (uniform) entry loop; shorter
-  // lists compute on word 0 and drop the result
-  int wlen = xlen;
-  for (int o = 32; o > 0; o >>= 1) wlen = max(wlen, __shfl_xor(wlen, o));
-  const int per = (h * N4 + kBT - 1) / kBT;  // float4 a thread stages per chunk (<= 8)
-  const int nch = (m4dims + RD - 1) / RD;
-  float4 nx[8];
-  auto fetch = [&](int d0) {
+  __device__ __forceinline__ void load_rows(int sl) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int f = tid + i * kBT;
-      const int c = f / N4, q4 = f % N4, d = d0 + 4 * q4;
-      nx[i] = (i < per && c < h && d < a.m_pad) ? *(const float4*)(a.V + (size_t)sm.cid[c] * a.m_pad + d)
-                                              : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  const float* vrow = a.V + (size_t)xw * a.m_pad + sub * HALF;
-  float4 vc[Q];
-  fetch(0);
-  for (int ch = 0; ch < nch; ++ch) {
-    const int d0 = ch * RD;
+    for (int i = 0; i < 4; ++i) r[i] = *(const uint4*)(rptr + sl * 128 + i * 16);
+  }
+  __device__ __forceinline__ void load_words(int sl) { w = *(const uint4*)(wptr + sl * 128); }
+};
+
+// One pass: the 64 words from c0 on, all slices, then their keys into the
+// list.
+template <int LK>
+__device__ __forceinline__ void bf16_pass(const BfLds& sm, BfFlight& fl, uint32_t (&lst)[LK], int c0, int h, int nsl,
+                                          const uint16_t* vbq, size_t rowbytes, int tid) {
+  constexpr int NT = kBW / 32;
+  const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  floatx16 acc[NT];
 #pragma unroll
-    for (int q = 0; q < Q; ++q)  // the row's chunk, in flight through the staging
-      vc[q] = d0 + 4 * q + sub * HALF < a.m_pad ? *(const float4*)(vrow + d0 + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();  // the previous chunk is consumed
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int f = tid + i * kBT;
-      const int c = f / N4, q4 = f % N4;
-      if (i < per && c < h) *(float4*)(&sm.u.qf[c * RS + 4 * q4]) = nx[i];
+    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+  const bool more = c0 + kBW < h;
+#pragma unroll 1
+  for (int sl = 0; sl < nsl; ++sl) {
+    unsigned char* st = sm.st + (sl & 1) * (kBW * kBStride);  // (last read two slices ago, before a barrier)
+    *(uint4*)(st + (tid >> 3) * kBStride + (tid & 7) * 16) = fl.w;
+    if (sl + 1 < nsl) {
+      fl.load_words(sl + 1);
+    } else if (more) {  // the next pass's first slice
+      fl.words(vbq, rowbytes, sm.cid + c0 + kBW, tid);
+      fl.load_words(0);
     }
     __syncthreads();
-    if (ch + 1 < nch) fetch(d0 + RD);  // in flight during this chunk's products
-    float4 qv[Q];
-    // fully unrolled (entries skipped by a wave-uniform test, not a loop
-    // exit), so pos[] and dot[] stay in fixed registers
+    // lane half lh supplies dims [32 lh, 32 lh + 32) of the 64-dim slice
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bf16x8 rv = *reinterpret_cast<const bf16x8*>(&fl.r[s]);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            *(const bf16x8*)(st + (32 * t + li) * kBStride + lh * 64 + s * 16), rv, acc[t], 0, 0, 0);
+    }
+    // (into the registers just read: a second set would cost a workgroup per CU)
+    if (sl + 1 < nsl) fl.load_rows(sl + 1);
+    else if (more) fl.load_rows(0);
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int j0 = c0 + 32 * t;
+    if (j0 >= h) break;
+    const int jb = j0 | (lh << 2);
+    uint32_t k[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      // d2 >= 0: its bits order like the values; the 9 low bits give way to the position
+      k[r] = (__float_as_uint(fmaxf(acc[t][r], 0.f)) & ~kPosMask) | (uint32_t)jb | (uint32_t)(8 * (r >> 2) + (r & 3));
+    if (j0 + 32 > h) {  // words past the query's
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if ((jb | (8 * (r >> 2) + (r & 3))) >= h) k[r] = kNone;
+    }
+    net_sort<16>(k);
+    net_merge<LK, 16>(lst, k);
+  }
+  // (an odd slice count: the next pass starts on the buffer that was read last)
+  if (nsl & 1) __syncthreads();
+}
+
+// Float32 dot products of row xr's listed words (a row's two lanes, sub): of
+// every RD dims lane sub takes [sub RD / 2, (sub + 1) RD / 2), in order,
+// staged W dims (W / 2 of each half) at a time.  off[e]: the word's staged
+// row in floats.  The row's dims are loaded a stage ahead, the words' while
+// the stage before them is worked on (up to 4 pieces a thread; the rest of a
+// long query's at the stage).
+template <int W, int LK>
+__device__ __forceinline__ void recompute(const P1Args& a, const BfLds& sm, int h, int dims, int RD, int rid, int sub,
+                                          int wlen, const int (&off)[LK], float (&dot)[LK]) {
+  constexpr int WS = W + 4;    // floats per staged word
+  constexpr int Q = W / 8;     // float4 of a lane's half of a stage
+  constexpr int N4 = W / 4;    // float4 per staged word
+  constexpr int kAhead = 4;
+  const int tid = threadIdx.x;
+  const int pieces = h * N4;
+  const int per = RD / W;      // stages per chunk of RD dims (1, 2 or 4)
+  const int nst = (dims + RD - 1) / RD * per;
+  // a stage's first dim of either half
+  auto dim0 = [&](int i, int half) { return i / per * RD + half * (RD / 2) + i % per * (W / 2); };
+  auto fetch1 = [&](int i, int f) {
+    const int c = f / N4, q4 = f % N4;
+    const int d = dim0(i, q4 / Q) + 4 * (q4 % Q);
+    return f < pieces && d < a.m_pad ? *(const float4*)(a.V + (size_t)sm.cid[c] * a.m_pad + d)
+                                     : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  auto put1 = [&](int f, const float4& x) {
+    if (f < pieces) *(float4*)(&sm.qf[f / N4 * WS + f % N4 * 4]) = x;
+  };
+  float4 nx[kAhead], vn[Q];
+  const float* vrow = a.V + (size_t)rid * a.m_pad;
+  auto fetch = [&](int i) {
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) nx[k] = fetch1(i, tid + k * kBT);
+    const int d = dim0(i, sub);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      vn[q] = d + 4 * q < a.m_pad ? *(const float4*)(vrow + d + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  fetch(0);
+#pragma unroll 1
+  for (int i = 0; i < nst; ++i) {
+    __syncthreads();  // the previous stage (at first: the lists) is consumed
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) put1(tid + k * kBT, nx[k]);
+    float4 vc[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) vc[q] = vn[q];
+    __syncthreads();
+    if (i + 1 < nst) fetch(i + 1);
 #pragma unroll
     for (int e = 0; e < LK; ++e) {
-      if (e < wlen) {
-        const float* qp = &sm.u.qf[pos[e] * RS + sub * HALF];
+      if (e < wlen) {  // uniform (a loop exit would have off[] and dot[] indexed at run time)
+        const float* qp = sm.qf + off[e] + sub * (W / 2);
+        float4 qv[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) qv[q] = *(const float4*)(qp + 4 * q);
         float t = dot[e];
@@ -259,27 +373,13 @@ __device__ __forceinline__ void recompute(const P1Args& a, BfSmem& sm, int h, in
       }
     }
   }
-  __syncthreads();  // the staged vectors are dead: zb may reuse their LDS
-  const float vn = sm.rvn[xr];
-#pragma unroll
-  for (int e = 0; e < LK; ++e) {
-    const float o = __shfl_xor(dot[e], 1);
-    if (e < xlen && (e & 1) == sub) {
-      const float full = sub == 0 ? dot[e] + o : o + dot[e];  // fixed order: even half first
-      const float qn = sm.qn[pos[e]];
-      float d2 = (vn + qn) - 2.f * full;
-      if (!(d2 >= kGuard * (vn + qn))) d2 = exact_d2(a.V, a.m_pad, a.m4, xw, sm.cid[pos[e]]);
-      sm.u.zb[xr * 32 + e] = d2;
-    }
-  }
 }
 
-template <int MODE, int LK, int NKS>
-__device__ __forceinline__ void bf16_task(const P1Args& a, BfSmem& sm, int64_t item) {
+template <int MODE, int LK>
+__device__ __forceinline__ void bf16_task(const P1Args& a, const BfLds& sm, int64_t item) {
   static_assert(LK == 16 || LK == 32, "list sizes 16 or 32");
-  static_assert(NKS >= 1 && NKS <= kBKS, "K steps held in registers");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lh = lane >> 5, li = lane & 31;
+  const int li = lane & 31, lh = lane >> 5;
   constexpr bool kCapStop = MODE != P1_TABLE_FULL;
 
   // ---------------- item decode ----------------
@@ -291,44 +391,30 @@ __device__ __forceinline__ void bf16_task(const P1Args& a, BfSmem& sm, int64_t i
   const int64_t r0 = sb * kBR;
   const int64_t b = a.q0 + qi;
   const int nrows = (int)min((int64_t)kBR, a.v_used - r0);
-  const int64_t out_row0 = qi * a.v_used + r0;
   const int64_t s0 = a.qptr[b];
   const int h = (int)(a.qptr[b + 1] - s0);
   if (h <= 0) return;  // padding slot of a fixed-size batch
-  const int m = 4 * a.m4 <= a.m_pad ? a.m4 * 4 : a.m_pad;  // real dims rounded up to 4
-  const int mb = a.mb;  // == 16 * NKS (checked by the launcher)
 
   // one 16-byte record per row and per query word (built per call by
   // k_bf16_info): word id, bound / weight, |v|^2, |v - bf16(v)|
-  if (tid < kBR) {
-    const bool ok = tid < nrows;
-    const float4 ri = ok ? a.rinfo[r0 + tid] : make_float4(0.f, 0.f, 0.f, 0.f);
-    sm.rid[tid] = __float_as_int(ri.x);
-    sm.rbound[tid] = ok ? (MODE == P1_TABLE ? ri.y : INFINITY) : 0.f;
-    sm.rvn[tid] = ri.z;
-    sm.reps[tid] = ri.w;  // |e_v|, replaced by the row's eps below
-    sm.rflag[tid] = 0;
+  const int row = 32 * wave + li;
+  const bool row_ok = row < nrows;
+  const float4 ri = a.rinfo[r0 + (row_ok ? row : 0)];
+  for (int c = tid; c < h + kBW; c += kBT) {
+    const float4 q = c < h ? a.qinfo[s0 + c] : make_float4(0.f, 0.f, 0.f, 0.f);  // (word 0 past the query's)
+    sm.cid[c] = __float_as_int(q.x);
+    sm.cap[c] = q.y;
+    sm.qn[c] = q.z;
   }
-  for (int c = tid; c < h; c += kBT) {
-    const float4 qi = a.qinfo[s0 + c];
-    sm.cid[c] = __float_as_int(qi.x);
-    sm.cap[c] = qi.y;
-    sm.qn[c] = qi.z;
-  }
-  if (tid == 0) {  // the query's largest |q|^2 and |q - bf16(q)| (k_bf16_qmax)
-    const float2 mx = a.qmx[qi];
-    sm.qmax = sqrtf(mx.x) * 1.0001f;
-    sm.eqmax = mx.y;
-  }
-  __syncthreads();
-  if (tid < kBR) {
-    const float nv = sqrtf(sm.rvn[tid]) * 1.0001f, qm = sm.qmax;
-    const float ev = sm.reps[tid];
+  const float2 mx = a.qmx[qi];  // the query's largest |q|^2 and |q - bf16(q)| (k_bf16_qmax)
+  const float bound = row_ok ? (MODE == P1_TABLE ? ri.y : INFINITY) : 0.f;
+  float eps, band;
+  {
+    const float qm = sqrtf(mx.x) * 1.0001f, nv = sqrtf(ri.z) * 1.0001f;
     // |v_b| <= |v| (1 + 2^-8); K + 6 float32 accumulation steps
-    const float eps = 2.02f * (ev * qm + nv * sm.eqmax) +
-                      (float)(mb + 8) * 6.0e-8f * (sm.rvn[tid] + qm * qm + 2.f * nv * qm) * 1.1f + 1e-30f;
-    sm.reps[tid] = eps;
-    sm.rband[tid] = 2.f * eps + kQuant * (sm.rvn[tid] + qm * qm + 2.f * nv * qm);
+    eps = 2.02f * (ri.w * qm + nv * mx.y) +
+          (float)(a.mb + 8) * 6.0e-8f * (ri.z + qm * qm + 2.f * nv * qm) * 1.1f + 1e-30f;
+    band = 2.f * eps + kQuant * (ri.z + qm * qm + 2.f * nv * qm);
   }
   int kef;
   if constexpr (MODE == P1_TABLE_FULL) {
@@ -339,251 +425,203 @@ __device__ __forceinline__ void bf16_task(const P1Args& a, BfSmem& sm, int64_t i
     else if (a.method == LCEMD_RWMD) kef = 1;
     else kef = min(a.k, h);
   }
+  __syncthreads();
 
-  // ---------------- row operand: all K steps in registers ----------------
-  const int row = 32 * wave + li;
-  const bool row_ok = row < nrows;
-  uint4 bfr[NKS];
-  {
-    const uint16_t* bp = a.Vb + (size_t)sm.rid[row] * mb + 8 * lh;
-#pragma unroll
-    for (int s = 0; s < NKS; ++s) bfr[s] = *(const uint4*)(bp + 16 * s);
-  }
-  __syncthreads();  // row bands ready
-  const float band = sm.rband[row];
-  const float bound = sm.rbound[row];
-
+  // ---------------- contraction and selection ----------------
   uint32_t lst[LK];
 #pragma unroll
   for (int i = 0; i < LK; ++i) lst[i] = kNone;
-  uint32_t drop = kNone;  // smallest key pushed out of a full list
-  float theta = INFINITY;
-  bool first = true;
-  uint32_t* stg = &sm.lst[row * kBStg + lh * 17];
-
-  for (int c0 = 0; c0 < h; c0 += kBW) {
-    const int cw = min(kBW, h - c0);
-    if (c0 > 0) __syncthreads();  // every wave is done with the previous chunk
-    stage_words(a, sm, c0, cw, mb);
-    __syncthreads();
-    const int nt = (cw + 31) >> 5;
-    for (int t = 0; t < nt; ++t) {
-      floatx16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-      const unsigned char* ap = sm.u.qa + (32 * t + li) * kBQa + 16 * lh;
-      // A fragments read three steps ahead of their MFMA (LDS latency)
-      constexpr int kAhead = 3;
-      bf16x8 av[kAhead];
-#pragma unroll
-      for (int s = 0; s < kAhead && s < NKS; ++s) av[s] = *(const bf16x8*)(ap + 32 * s);
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) {
-        const bf16x8 cur = av[s % kAhead];
-        if (s + kAhead < NKS) av[s % kAhead] = *(const bf16x8*)(ap + 32 * (s + kAhead));
-        const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&bfr[s]);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, bv, acc, 0, 0, 0);
-      }
-      const int jb = c0 + 32 * t + 4 * lh;
-      if (first) {
-        uint32_t kk[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = jb + 8 * (r >> 2) + (r & 3);
-          kk[r] = (row_ok && j < h) ? pk(fmaxf(acc[r], 0.f), j) : kNone;
-        }
-        sort16(kk);
-#pragma unroll
-        for (int i = 0; i < LK; ++i) lst[i] = i < 16 ? kk[i] : kNone;
-        first = false;
-      } else {
-        int cnt = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = jb + 8 * (r >> 2) + (r & 3);
-          const float d2 = fmaxf(acc[r], 0.f);
-          const bool cand = row_ok && j < h && d2 < theta;
-          stg[cnt] = pk(d2, j);  // slot cnt is overwritten unless this key counts
-          cnt += cand ? 1 : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          if (!__any(i < cnt)) break;
-          const uint32_t cnd = i < cnt ? stg[i] : kNone;
-          drop = umin(drop, insert<LK>(lst, cnd));
-        }
-      }
-      // threshold from this lane's list; the row's cut key is at most it
-      const uint32_t K0 = list_cut<LK, kCapStop>(lst, sm.cap, kef, bound);
-      // (no cut yet: no threshold -- keys pushed out of a full list are
-      // remembered by insert(), never dropped silently)
-      float th = K0 != kNone ? pk_key(K0) * (1.f + kQuant) + band : INFINITY;
-      th = fminf(th, __shfl_xor(th, 32));
-      theta = fminf(theta, th);
-    }
-  }
-
-  // ---------------- the row's list: merge of its two lanes ----------------
   {
+    const size_t rowbytes = (size_t)a.mb * 2;
+    const int nsl = a.mb >> 6;  // 64-dim slices
+    BfFlight fl;
+    fl.rptr = (const unsigned char*)a.Vb + (size_t)__float_as_int(ri.x) * rowbytes + lh * 64;
+    fl.words(a.Vbq, rowbytes, sm.cid, tid);
+    fl.load_rows(0);
+    fl.load_words(0);
+#pragma unroll 1
+    for (int c0 = 0; c0 < h; c0 += kBW) bf16_pass<LK>(sm, fl, lst, c0, h, nsl, a.Vbq, rowbytes, tid);
+    __syncthreads();  // every wave is done with the word slices
+  }
+  {  // the row's list: merge of its two lanes
     uint32_t other[LK];
 #pragma unroll
     for (int i = 0; i < LK; ++i) other[i] = (uint32_t)__shfl_xor((int)lst[i], 32);
-    uint32_t lost = kNone;
-#pragma unroll
-    for (int i = 0; i < LK; ++i) {
-      const uint32_t x = lst[i], y = other[LK - 1 - i];
-      lst[i] = umin(x, y);
-      lost = umin(lost, umax(x, y));
-    }
-    // lst is now bitonic and holds the LK smallest: clean it
-#pragma unroll
-    for (int jb = LK >> 1; jb > 0; jb >>= 1) {
-#pragma unroll
-      for (int i = 0; i < LK; ++i) {
-        const int l = i ^ jb;
-        if (l > i) {
-          const uint32_t x = lst[i], y = lst[l];
-          lst[i] = umin(x, y);
-          lst[l] = umax(x, y);
-        }
-      }
-    }
-    drop = umin(umin(drop, lost), (uint32_t)__shfl_xor((int)drop, 32));
+    net_merge<LK, LK>(lst, other);
+  }
+  {
     const uint32_t K0 = list_cut<LK, kCapStop>(lst, sm.cap, kef, bound);
-    int len = 0;
     const float lim = K0 != kNone ? pk_key(K0) * (1.f + kQuant) + band : INFINITY;
+    int len = 0;
 #pragma unroll
     for (int i = 0; i < LK; ++i)
       if (lst[i] != kNone && pk_key(lst[i]) <= lim) len = i + 1;
+    uint32_t* L = sm.lst + row * (LK + 1);
     // both lanes hold the same list: each writes half of it
-    uint32_t* L = &sm.lst[row * kBStg];
 #pragma unroll
     for (int i = 0; i < LK; ++i)
       if ((i >= LK / 2) == (lh == 1)) L[i] = lst[i];
-    if (lh == 0 && row_ok) {
-      sm.rlen[row] = len;
-      sm.rdrop[row] = drop;
-      // a full list without a cut is an ICT row deeper than the list
-      sm.rflag[row] = K0 != kNone ? 2 : (lst[LK - 1] != kNone ? 1 : 0);
+    if (lh == 0) {
+      sm.rid[row] = __float_as_int(ri.x);
+      sm.rbound[row] = bound;
+      sm.rvn[row] = ri.z;
+      sm.reps[row] = eps;
+      // words left out of a full list have keys of at least its last entry
+      sm.rdrop[row] = h > LK ? lst[LK - 1] : kNone;
+      sm.rflag[row] = K0 != kNone ? 1 : 0;
+      sm.rkey[row] = (row_ok ? len : 0) * kBR + (kBR - 1 - row);
     }
-    if (lh == 0 && !row_ok) sm.rlen[row] = 0;
   }
   __syncthreads();
 
   // ---------------- exact float32 distances of the listed words ----------------
-  // rows by list length (counting sort): the lanes of a wave then take rows
-  // of similar lengths, so a wave's entry loop is not set by one long list
-  // among short ones (which row a lane pair takes does not change results)
-  if (tid < 34) sm.lhist[tid] = 0;
-  __syncthreads();
-  if (tid < kBR) atomicAdd(&sm.lhist[sm.rlen[tid]], 1);
-  __syncthreads();
-  if (tid == 0) {
-    int acc0 = 0;
-    for (int L = 33; L >= 0; --L) {  // longest lists first
-      const int c = sm.lhist[L];
-      sm.lhist[L] = acc0;
-      acc0 += c;
+  // rows by list length, longest first (a row's rank: how many keys are
+  // larger), so that the lanes of a wave have lists of similar lengths
+  if (tid < kBR) {
+    const int me = sm.rkey[tid];
+    int rank = 0;
+#pragma unroll 8
+    for (int i = 0; i < kBR; i += 4) {
+      const int4 o = *(const int4*)(sm.rkey + i);
+      rank += (o.x > me) + (o.y > me) + (o.z > me) + (o.w > me);
     }
+    sm.rorder[rank] = tid;
   }
   __syncthreads();
-  if (tid < kBR) sm.rorder[atomicAdd(&sm.lhist[sm.rlen[tid]], 1)] = tid;
-  __syncthreads();
   const int xr = sm.rorder[tid >> 1], sub = tid & 1;
-  if (h <= 256) recompute<64, LK>(a, sm, h, m, xr, sub);
-  else recompute<32, LK>(a, sm, h, m, xr, sub);
-  __syncthreads();
+  const int len = sm.rkey[xr] / kBR, xid = sm.rid[xr];
+  // the longest list of the wave bounds its (uniform) entry loop; shorter
+  // lists compute on word 0 and drop the result
+  const int wlen = __builtin_amdgcn_readfirstlane(len);  // (the wave's first row has its longest list)
+  const int W = bf_stage(h), ws = W + 4;
+  int off[LK];  // the listed words' staged rows
+  float dot[LK];
+#pragma unroll
+  for (int e = 0; e < LK; ++e) {
+    off[e] = e < len ? pk_pos(sm.lst[xr * (LK + 1) + e]) * ws : 0;
+    dot[e] = 0.f;
+  }
+  const int dims = 4 * a.m4 <= a.m_pad ? a.m4 * 4 : a.m_pad;  // real dims rounded up to 4
+  const int RD = h <= 256 ? 64 : 32;
+  if (W == 32) recompute<32, LK>(a, sm, h, dims, RD, xid, sub, wlen, off, dot);
+  else recompute<16, LK>(a, sm, h, dims, RD, xid, sub, wlen, off, dot);
 
   // ---------------- re-sort, cut, certificate, outputs ----------------
-  if (sub == 0 && xr < nrows) {
-    uint32_t* Lw = &sm.lst[xr * kBStg];
-    float* Z2 = &sm.u.zb[xr * 32];
-    const int len = sm.rlen[xr];
-    for (int i = 0; i < len; ++i) Lw[i] = (uint32_t)pk_pos(Lw[i]);
-    for (int i = 1; i < len; ++i) {
-      const float z = Z2[i];
-      const uint32_t p = Lw[i];
-      int j = i - 1;
-      while (j >= 0 && (Z2[j] > z || (Z2[j] == z && Lw[j] > p))) {
-        Lw[j + 1] = Lw[j];
-        Z2[j + 1] = Z2[j];
-        --j;
-      }
-      Lw[j + 1] = p;
-      Z2[j + 1] = z;
-    }
-    const float xb = sm.rbound[xr];
-    int D = 0;
-    bool covered = false;
-    {
-      float Pc = 0.f;
-      for (int l = 0; l < len; ++l) {
-        ++D;
-        Pc += sm.cap[Lw[l]];
-        if (D >= kef) { covered = true; break; }
-        if (kCapStop) {
-          if (Pc >= xb) { covered = true; break; }
-          if (a.method == LCEMD_OMR && l == 0 && Z2[0] != 0.f) { covered = true; break; }
-        }
+  // both lanes of a row do the same arithmetic and share the stores
+  const float vn = sm.rvn[xr];
+  double ex[LK];
+  uint32_t need = 0;  // entries that cancellation could have hurt
+#pragma unroll
+  for (int e = 0; e < LK; ++e) {
+    uint32_t bits = kNoD2;
+    const int pos = W == 32 ? (int)((uint32_t)off[e] / 36u) : (int)((uint32_t)off[e] / 20u);
+    if (e < wlen) {
+      const float full = dot[e] + __shfl_xor(dot[e], 1);  // (the sum of the halves, either way round)
+      const float sq = vn + sm.qn[pos];
+      const float d2 = sq - 2.f * full;
+      if (e < len) {
+        bits = __float_as_uint(d2);
+        if (!(d2 >= kGuard * sq)) need |= 1u << e;
       }
     }
-    // the merge cut this list (k_eff or capacity reached in key order); a
-    // shortfall after the exact re-sort is a rounding residue of the
-    // capacity sum, which the last entry absorbs
-    if (!covered && sm.rflag[xr] == 2) covered = true;
-    const bool can_redo = a.fix_list != nullptr;
-    bool redo = false;
-    if (!covered && D < h) {
-      if (can_redo) redo = true;
-      else if (a.overflow) a.overflow[0] = 1;
+    ex[e] = __hiloint2double((int)bits, pos);
+  }
+  // (rare: one copy of the loop over the dims, entry by entry)
+  while (need) {
+    const int e = __ffs(need) - 1;
+    need &= need - 1;
+    int pos = 0;
+#pragma unroll
+    for (int i = 0; i < LK; ++i) pos = i == e ? __double2loint(ex[i]) : pos;
+    const float d2 = exact_d2(a.V, a.m_pad, a.m4, xid, sm.cid[pos]);
+#pragma unroll
+    for (int i = 0; i < LK; ++i) ex[i] = i == e ? __hiloint2double(__float_as_int(d2), pos) : ex[i];
+  }
+  net_sort<LK>(ex);
+  if (xr >= nrows) return;  // (no barrier past this point)
+  const float xb = sm.rbound[xr];
+  float z[LK], w[LK];
+  int pos[LK];
+  int D = 0;
+  bool covered = false;
+  float Pc = 0.f, last = 0.f;
+#pragma unroll
+  for (int l = 0; l < LK; ++l) {
+    z[l] = 0.f;
+    w[l] = 0.f;
+    pos[l] = 0;
+    const uint32_t bits = (uint32_t)__double2hiint(ex[l]);
+    const bool live = !covered && bits != kNoD2;
+    if (!__any(live)) continue;
+    if (live) {
+      const float d2 = __uint_as_float(bits);
+      pos[l] = __double2loint(ex[l]);
+      z[l] = sqrtf(fmaxf(d2, 0.f));
+      w[l] = sm.cap[pos[l]];
+      last = d2;
+      ++D;
+      Pc += w[l];
+      covered = D >= kef;
+      if (kCapStop) covered = covered || Pc >= xb || (a.method == LCEMD_OMR && l == 0 && d2 != 0.f);
     }
-    // a word pushed out of a full list has an exact squared distance of at
+  }
+  // the merge cut this list (k_eff or capacity reached in key order); a
+  // shortfall after the exact re-sort is a rounding residue of the
+  // capacity sum, which the last entry absorbs
+  if (!covered && sm.rflag[xr]) covered = true;
+  const int64_t r = r0 + xr;
+  if (sub == 0) {
+    bool redo = !covered && D < h;
+    // a word left out of a full list has an exact squared distance of at
     // least its key minus eps: every used entry must be nearer
     const uint32_t dr = sm.rdrop[xr];
-    if (dr != kNone && D > 0 && !(Z2[D - 1] < pk_key(dr) - sm.reps[xr])) {
-      if (can_redo) redo = true;
-      else if (a.overflow) a.overflow[0] = 1;
-    }
+    if (dr != kNone && D > 0 && !(last < pk_key(dr) - sm.reps[xr])) redo = true;
     if (redo) {
-      const int slot = atomicAdd(a.fix_count, 1);
-      if (slot < a.fix_cap) a.fix_list[slot] = out_row0 + xr;
-      else if (a.overflow) a.overflow[0] = 1;
+      bool listed = false;
+      if (a.fix_list) {
+        const int slot = atomicAdd(a.fix_count, 1);
+        listed = slot < a.fix_cap;
+        if (listed) a.fix_list[slot] = qi * a.v_used + r;
+      }
+      if (!listed && a.overflow) a.overflow[0] = 1;
     }
-    if constexpr (MODE == P1_TABLE) {
-      const int64_t flat = out_row0 + xr;
-      zw_write_row(a.ZW, a.zw_nq, a.KT, flat / a.v_used, flat % a.v_used, D,
-                   [&](int l) { return sqrtf(fmaxf(Z2[l], 0.f)); },
-                   [&](int l) { return l == D - 1 ? INFINITY : sm.cap[Lw[l]]; });
-      if (D > a.KT && a.overflow) a.overflow[0] = 1;
-    } else {
-      const int64_t o0 = (out_row0 + xr) * (int64_t)a.k;
-      for (int l = 0; l < a.k; ++l) {
-        if (l < D) {
-          const int p = (int)Lw[l];
-          a.S[o0 + l] = p;
-          a.Z[o0 + l] = sqrtf(fmaxf(Z2[l], 0.f));
-          a.W[o0 + l] = sm.cap[p];
-        } else {
-          a.S[o0 + l] = -1;
-          a.Z[o0 + l] = 0.f;
-          a.W[o0 + l] = 0.f;
-        }
+  }
+  if constexpr (MODE == P1_TABLE) {
+    if (D > a.KT && a.overflow) a.overflow[0] = 1;
+#pragma unroll
+    for (int l = 0; l < LK; l += 2) {
+      if (((l >> 1) & 1) == sub && l < D && l < a.KT) {
+        const bool two = l + 1 < D && l + 1 < a.KT;
+        *zw_pair(a.ZW, a.zw_nq, a.KT, qi, r, l >> 1) =
+            make_float4(z[l], l == D - 1 ? INFINITY : w[l], two ? z[l + 1] : 0.f,
+                        two ? (l + 1 == D - 1 ? INFINITY : w[l + 1]) : 0.f);
+      }
+    }
+  } else {
+    const int64_t o0 = (qi * a.v_used + r) * (int64_t)a.k;
+#pragma unroll
+    for (int l = 0; l < LK; ++l) {
+      if ((l & 1) == sub && l < a.k) {
+        const bool in = l < D;
+        a.S[o0 + l] = in ? pos[l] : -1;
+        a.Z[o0 + l] = in ? z[l] : 0.f;
+        a.W[o0 + l] = in ? w[l] : 0.f;
       }
     }
   }
 }
 
-// Persistent grid: one workgroup per CU pulls items from the counter of its
-// XCD (workgroup i runs on XCD i % 8), which walks a contiguous eighth of the
-// items; every workgroup exits once its counter passes its range.
-template <int MODE, int LK, int NKS>
-__global__ __launch_bounds__(kBT, 1) void k_phase1_bf16(P1Args a, int64_t total) {
+// Persistent grid: as many workgroups as stay resident pull items from the
+// counter of their XCD (workgroup i runs on XCD i % 8), which walks a
+// contiguous eighth of the items; the counter is read one item ahead.  Every
+// workgroup exits once its counter passes its range.
+template <int MODE, int LK>
+__global__ __launch_bounds__(kBT, LK == 16 ? 4 : 2) void k_phase1_bf16(P1Args a, int64_t total, int hmax) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ int64_t s_item;
-  BfSmem& sm = *reinterpret_cast<BfSmem*>(smem_raw);
+  const BfLds sm = bf_lds(smem_raw, hmax, LK);
   const int xcd = blockIdx.x & 7;
   const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
-  // the counter is read one item ahead: its round trip overlaps an item
   unsigned long long nxt = 0;
   if (threadIdx.x == 0) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
   while (true) {
@@ -595,14 +633,14 @@ __global__ __launch_bounds__(kBT, 1) void k_phase1_bf16(P1Args a, int64_t total)
     __syncthreads();
     const int64_t item = s_item;
     if (item >= hi) break;
-    bf16_task<MODE, LK, NKS>(a, sm, item);
+    bf16_task<MODE, LK>(a, sm, item);
   }
 }
 
-template <int MODE, int LK, int NKS>
-hipError_t launch_bf16_one(const P1Args& a, hipStream_t s) {
-  const size_t shmem = sizeof(BfSmem);
-  const void* fn = (const void*)k_phase1_bf16<MODE, LK, NKS>;
+template <int MODE, int LK>
+hipError_t launch_bf16_one(const P1Args& a, int hmax, hipStream_t s) {
+  const size_t shmem = bf_bytes(hmax, LK);
+  const void* fn = (const void*)k_phase1_bf16<MODE, LK>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
   const int64_t nsb = (a.v_used + kBR - 1) / kBR;
@@ -613,7 +651,7 @@ hipError_t launch_bf16_one(const P1Args& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int grid = persistent_grid(fn, kBT, shmem, total);
   if (grid <= 0) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_phase1_bf16<MODE, LK, NKS>), dim3(grid), dim3(kBT), shmem, s, a, total);
+  hipLaunchKernelGGL((k_phase1_bf16<MODE, LK>), dim3(grid), dim3(kBT), shmem, s, a, total, hmax);
   return hipGetLastError();
 }
 
@@ -663,22 +701,9 @@ bool phase1_bf16_fits(int mb, int seg_hmax, int depth) {
   return mb <= kBMaxMb && mb % 64 == 0 && seg_hmax <= kBSeg && depth + 8 <= 32;
 }
 
-template <int MODE, int LK>
-hipError_t launch_bf16_width(const P1Args& a, hipStream_t s) {
-  switch (a.mb / 16) {  // K steps of the rows: one instantiation per width
-    case 4: return launch_bf16_one<MODE, LK, 4>(a, s);
-    case 8: return launch_bf16_one<MODE, LK, 8>(a, s);
-    case 12: return launch_bf16_one<MODE, LK, 12>(a, s);
-    case 16: return launch_bf16_one<MODE, LK, 16>(a, s);
-    case 20: return launch_bf16_one<MODE, LK, 20>(a, s);
-    case 24: return launch_bf16_one<MODE, LK, 24>(a, s);
-  }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_phase1_bf16(const P1Args& a, int mode, int depth, hipStream_t s) {
+hipError_t launch_phase1_bf16(const P1Args& a, int mode, int depth, int seg_hmax, hipStream_t s) {
   if (!a.Vb || !a.Vbq || !a.vres || !a.rinfo || !a.qinfo || !a.qmx || a.mb % 64 != 0 || a.mb > kBMaxMb ||
-      a.mb < a.m + 6)
+      a.mb < a.m + 6 || seg_hmax < 1 || seg_hmax > kBSeg)
     return hipErrorInvalidValue;
   {
     // grid-stride over the rows and the launch's query words (at most qnnz)
@@ -694,9 +719,11 @@ hipError_t launch_phase1_bf16(const P1Args& a, int mode, int depth, hipStream_t 
     }
   }
   const bool small = depth + 8 <= 16;
-  if (mode == P1_TABLE) return small ? launch_bf16_width<P1_TABLE, 16>(a, s) : launch_bf16_width<P1_TABLE, 32>(a, s);
+  if (mode == P1_TABLE)
+    return small ? launch_bf16_one<P1_TABLE, 16>(a, seg_hmax, s) : launch_bf16_one<P1_TABLE, 32>(a, seg_hmax, s);
   if (mode == P1_TABLE_FULL)
-    return small ? launch_bf16_width<P1_TABLE_FULL, 16>(a, s) : launch_bf16_width<P1_TABLE_FULL, 32>(a, s);
+    return small ? launch_bf16_one<P1_TABLE_FULL, 16>(a, seg_hmax, s)
+                 : launch_bf16_one<P1_TABLE_FULL, 32>(a, seg_hmax, s);
   return hipErrorInvalidValue;
 }
 
