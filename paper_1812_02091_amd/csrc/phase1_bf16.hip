@@ -51,8 +51,8 @@
 // Measured on ACT k = 8 tables of 300-dim words, CU cycles per query x 256
 // rows.  The form before this one (rows and words both staged in LDS, keys
 // inserted into LDS lists one at a time, queue merges): 76 k at 32 words,
-// 88 k at 64, 110 k at 128; this one: 63 k, 68 k, 89 k (256 queries of about
-// 118 words over 72 k rows: 69 ms, now 55 ms).  Workgroups of four waves and
+// 88 k at 64, 110 k at 128; this one: 63 k, 68 k, 89 k (192 queries of about
+// 118 words over 485 k rows: 69 ms, now 55 ms).  Workgroups of four waves and
 // passes of up to 128 words, three to a CU: 64 k, 72 k, 95 k, and 0.30 ms
 // instead of 0.22 ms for one query (an item of half the rows stages the same
 // words).  The row's dims all in registers and a tile of 32 words at a time:
@@ -214,7 +214,8 @@ __device__ __forceinline__ uint32_t list_cut(const uint32_t (&a)[LK], const floa
   return K0;
 }
 
-__device__ __forceinline__ float exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b) {
+__device__ __forceinline__ float exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b, float an) {
+  if (a == b && an < INFINITY) return 0.f;  // (an = |a|^2: a row of finite numbers against itself)
   const float4* x = (const float4*)(V + (size_t)a * m_pad);
   const float4* y = (const float4*)(V + (size_t)b * m_pad);
   float s = 0.f;
@@ -533,7 +534,7 @@ __device__ __forceinline__ void bf16_task(const P1Args& a, const BfLds& sm, int6
     int pos = 0;
 #pragma unroll
     for (int i = 0; i < LK; ++i) pos = i == e ? __double2loint(ex[i]) : pos;
-    const float d2 = exact_d2(a.V, a.m_pad, a.m4, xid, sm.cid[pos]);
+    const float d2 = exact_d2(a.V, a.m_pad, a.m4, xid, sm.cid[pos], vn);
 #pragma unroll
     for (int i = 0; i < LK; ++i) ex[i] = i == e ? __hiloint2double(__float_as_int(d2), pos) : ex[i];
   }

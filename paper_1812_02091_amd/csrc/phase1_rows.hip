@@ -5,18 +5,26 @@
 // of the query's mass summed per block of rows.
 //
 // Bound: the float32 MFMA (157 TFLOP/s; 134-150 in a loop of nothing but
-// MFMAs and their LDS reads; here the pipe is busy 74 % of the time at 128
-// words).  Float32 MFMAs and vector instructions hardly run side by side on a
-// SIMD, so every vector instruction adds to the contraction's time, and
-// keeping them few is what this kernel is about.
+// MFMAs and their LDS reads; here 113 on lists of 4, 110 on lists of 8).
+// Float32 MFMAs and vector instructions hardly run side by side on a SIMD, so
+// every vector instruction adds to the contraction's time, and keeping them
+// few is what this kernel is about.
 //
-// Contraction: a workgroup of four waves takes 128 vocabulary rows against
-// one query; wave w owns rows 32w .. 32w + 31.  The rows are the MFMA's N
-// operand (each lane reads its row's dims straight from global memory, a
-// 32-dim slice ahead), the query's words its M operand (a slice of 128 words
-// staged in LDS for the four waves), so that after a pass a lane holds 64
-// keys of its own row -- words 32 t + 8 (r / 4) + 4 (lane / 32) + r % 4 -- in
-// its accumulators.
+// Contraction: a workgroup of four waves takes 128 vocabulary rows; wave w
+// owns rows 32w .. 32w + 31.  The rows are the MFMA's N operand (each lane
+// reads its row's dims straight from global memory, a 32-dim slice ahead),
+// the queries' words its M operand (a slice of two or three tiles of 32
+// staged in LDS for the four waves), so that after a pass a lane holds 32 or
+// 48 keys of its own row -- words 32 t + 8 (r / 4) + 4 (lane / 32) + r % 4 --
+// in its accumulators.
+//
+// Queries: an item takes up to eight, their words end to end, so that tiles
+// are full (a query alone wastes half a tile, 13 % at 118 words) and the next
+// query's slices are in flight while a query ends.  The tile in which a
+// query ends is selected from once per query that has words there, the
+// others' keys masked.  18,000 documents of ~118 words x 5,300 words of 61
+// others and back, RWMD: items of one query 54.8 ms, of eight 48.7; 250
+// queries, k = 16: 29.1 -> 26.3 ms.
 //
 // Selection: in registers.  A key and its word's position make one 64-bit
 // number that orders by (key, position), compared as float64 (the key's bits
@@ -27,13 +35,15 @@
 // nothing has to be certified or redone but ICT rows deeper than the list.
 // The kernel this replaced put every key through LDS (two barriers per 64
 // words) and merged lists held there entry by entry with a band for quantised
-// keys.  62,000 words x 300 dims x 250 queries of ~118 words: RWMD 17.0 ->
-// 13.6 ms, k = 8 20.5 -> 14.6, k = 16 22.4 -> 15.0; 784 grid words x 20,000
-// images, k = 8, 7.7 -> 2.9 ms.
+// keys.  62,000 words x 300 dims x 250 queries of ~118 words, against it:
+// RWMD 17.0 -> 11.6 ms, k = 16 22.4 -> 13.5; 784 grid words x 20,000 images,
+// k = 8, 7.7 -> 2.6 ms.
 //
 // Distances: |v|^2 + key unless cancellation could bite (below a quarter of
-// |v|^2 + |c|^2), where it is recomputed by direct differences (identical
-// words give exactly 0).
+// |v|^2 + |c|^2), where it is recomputed by direct differences.  Most of
+// those are a word against itself, which is 0 without a look at its dims
+// (the loop over 300 dims was 9 % of the RWMD matrix above: in most items
+// some row meets its own word).
 #include <algorithm>
 #include <type_traits>
 
@@ -46,30 +56,34 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 namespace {
 
 constexpr int kFR = 128;        // rows per workgroup
-constexpr int kFC = 128;        // words per pass
 constexpr int kFStride = 144;   // bytes per staged word slice (128 + 16 pad: conflict-free 16-byte reads)
-constexpr int kFSeg = LCEMD_MAX_HIST;
+constexpr int kFCat = 2 * LCEMD_MAX_HIST;  // words of an item's queries in LDS at a time
 constexpr float kFGuard = 0.25f;
 constexpr uint32_t kNoKey = 0x7f800000u;  // +inf: above every key
 
-// Tiles per pass at most.  Embeddings of at most 28 dims (SMALL) have one
-// slice and little to contract, so what counts there is how many waves hide
-// the set-up and the selection: with two tiles a wave of lists of up to 8
-// entries fits 168 registers, three workgroups per CU instead of two (four,
-// at 128 registers, spill: 20,000 images x 784 words, k = 8, 2.9 against 2.6
-// ms).
-template <bool SMALL>
-constexpr int max_tiles() { return SMALL ? 2 : 4; }
-template <int LK, bool SMALL>
-constexpr int groups_per_cu() { return SMALL && LK <= 8 ? 3 : 2; }
+// Tiles per pass at most, and workgroups per CU.  Two tiles let a wave of
+// lists of up to 8 entries fit 168 registers, three workgroups per CU, which
+// hide each other's latencies: lists of 1, items of eight queries, two tiles
+// and three workgroups 48.7 ms, three and two 50.3, four and two 52.0 (the
+// RWMD matrix above).  Longer lists spill there (k = 16: 30.2 ms against 26.4
+// with three tiles and two workgroups, 28.0 with four), and the pair mode has
+// one short segment per item, for which two workgroups of wider passes are
+// the faster (2.1 against 2.3 ms over 250 queries).  Embeddings of at most 28
+// dims (SMALL) have one slice and little to contract, so what counts there is
+// how many waves hide the set-up and the selection (four workgroups, at 128
+// registers, spill: 20,000 images x 784 words, k = 8, 2.9 against 2.6 ms).
+template <int MODE, int LK, bool SMALL>
+constexpr int max_tiles() { return SMALL || (MODE != P1_PAIR && LK <= 8) ? 2 : 3; }
+template <int MODE, int LK, bool SMALL>
+constexpr int groups_per_cu() { return LK <= 8 && (SMALL || MODE != P1_PAIR) ? 3 : 2; }
 
-template <bool SMALL>
+template <int MODE, int LK, bool SMALL>
 struct F32Smem {
-  unsigned char st[SMALL ? 1 : 2][32 * max_tiles<SMALL>() * kFStride];  // word slices, double-buffered
+  unsigned char st[SMALL ? 1 : 2][32 * max_tiles<MODE, LK, SMALL>() * kFStride];  // word slices, double-buffered
   float rcost[kFR];       // pair mode: the rows' costs
-  int cid[kFSeg + kFC];   // word 0 past the query's words, up to a pass's end
-  float cap[kFSeg + kFC];
-  float qn[kFSeg + kFC];  // +inf there: those keys are above every key
+  int cid[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];   // word 0 past the queries' words, up to a pass's end
+  float cap[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];
+  float qn[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];  // +inf there: those keys are above every key
 };
 
 // queries per item group: 8, or 32 over vocabularies of at least 2^18 used
@@ -77,6 +91,14 @@ struct F32Smem {
 // leave L2 (1M words: phase 1 -2 %; 70,000 words: 8 keeps a group's query
 // vectors within an XCD's L2)
 __host__ __device__ inline int f32_group_log2(int64_t v_used) { return v_used >= (int64_t(1) << 18) ? 5 : 3; }
+
+// Table modes over embeddings of more than 28 dims take several queries per
+// item, their words end to end.  (SMALL: with next to nothing to contract the
+// selection over all tiles at once, unrolled, is worth more: 2.6 ms against
+// 2.9 on the images above.)
+template <int MODE, bool SMALL>
+constexpr bool streams() { return MODE != P1_PAIR && !SMALL; }
+constexpr int kStreamLog2 = 3;
 
 __device__ __forceinline__ double dmin(double a, double b) {
   double d;
@@ -148,11 +170,14 @@ __device__ __forceinline__ void take16(double (&lst)[LK], double (&k)[16]) {
 // hold the real dims.  FOUR: four partial sums over pairs of groups (at most
 // 28 dims), else one sum.
 template <bool FOUR>
-__device__ __forceinline__ float f32_exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b) {
+__device__ __forceinline__ float f32_exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b,
+                                              float an) {
   const float4* x = (const float4*)(V + (size_t)a * m_pad);
   const float4* y = (const float4*)(V + (size_t)b * m_pad);
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+  if (a == b && an < INFINITY) return 0.f;  // (an = |a|^2: a row of finite numbers against itself)
   const int n4 = FOUR ? (m4 + 1) & ~1 : m4;  // (m_pad / 4 is even; the padding adds exact zeros)
+#pragma unroll 4
   for (int d = 0; d < n4; ++d) {
     const float4 p = x[d], q = y[d];
     const float e0 = p.x - q.x, e1 = p.y - q.y, e2 = p.z - q.z, e3 = p.w - q.w;
@@ -174,8 +199,8 @@ __device__ __forceinline__ float f32_exact_d2(const float* __restrict__ V, int m
 // One staged slice on NT 32-word tiles (NT fixed at compile time so the
 // MFMAs issue back to back without branches); the first njq of its four
 // groups of MFMAs (the others hold no real dims and would add exact zeros).
-template <int NT, bool FULL>
-__device__ __forceinline__ void f32_slice(floatx16 (&acc)[NT], const float4 (&rows)[4], const unsigned char* st, int li,
+template <int NT, bool FULL, int MAXT>
+__device__ __forceinline__ void f32_slice(floatx16 (&acc)[MAXT], const float4 (&rows)[4], const unsigned char* st, int li,
                                           int lh, int njq) {
   // lane half lh supplies dims [16 lh, 16 lh + 16) of the 32-dim slice
 #pragma unroll
@@ -200,9 +225,9 @@ __device__ __forceinline__ void f32_slice(floatx16 (&acc)[NT], const float4 (&ro
 // the words' next slice that it stages (word 32 it + tid / 8, piece tid % 8).
 struct Flight {
   const unsigned char* rptr;
-  const unsigned char* wptr[4];
+  const unsigned char* wptr[3];
   float4 r[4];
-  float4 w[4];
+  float4 w[3];
   template <int NT>
   __device__ __forceinline__ void words(const unsigned char* vb, size_t rowbytes, const int* cid, int tid) {
 #pragma unroll
@@ -224,43 +249,36 @@ struct Flight {
   }
 };
 
-// One pass: NT tiles of words from c0 on, all slices, then their keys into
-// the list (live: the wave has rows; it stages words either way).  A pass is a function of its own tile count so that the
-// accumulators stay in the same registers throughout (a switch inside the
-// slice loop had them copied, 200 moves a slice).
-template <int NT, int LK, bool SMALL>
-__device__ __forceinline__ void f32_pass(F32Smem<SMALL>& sm, Flight& fl, double (&lst)[LK], int c0, bool more,
-                                         bool live, int nsl, int last_njq, const unsigned char* vb, size_t rowbytes,
-                                         int tid) {
+// One pass: the dot products of NT tiles of words from c0 on, all slices
+// (live: the wave has rows; it stages words either way).  A pass is a
+// function of its own tile count so that the accumulators stay in the same
+// registers throughout (a switch inside the slice loop had them copied, 200
+// moves a slice).
+template <int NT, int MODE, int LK, bool SMALL>
+__device__ __forceinline__ void f32_pass(F32Smem<MODE, LK, SMALL>& sm, Flight& fl, floatx16 (&acc)[max_tiles<MODE, LK, SMALL>()], int c0,
+                                         bool more, bool live, int nsl, int last_njq, const unsigned char* vb,
+                                         size_t rowbytes, int tid) {
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
-  floatx16 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  float4 rows[4];
   auto stage = [&](int buf) {
 #pragma unroll
     for (int it = 0; it < NT; ++it)
       *(float4*)(sm.st[buf] + (32 * it + (tid >> 3)) * kFStride + (tid & 7) * 16) = fl.w[it];
   };
-  auto take_rows = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rows[i] = fl.r[i];
-  };
   // (one barrier a slice; two, with one buffer, took the same time)
   __syncthreads();  // the previous pass's slices are consumed
   stage(0);
-  take_rows();
   if constexpr (!SMALL) {
-    if (nsl > 1) fl.load<NT>(1);
+    if (nsl > 1) fl.load_words<NT>(1);
     __syncthreads();
     for (int sl = 0; sl < nsl - 1; ++sl) {
       stage((sl + 1) & 1);  // (last read a slice ago, before the barrier)
       if (sl + 2 < nsl) fl.load_words<NT>(sl + 2);
-      if (live) f32_slice<NT, true>(acc, rows, sm.st[sl & 1], li, lh, 4);
-      take_rows();
-      if (sl + 2 < nsl) fl.load_rows(sl + 2);
+      if (live) f32_slice<NT, true>(acc, fl.r, sm.st[sl & 1], li, lh, 4);
+      fl.load_rows(sl + 1);
       __syncthreads();
     }
   } else {
@@ -268,200 +286,284 @@ __device__ __forceinline__ void f32_pass(F32Smem<SMALL>& sm, Flight& fl, double 
   }
   if (more) {  // the next pass's first slice (it has at most NT tiles)
     fl.words<NT>(vb, rowbytes, sm.cid + c0 + 32 * NT, tid);
-    fl.load<NT>(0);
+    fl.load_words<NT>(0);
   }
-  if (!live) return;
-  f32_slice<NT, false>(acc, rows, sm.st[SMALL ? 0 : (nsl - 1) & 1], li, lh, last_njq);
+  if (live) f32_slice<NT, false>(acc, fl.r, sm.st[SMALL ? 0 : (nsl - 1) & 1], li, lh, last_njq);
+  if (more) fl.load_rows(0);
+}
 
-  // ---- selection: 16 keys of the lane's row per tile ----
+// The lane's row.
+struct RowInfo {
+  int64_t r;    // table modes: table row
+  int id;       // word
+  float vn;     // |v|^2
+  float bound;  // table modes: largest database weight; pair mode: weight
+  bool ok;
+};
+
+// A finished list (merged over the row's two lanes): distances and cut.
+// Both lanes of a row do the same arithmetic.
+template <int MODE, int LK, bool SMALL>
+struct Cut {
+  float z[LK], w[LK];
+  int pos[LK];  // in the item's words
+  int D = 0;
+  bool covered = false;
+  __device__ __forceinline__ Cut(const P1Args& a, const F32Smem<MODE, LK, SMALL>& sm, double (&lst)[LK], const RowInfo& row,
+                                 int h) {
+    constexpr bool kCapStop = MODE != P1_TABLE_FULL;
+    {
+      double other[LK];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int pbase = (c0 + 32 * t) | (lh << 2);  // position bits that the 16 keys share
-    double k[16];
+      for (int i = 0; i < LK; ++i)
+        other[i] = __hiloint2double(__shfl_xor(__double2hiint(lst[i]), 32), __shfl_xor(__double2loint(lst[i]), 32));
+      net_merge<LK, LK>(lst, other);
+    }
+    int kef;
+    if constexpr (MODE == P1_TABLE_FULL) {
+      kef = min(a.k, h);
+    } else {
+      if (a.method == LCEMD_ICT) kef = h;
+      else if (a.method == LCEMD_OMR) kef = min(2, h);
+      else if (a.method == LCEMD_RWMD) kef = 1;
+      else kef = min(a.k, h);
+    }
+    float Pc = 0.f;
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      const float4 qn = *(const float4*)(sm.qn + c0 + 32 * t + 8 * rq + 4 * lh);
-      const float qv[4] = {qn.x, qn.y, qn.z, qn.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int bits = __float_as_int(qv[i] - 2.f * acc[t][4 * rq + i]);
-        k[4 * rq + i] = __hiloint2double(bits, (bits >> 31) ^ (pbase | (8 * rq + i)));
+    for (int l = 0; l < LK; ++l) {
+      z[l] = 0.f;
+      w[l] = 0.f;
+      pos[l] = 0;
+      const int bits = __double2hiint(lst[l]);
+      const bool live = row.ok && !covered && bits != (int)kNoKey;
+      if (!__any(live)) continue;
+      if (live) {
+        pos[l] = __double2loint(lst[l]) ^ (bits >> 31);
+        const float qn = sm.qn[pos[l]];
+        float d2 = row.vn + __int_as_float(bits);
+        bool need = !(d2 >= kFGuard * (row.vn + qn));
+        if (kCapStop && a.method == LCEMD_OMR && l == 0) need = true;
+        if (need) d2 = f32_exact_d2<SMALL>(a.V, a.m_pad, a.m4, row.id, sm.cid[pos[l]], row.vn);
+        z[l] = sqrtf(fmaxf(d2, 0.f));
+        w[l] = sm.cap[pos[l]];
+        ++D;
+        Pc += w[l];
+        covered = D >= kef;
+        if (kCapStop) covered = covered || Pc >= row.bound || (a.method == LCEMD_OMR && l == 0 && d2 != 0.f);
       }
     }
-    take16<LK>(lst, k);
+  }
+};
+
+// Table modes: a row's list for the query at words [seg, seg + h) of the
+// item, out.  The two lanes of a row share the stores.
+template <int MODE, int LK, bool SMALL>
+__device__ __forceinline__ void f32_store(const P1Args& a, const F32Smem<MODE, LK, SMALL>& sm, double (&lst)[LK],
+                                          const RowInfo& row, int64_t qi, int seg, int h, int lh) {
+  const Cut<MODE, LK, SMALL> c(a, sm, lst, row, h);
+  if (!row.ok) return;
+  // an ICT row deeper than the list: redone exactly by k_fix_rows while the
+  // redo list has room, else the launch reports overflow
+  if (!c.covered && c.D < h && lh == 0) {
+    if (a.fix_list) {
+      const int slot = atomicAdd(a.fix_count, 1);
+      if (slot < a.fix_cap) a.fix_list[slot] = qi * a.v_used + row.r;
+      else if (a.overflow) a.overflow[0] = 1;
+    } else if (a.overflow) {
+      a.overflow[0] = 1;
+    }
+  }
+  if constexpr (MODE == P1_TABLE) {
+    if (c.D > a.KT && a.overflow) a.overflow[0] = 1;
+#pragma unroll
+    for (int l = 0; l < LK; l += 2) {
+      if (((l >> 1) & 1) == lh && l < c.D && l < a.KT) {
+        constexpr int kOdd = LK > 1 ? 1 : 0;  // (LK = 1: a row has one entry)
+        const bool two = kOdd && l + 1 < c.D && l + 1 < a.KT;
+        *zw_pair(a.ZW, a.zw_nq, a.KT, qi, row.r, l >> 1) =
+            make_float4(c.z[l], l == c.D - 1 ? INFINITY : c.w[l], two ? c.z[l + kOdd] : 0.f,
+                        two ? (l + 1 == c.D - 1 ? INFINITY : c.w[l + kOdd]) : 0.f);
+      }
+    }
+  } else {
+    const int64_t o0 = (qi * a.v_used + row.r) * (int64_t)a.k;
+#pragma unroll
+    for (int l = 0; l < LK; ++l) {
+      if ((l & 1) == lh && l < a.k) {
+        const bool in = l < c.D;
+        a.S[o0 + l] = in ? c.pos[l] - seg : -1;
+        a.Z[o0 + l] = in ? c.z[l] : 0.f;
+        a.W[o0 + l] = in ? c.w[l] : 0.f;
+      }
+    }
   }
 }
 
-// One work item: (query, 128-row block) in the table modes, (candidate pair,
-// 128-row block of the query's words) in pair mode.  Returns early
-// (uniformly) for empty items.
+// The words in LDS (n of them) against the lanes' rows.  Streams: they are
+// those of the queries qs .. qe - 1 of the launch, the first of which starts
+// at word s0 of the batch, and each query's list is stored where its words
+// end, inside the last tile that has some.  Else they are one query's (pair
+// mode: the database row's), and lst is left to the caller.
 template <int MODE, int LK, bool SMALL>
-__device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<SMALL>& sm, int64_t item) {
+__device__ __forceinline__ void f32_words(const P1Args& a, F32Smem<MODE, LK, SMALL>& sm, double (&lst)[LK], const RowInfo& row,
+                                          int n, int64_t qs, int64_t qe, int64_t s0, int tid) {
+  constexpr bool kStream = streams<MODE, SMALL>();
+  const int lh = (tid & 63) >> 5;
+  const bool live = __any(row.ok);  // the wave has rows
+  const size_t rowbytes = (size_t)a.m_pad * 4;
+  const int nsl = SMALL ? 1 : (a.m4 + 7) >> 3;  // 32-dim slices that hold real dims
+  const int last_njq = min(4, a.m4 - 8 * (nsl - 1));
+  const unsigned char* vb = (const unsigned char*)a.V;
+  auto reset = [&]() {
+#pragma unroll
+    for (int i = 0; i < LK; ++i) lst[i] = __hiloint2double((int)kNoKey, 0);
+  };
+  // the query whose words are being taken, and where they begin and end
+  int64_t qi = qs;
+  int b = 0, e = n;
+  auto next = [&]() {  // the next query that has words (fixed-size batches have empty slots)
+    do {
+      b = e;
+      if (++qi >= qe) break;
+      e = (int)(a.qptr[a.q0 + qi + 1] - s0);
+    } while (e == b);
+  };
+  if constexpr (kStream) {
+    qi = qs - 1;
+    e = 0;
+    next();
+  }
+  // the lane's i-th key of the tile of words from j0 on: its word and bits
+  auto at = [&](int j0, int i) { return j0 | (lh << 2) | (8 * (i >> 2) + (i & 3)); };
+  auto keys = [&](const floatx16& acc, int j0, int (&bits)[16]) {
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      const float4 qn = *(const float4*)(sm.qn + j0 + 8 * rq + 4 * lh);
+      const float qv[4] = {qn.x, qn.y, qn.z, qn.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bits[4 * rq + i] = __float_as_int(qv[i] - 2.f * acc[4 * rq + i]);
+    }
+  };
+  auto take = [&](int j0, const int (&bits)[16]) {
+    double k[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) k[i] = __hiloint2double(bits[i], (bits[i] >> 31) ^ at(j0, i));
+    take16<LK>(lst, k);
+  };
+  reset();
+  // passes of at most kNT tiles, as even as they come (a pass of one tile
+  // costs its barriers and latencies like one of four), longer ones first
+  constexpr int kNT = max_tiles<MODE, LK, SMALL>();
+  const int nt = (n + 31) >> 5, npass = (nt + kNT - 1) / kNT, base = nt / npass, extra = nt % npass;
+  Flight fl;
+  fl.rptr = vb + (size_t)row.id * rowbytes + lh * 64;
+  fl.words<kNT>(vb, rowbytes, sm.cid, tid);
+  fl.load<kNT>(0);
+  int c0 = 0;
+#pragma unroll 1
+  for (int p = 0; p < npass; ++p) {
+    const int tiles = base + (p < extra ? 1 : 0);
+    const bool more = p + 1 < npass;
+    floatx16 acc[kNT];
+    auto pass = [&](auto nt_) {
+      f32_pass<decltype(nt_)::value, MODE, LK, SMALL>(sm, fl, acc, c0, more, live, nsl, last_njq, vb, rowbytes, tid);
+    };
+    if (tiles == 1) pass(std::integral_constant<int, 1>());
+    else if (kNT == 2 || tiles == 2) pass(std::integral_constant<int, 2>());
+    else pass(std::integral_constant<int, kNT>());
+    // ---- selection: 16 keys of the lane's row per tile ----
+    if constexpr (!kStream) {
+      if (live) {
+#pragma unroll
+        for (int t = 0; t < kNT; ++t) {
+          if (t >= tiles) break;
+          int bits[16];
+          keys(acc[t], c0 + 32 * t, bits);
+          take(c0 + 32 * t, bits);
+        }
+      }
+    } else if (live) {
+      // per query of the tile; one copy of the code for all tiles (the next
+      // one's sums move to acc[0])
+#pragma unroll 1
+      for (int t = 0; t < tiles; ++t) {
+        const int j0 = c0 + 32 * t, j1 = j0 + 32;
+#pragma unroll 1
+        while (qi < qe) {
+          int bits[16];
+          keys(acc[0], j0, bits);
+          if (b > j0 || e < j1) {  // not the other queries' words
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              if ((unsigned)(at(j0, i) - b) >= (unsigned)(e - b)) bits[i] = (int)kNoKey;
+          }
+          take(j0, bits);
+          if (e > j1) break;
+          f32_store<MODE, LK, SMALL>(a, sm, lst, row, qi, b, e - b, lh);
+          reset();
+          next();
+          if (b >= j1) break;
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < kNT; ++i) acc[i] = acc[i + 1];
+      }
+    }
+    c0 += 32 * tiles;
+  }
+}
+
+// One work item: (up to 2^glog queries, 128-row block) in the table modes,
+// (candidate pair, 128-row block of the query's words) in pair mode.  Returns
+// early (uniformly) for empty items.
+template <int MODE, int LK, bool SMALL>
+__device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<MODE, LK, SMALL>& sm, int64_t item, int lg, int glog) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 31, lh = lane >> 5;
-  constexpr bool kCapStop = MODE != P1_TABLE_FULL;
-
-  int64_t qi = 0, r = 0;  // table modes: query of the launch, table row
-  int64_t pair = 0;       // pair mode: pair and the first of its partial sums here
-  int part = 0, nrows = kFR;
-  int64_t s0;             // the segment
-  int h, rid;
-  float bound;
-  bool row_ok;
+  constexpr int kPad = 32 * max_tiles<MODE, LK, SMALL>();  // (past the words: a pass's)
+  RowInfo row;
+  double lst[LK];
   if constexpr (MODE == P1_PAIR) {
     // partial sums of 128 rows, or 64 (SMALL: two per item)
     const int nblk = SMALL ? (a.rb_max + 1) >> 1 : a.rb_max;
-    pair = item / nblk;
+    const int64_t pair = item / nblk;
     const int blk = (int)(item % nblk);
-    part = SMALL ? 2 * blk : blk;
+    const int part = SMALL ? 2 * blk : blk;  // the first partial sum here
     const int64_t qr = pair / a.cand_use, b = a.qlist ? (int64_t)a.qlist[qr] : qr;
     const int64_t u = (int64_t)(uint32_t)a.cand[qr * a.cand_ld + pair % a.cand_use];
     const int64_t q0 = a.qptr[b] + blk * kFR;
-    nrows = (int)min((int64_t)kFR, a.qptr[b + 1] - q0);
+    const int nrows = (int)min((int64_t)kFR, a.qptr[b + 1] - q0);
     if (nrows <= 0 || u >= a.n) {
       if (tid == 0) a.partial[pair * a.rb_max + part] = 0.f;
       if (SMALL && tid == 0 && part + 1 < a.rb_max) a.partial[pair * a.rb_max + part + 1] = 0.f;
       return;
     }
-    row_ok = 32 * wave + li < nrows;
-    const int64_t i = q0 + (row_ok ? 32 * wave + li : 0);
-    rid = a.qcol[i];
-    bound = row_ok ? a.qval[i] : 0.f;
-    s0 = a.xptr[u];
-    h = (int)(a.xptr[u + 1] - s0);
-    for (int c = tid; c < h + kFC; c += kThreads) {
+    row.ok = 32 * wave + li < nrows;
+    const int64_t i = q0 + (row.ok ? 32 * wave + li : 0);
+    row.id = a.qcol[i];
+    row.bound = row.ok ? a.qval[i] : 0.f;
+    const int64_t s0 = a.xptr[u];
+    const int h = (int)(a.xptr[u + 1] - s0);
+    for (int c = tid; c < h + kPad; c += kThreads) {
       const int w = c < h ? a.xcol[s0 + c] : 0;
       sm.cid[c] = w;
       sm.cap[c] = c < h ? __int_as_float(a.xcv[s0 + c].y) : 0.f;
       sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
     }
-  } else {
-    // items run query-fastest within a group of queries, then row block, then
-    // group: an XCD's contiguous range of items keeps a group's query vectors
-    // and a row block's vectors in its L2
-    const int64_t nrb = (a.v_used + kFR - 1) / kFR;
-    const int lg = f32_group_log2(a.v_used);
-    const int64_t t0 = item >> lg;
-    const int64_t rblk = t0 % nrb;
-    qi = ((t0 / nrb) << lg) + (item & ((int64_t(1) << lg) - 1));
-    if (qi >= a.nq) return;
-    const int64_t r0 = rblk * kFR;
-    s0 = a.qptr[a.q0 + qi];
-    h = (int)(a.qptr[a.q0 + qi + 1] - s0);
-    if (h <= 0) return;  // padding slot of a fixed-size batch
-    r = r0 + 32 * wave + li;  // the lane's row (both halves)
-    row_ok = r < a.v_used;
-    rid = row_ok ? a.used[r] : a.used[r0];
-    bound = MODE == P1_TABLE ? (row_ok ? a.xmax[r] : 0.f) : INFINITY;
-    for (int c = tid; c < h + kFC; c += kThreads) {
-      const int w = c < h ? a.qcol[s0 + c] : 0;
-      sm.cid[c] = w;
-      sm.cap[c] = c < h ? a.qval[s0 + c] : 0.f;
-      sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
-    }
-  }
-  const float rvn = a.vnorm[rid];
-  const bool live = __any(row_ok);  // the wave has rows
-  __syncthreads();
-
-  int kef;
-  if constexpr (MODE == P1_TABLE_FULL) {
-    kef = min(a.k, h);
-  } else {
-    if (a.method == LCEMD_ICT) kef = h;
-    else if (a.method == LCEMD_OMR) kef = min(2, h);
-    else if (a.method == LCEMD_RWMD) kef = 1;
-    else kef = min(a.k, h);
-  }
-
-  // ---------------- contraction ----------------
-  const size_t rowbytes = (size_t)a.m_pad * 4;
-  const int nsl = SMALL ? 1 : (a.m4 + 7) >> 3;  // 32-dim slices that hold real dims
-  const int last_njq = min(4, a.m4 - 8 * (nsl - 1));
-  const unsigned char* vb = (const unsigned char*)a.V;
-  double lst[LK];
-#pragma unroll
-  for (int i = 0; i < LK; ++i) lst[i] = __hiloint2double((int)kNoKey, 0);
-  // passes of at most kNT tiles, as even as they come (a pass of one tile
-  // costs its barriers and latencies like one of four), longer ones first
-  constexpr int kNT = max_tiles<SMALL>();
-  const int nt = (h + 31) >> 5, npass = (nt + kNT - 1) / kNT, base = nt / npass, extra = nt % npass;
-  Flight fl;
-  fl.rptr = vb + (size_t)rid * rowbytes + lh * 64;
-  fl.words<kNT>(vb, rowbytes, sm.cid, tid);
-  fl.load<kNT>(0);
-  int c0 = 0;
-  for (int p = 0; p < npass; ++p) {
-    const int n = base + (p < extra ? 1 : 0);
-    const bool more = p + 1 < npass;
-    auto pass = [&](auto tiles) {
-      f32_pass<decltype(tiles)::value, LK, SMALL>(sm, fl, lst, c0, more, live, nsl, last_njq, vb, rowbytes, tid);
-    };
-    if constexpr (SMALL) {
-      if (n == 1) pass(std::integral_constant<int, 1>());
-      else pass(std::integral_constant<int, 2>());
-    } else {
-      switch (n) {
-        case 1: pass(std::integral_constant<int, 1>()); break;
-        case 2: pass(std::integral_constant<int, 2>()); break;
-        case 3: pass(std::integral_constant<int, 3>()); break;
-        default: pass(std::integral_constant<int, 4>()); break;
-      }
-    }
-    c0 += 32 * n;
-  }
-
-  // ---------------- the row's list: merge of its two lanes ----------------
-  {
-    double other[LK];
-#pragma unroll
-    for (int i = 0; i < LK; ++i)
-      other[i] = __hiloint2double(__shfl_xor(__double2hiint(lst[i]), 32), __shfl_xor(__double2loint(lst[i]), 32));
-    net_merge<LK, LK>(lst, other);
-  }
-
-  // ---------------- distances, cut, outputs ----------------
-  // both lanes of a row do the same arithmetic and share the stores
-  float z[LK], w[LK];
-  int pos[LK];
-  int D = 0;
-  bool covered = false;
-  float Pc = 0.f;
-#pragma unroll
-  for (int l = 0; l < LK; ++l) {
-    z[l] = 0.f;
-    w[l] = 0.f;
-    pos[l] = 0;
-    const int bits = __double2hiint(lst[l]);
-    const bool live = row_ok && !covered && bits != (int)kNoKey;
-    if (!__any(live)) continue;
-    if (live) {
-      pos[l] = __double2loint(lst[l]) ^ (bits >> 31);
-      const float qn = sm.qn[pos[l]];
-      float d2 = rvn + __int_as_float(bits);
-      bool need = !(d2 >= kFGuard * (rvn + qn));
-      if (kCapStop && a.method == LCEMD_OMR && l == 0) need = true;
-      if (need) d2 = f32_exact_d2<SMALL>(a.V, a.m_pad, a.m4, rid, sm.cid[pos[l]]);
-      z[l] = sqrtf(fmaxf(d2, 0.f));
-      w[l] = sm.cap[pos[l]];
-      ++D;
-      Pc += w[l];
-      covered = D >= kef;
-      if (kCapStop) covered = covered || Pc >= bound || (a.method == LCEMD_OMR && l == 0 && d2 != 0.f);
-    }
-  }
-  if constexpr (MODE == P1_PAIR) {
+    row.vn = a.vnorm[row.id];
+    __syncthreads();
+    f32_words<MODE, LK, SMALL>(a, sm, lst, row, h, 0, 1, 0, tid);
+    const Cut<MODE, LK, SMALL> c(a, sm, lst, row, h);
     // the transfers of the row's mass (the last entry takes the rest), then
     // the rows' sum in order
-    if (!covered && D < h && row_ok && a.overflow) a.overflow[0] = 1;  // a list too short
+    if (!c.covered && c.D < h && row.ok && a.overflow) a.overflow[0] = 1;  // a list too short
     if (lh == 0) {
-      float rem = bound, cost = 0.f;
+      float rem = row.bound, cost = 0.f;
 #pragma unroll
       for (int l = 0; l < LK; ++l) {
-        if (l < D) {
-          const float t = l == D - 1 ? rem : fminf(rem, w[l]);
+        if (l < c.D) {
+          const float t = l == c.D - 1 ? rem : fminf(rem, c.w[l]);
           rem -= t;
-          cost = fmaf(t, z[l], cost);
+          cost = fmaf(t, c.z[l], cost);
         }
       }
       sm.rcost[32 * wave + li] = cost;
@@ -473,42 +575,41 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<SMALL>& sm, in
       for (int i = tid; i < min(tid + kPart, nrows); ++i) tot += sm.rcost[i];
       a.partial[pair * a.rb_max + part + tid / kPart] = tot;
     }
-    return;
-  }
-  if (!row_ok) return;  // (no barrier past this point)
-  // an ICT row deeper than the list: redone exactly by k_fix_rows while the
-  // redo list has room, else the launch reports overflow
-  if (!covered && D < h && lh == 0) {
-    if (a.fix_list) {
-      const int slot = atomicAdd(a.fix_count, 1);
-      if (slot < a.fix_cap) a.fix_list[slot] = qi * a.v_used + r;
-      else if (a.overflow) a.overflow[0] = 1;
-    } else if (a.overflow) {
-      a.overflow[0] = 1;
-    }
-  }
-  if constexpr (MODE == P1_TABLE) {
-    if (D > a.KT && a.overflow) a.overflow[0] = 1;
-#pragma unroll
-    for (int l = 0; l < LK; l += 2) {
-      if (((l >> 1) & 1) == lh && l < D && l < a.KT) {
-        constexpr int kOdd = LK > 1 ? 1 : 0;  // (LK = 1: a row has one entry)
-        const bool two = kOdd && l + 1 < D && l + 1 < a.KT;
-        *zw_pair(a.ZW, a.zw_nq, a.KT, qi, r, l >> 1) =
-            make_float4(z[l], l == D - 1 ? INFINITY : w[l], two ? z[l + kOdd] : 0.f,
-                        two ? (l + 1 == D - 1 ? INFINITY : w[l + kOdd]) : 0.f);
+  } else {
+    // items run query-fastest within a group of queries, then row block, then
+    // group: an XCD's contiguous range of items keeps a group's query vectors
+    // and a row block's vectors in its L2
+    const int64_t nrb = (a.v_used + kFR - 1) / kFR;
+    const int64_t t0 = item >> (lg - glog);
+    const int64_t rblk = t0 % nrb;
+    int64_t qs = ((t0 / nrb) << lg) + ((item & ((int64_t(1) << (lg - glog)) - 1)) << glog);
+    const int64_t qend = min(qs + (int64_t(1) << glog), a.nq);
+    const int64_t r0 = rblk * kFR;
+    row.r = r0 + 32 * wave + li;  // the lane's row (both halves)
+    row.ok = row.r < a.v_used;
+    row.id = row.ok ? a.used[row.r] : a.used[r0];
+    row.bound = MODE == P1_TABLE ? (row.ok ? a.xmax[row.r] : 0.f) : INFINITY;
+    row.vn = a.vnorm[row.id];
+#pragma unroll 1
+    while (qs < qend) {
+      // as many of the queries as LDS holds
+      const int64_t s0 = a.qptr[a.q0 + qs];
+      int64_t qe = qs + 1;
+      while (streams<MODE, SMALL>() && qe < qend && a.qptr[a.q0 + qe + 1] - s0 <= kFCat) ++qe;
+      const int n = (int)(a.qptr[a.q0 + qe] - s0);
+      if (n > 0) {
+        __syncthreads();  // the words before are done with
+        for (int c = tid; c < n + kPad; c += kThreads) {
+          const int w = c < n ? a.qcol[s0 + c] : 0;
+          sm.cid[c] = w;
+          sm.cap[c] = c < n ? a.qval[s0 + c] : 0.f;
+          sm.qn[c] = c < n ? a.vnorm[w] : INFINITY;
+        }
+        __syncthreads();
+        f32_words<MODE, LK, SMALL>(a, sm, lst, row, n, qs, qe, s0, tid);
+        if constexpr (!streams<MODE, SMALL>()) f32_store<MODE, LK, SMALL>(a, sm, lst, row, qs, 0, n, lh);
       }
-    }
-  } else if constexpr (MODE == P1_TABLE_FULL) {
-    const int64_t o0 = (qi * a.v_used + r) * (int64_t)a.k;
-#pragma unroll
-    for (int l = 0; l < LK; ++l) {
-      if ((l & 1) == lh && l < a.k) {
-        const bool in = l < D;
-        a.S[o0 + l] = in ? pos[l] : -1;
-        a.Z[o0 + l] = in ? z[l] : 0.f;
-        a.W[o0 + l] = in ? w[l] : 0.f;
-      }
+      qs = qe;
     }
   }
 }
@@ -518,8 +619,9 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<SMALL>& sm, in
 // contiguous eighth of the items; the counter is read one item ahead.  Every
 // workgroup exits once its counter passes the end of its range.
 template <int MODE, int LK, bool SMALL>
-__global__ __launch_bounds__(kThreads, (groups_per_cu<LK, SMALL>())) void k_phase1_rows(P1Args a, int64_t total) {
-  __shared__ F32Smem<SMALL> sm;
+__global__ __launch_bounds__(kThreads, (groups_per_cu<MODE, LK, SMALL>())) void k_phase1_rows(P1Args a, int64_t total,
+                                                                                      int lg, int glog) {
+  __shared__ F32Smem<MODE, LK, SMALL> sm;
   __shared__ int64_t s_item;
   const int xcd = blockIdx.x & 7;
   const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
@@ -534,27 +636,36 @@ __global__ __launch_bounds__(kThreads, (groups_per_cu<LK, SMALL>())) void k_phas
     __syncthreads();
     const int64_t item = s_item;
     if (item >= hi) break;
-    f32_task<MODE, LK, SMALL>(a, sm, item);
+    f32_task<MODE, LK, SMALL>(a, sm, item, lg, glog);
   }
 }
 
 template <int MODE, int LK, bool SMALL>
 hipError_t launch_f32_one(const P1Args& a, hipStream_t s) {
   int64_t total;
+  int lg = f32_group_log2(a.v_used), glog = 0;
+  const void* fn = (const void*)k_phase1_rows<MODE, LK, SMALL>;
+  const int resident = persistent_grid(fn, kThreads, 0, int64_t(1) << 40);
+  if (resident <= 0) return hipErrorInvalidConfiguration;
   if (MODE == P1_PAIR) {
     total = a.npairs * (SMALL ? (a.rb_max + 1) / 2 : a.rb_max);
   } else {
     const int64_t nrb = (a.v_used + kFR - 1) / kFR;
-    const int64_t gw = int64_t(1) << f32_group_log2(a.v_used);
-    total = (a.nq + gw - 1) / gw * nrb * gw;
+    while (lg > 0 && (int64_t(1) << (lg - 1)) >= a.nq) --lg;  // (no empty items in a small batch)
+    // several queries per item as long as every resident workgroup still
+    // gets three items (16 queries of a 70,000-word vocabulary, 2160 items of
+    // two: 1.24 ms a call; items of one 1.30, of eight 1.45)
+    auto items = [&](int g) { return ((a.nq + (int64_t(1) << lg) - 1) >> lg) * nrb << (lg - g); };
+    if (streams<MODE, SMALL>())
+      while (glog < kStreamLog2 && glog < lg && items(glog + 1) >= 3 * resident) ++glog;
+    total = items(glog);
   }
   if (total <= 0) return hipSuccess;
   if (!a.work_ctr) return hipErrorInvalidValue;
   hipError_t e = launch_zero_ints((int*)a.work_ctr, 16, s);
   if (e != hipSuccess) return e;
-  const int grid = persistent_grid((const void*)k_phase1_rows<MODE, LK, SMALL>, kThreads, 0, total);
-  if (grid <= 0) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_phase1_rows<MODE, LK, SMALL>), dim3(grid), dim3(kThreads), 0, s, a, total);
+  const int grid = persistent_grid(fn, kThreads, 0, total);
+  hipLaunchKernelGGL((k_phase1_rows<MODE, LK, SMALL>), dim3(grid), dim3(kThreads), 0, s, a, total, lg, glog);
   return hipGetLastError();
 }
 

@@ -75,7 +75,8 @@ __device__ __forceinline__ uint32_t wk_pos(uint32_t k) { return k & kWPos; }
 
 // Squared distance by direct differences over the m4 float4 groups that
 // hold the real dims (the zero padding would add exact zeros).
-__device__ __forceinline__ float w_exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b) {
+__device__ __forceinline__ float w_exact_d2(const float* __restrict__ V, int m_pad, int m4, int a, int b, float an) {
+  if (a == b && an < INFINITY) return 0.f;  // (an = |a|^2: a row of finite numbers against itself)
   const float4* x = (const float4*)(V + (size_t)a * m_pad);
   const float4* y = (const float4*)(V + (size_t)b * m_pad);
   float s = 0.f;
@@ -461,7 +462,8 @@ __device__ __forceinline__ void wide_task(const P1Args& a, unsigned char* smem_r
       if (row_ok && sub + 2 * e < len) {
         const float qn = sm.qn[ps[e]];
         float d2 = (sm.rvn[row] + qn) - 2.f * ex[e];
-        if (!(d2 >= kGuardW * (sm.rvn[row] + qn))) d2 = w_exact_d2(a.V, a.m_pad, a.m4, sm.rid[row], sm.cid[ps[e]]);
+        if (!(d2 >= kGuardW * (sm.rvn[row] + qn)))
+          d2 = w_exact_d2(a.V, a.m_pad, a.m4, sm.rid[row], sm.cid[ps[e]], sm.rvn[row]);
         ex[e] = d2;
       }
     }

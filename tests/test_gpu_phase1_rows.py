@@ -107,3 +107,33 @@ def test_candidate_pairs(L, method, k, m):
     off = sum(P.check_topl(idx[b], dist[b], want[b], 5, f"{method} query {b}") for b in range(q.n))
     assert off <= 2
     ctx.close()
+
+
+@pytest.mark.parametrize("k", [1, 2, 8, 16])
+def test_queries_that_share_an_item(L, k):
+    """Batches large enough that an item takes eight queries end to end give
+    what each query alone gives (one query per item), bit for bit: queries
+    that end inside, at and past a tile's edge, several within one tile, and
+    more words than an item holds at a time."""
+    rng = np.random.default_rng(46)
+    v, nu, m, nq = 17000, 16500, 40, 150
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    words = np.arange(nu, dtype=np.int32)
+    ptr = np.arange(0, nu + 1, 500, dtype=np.int64)
+    ctx = L.open_context(V, ptr, words, np.full(nu, 1.0 / 500, np.float32))
+    lengths = rng.integers(1, 70, nq)
+    lengths[:24] = [1, 1, 1, 29, 32, 64, 31, 33, 1024, 1024, 1, 1023, 1024, 2, 500, 700, 32, 32, 32, 32, 5, 6, 7, 8]
+    q = _queries(rng, v, lengths.tolist())
+    print(f"[gpu] shared items k={k}", flush=True)
+    S, Z, W = ctx.tables(q.rowptr, q.col, q.val, k)
+    for b in list(range(24)) + [70, 147, 148, 149]:
+        qc, qw = q.row(b)
+        s1, z1, w1 = ctx.tables(np.array([0, qc.size], dtype=np.int64), qc, qw, k)
+        assert np.array_equal(S[b], s1[0]) and np.array_equal(Z[b], z1[0]) and np.array_equal(W[b], w1[0]), b
+    for method in ("rwmd", "omr", "act"):
+        g = ctx.distances(q.rowptr, q.col, q.val, method=method, k=k, direction="d2q")
+        for b in (0, 8, 9, 15, 149):
+            qc, qw = q.row(b)
+            one = ctx.distances(np.array([0, qc.size], dtype=np.int64), qc, qw, method=method, k=k, direction="d2q")
+            assert np.allclose(g[b], one[0], rtol=1e-6, atol=1e-7), (method, b)
+    ctx.close()
