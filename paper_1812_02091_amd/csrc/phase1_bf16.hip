@@ -42,22 +42,23 @@
 // re-sorted by (distance, position) and cut as Alg. 3 / the capacity bound
 // say.
 //
-// Bound: the recompute, about three fifths of an item's time, whose LDS reads
-// (a dot product reads the whole float32 word, 1.2 KB at 300 dims, from rows
-// that no order makes conflict-free: about twice the conflict-free time) take
-// half of a CU's cycles; the rest is the phases of a workgroup waiting on
-// each other through barriers.
+// Bound: the recompute, half of an item's time: its LDS reads (a dot product
+// reads the whole float32 word, 1.2 KB at 300 dims, from rows that no order
+// makes conflict-free) and its FMAs take about half of a CU's cycles each.
+// Reading a second list entry's words during the first one's sums took the
+// same time, with the registers for it (128 let two workgroups share a CU).
 //
 // Measured on ACT k = 8 tables of 300-dim words, CU cycles per query x 256
 // rows.  The form before this one (rows and words both staged in LDS, keys
 // inserted into LDS lists one at a time, queue merges): 76 k at 32 words,
-// 88 k at 64, 110 k at 128; this one: 63 k, 68 k, 89 k (192 queries of about
-// 118 words over 485 k rows: 69 ms, now 55 ms).  Workgroups of four waves and
-// passes of up to 128 words, three to a CU: 64 k, 72 k, 95 k, and 0.30 ms
-// instead of 0.22 ms for one query (an item of half the rows stages the same
-// words).  The row's dims all in registers and a tile of 32 words at a time:
-// 68 ms; the words of the next list entry read ahead of the sums: 99 k against
-// 75 k cycles for that phase (registers spill).
+// 88 k at 64, 110 k at 128; this one: 47 k, 51 k, 68 k (192 queries of about
+// 118 words over 485 k rows: 69 ms, now 44 ms).  Workgroups of four waves and
+// passes of up to 128 words, three to a CU, were slower (57 ms against 55 at
+// the time, and an item of half the rows stages the same words); the row's
+// dims all in registers and a tile of 32 words at a time: 68 ms.
+// What is computed from the thread's index is kept from being hoisted out of
+// the item and stage loops (fresh): 46 registers spilled, and a reload waits
+// for every load in flight before it, the next stage's words (55 -> 44 ms).
 #include <algorithm>
 
 #include "internal.h"
@@ -136,6 +137,13 @@ __device__ __forceinline__ BfLds bf_lds(unsigned char* base, int hmax, int LK) {
   s.cap = (float*)(p + hp);
   s.qn = (float*)(p + 2 * hp);
   return s;
+}
+
+// x, as a value of its own: what is computed from it is computed where it
+// stands, instead of ahead of a loop and spilled there
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 __device__ __forceinline__ float pk_key(uint32_t k) { return __uint_as_float(k & ~kPosMask); }
@@ -310,8 +318,7 @@ __device__ __forceinline__ void bf16_pass(const BfLds& sm, BfFlight& fl, uint32_
 // every RD dims lane sub takes [sub RD / 2, (sub + 1) RD / 2), in order,
 // staged W dims (W / 2 of each half) at a time.  off[e]: the word's staged
 // row in floats.  The row's dims are loaded a stage ahead, the words' while
-// the stage before them is worked on (up to 4 pieces a thread; the rest of a
-// long query's at the stage).
+// the stage before them is worked on (up to 4 pieces a thread).
 template <int W, int LK>
 __device__ __forceinline__ void recompute(const P1Args& a, const BfLds& sm, int h, int dims, int RD, int rid, int sub,
                                           int wlen, const int (&off)[LK], float (&dot)[LK]) {
@@ -325,31 +332,33 @@ __device__ __forceinline__ void recompute(const P1Args& a, const BfLds& sm, int 
   const int nst = (dims + RD - 1) / RD * per;
   // a stage's first dim of either half
   auto dim0 = [&](int i, int half) { return i / per * RD + half * (RD / 2) + i % per * (W / 2); };
-  auto fetch1 = [&](int i, int f) {
-    const int c = f / N4, q4 = f % N4;
-    const int d = dim0(i, q4 / Q) + 4 * (q4 % Q);
-    return f < pieces && d < a.m_pad ? *(const float4*)(a.V + (size_t)sm.cid[c] * a.m_pad + d)
-                                     : make_float4(0.f, 0.f, 0.f, 0.f);
-  };
   auto put1 = [&](int f, const float4& x) {
     if (f < pieces) *(float4*)(&sm.qf[f / N4 * WS + f % N4 * 4]) = x;
   };
   float4 nx[kAhead], vn[Q];
   const float* vrow = a.V + (size_t)rid * a.m_pad;
+  // (stages end within m_pad, a multiple of 64; the rows are 0 past their dims)
   auto fetch = [&](int i) {
+    const int t = fresh(tid);
+    const int d = dim0(i, t % N4 / Q) + 4 * (t % Q);
+    int id[kAhead];
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) nx[k] = fetch1(i, tid + k * kBT);
-    const int d = dim0(i, sub);
+    for (int k = 0; k < kAhead; ++k) id[k] = sm.cid[min(t + k * kBT, pieces - 1) / N4];
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
-      vn[q] = d + 4 * q < a.m_pad ? *(const float4*)(vrow + d + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = 0; k < kAhead; ++k)
+      nx[k] = t + k * kBT < pieces ? *(const float4*)(a.V + (size_t)id[k] * a.m_pad + d)
+                                   : make_float4(0.f, 0.f, 0.f, 0.f);
+    const int dr = dim0(i, sub);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) vn[q] = *(const float4*)(vrow + dr + 4 * q);
   };
   fetch(0);
 #pragma unroll 1
   for (int i = 0; i < nst; ++i) {
     __syncthreads();  // the previous stage (at first: the lists) is consumed
+    const int t = fresh(tid);
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) put1(tid + k * kBT, nx[k]);
+    for (int k = 0; k < kAhead; ++k) put1(t + k * kBT, nx[k]);
     float4 vc[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) vc[q] = vn[q];
@@ -379,7 +388,7 @@ __device__ __forceinline__ void recompute(const P1Args& a, const BfLds& sm, int 
 template <int MODE, int LK>
 __device__ __forceinline__ void bf16_task(const P1Args& a, const BfLds& sm, int64_t item) {
   static_assert(LK == 16 || LK == 32, "list sizes 16 or 32");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = fresh(threadIdx.x), lane = tid & 63, wave = tid >> 6;
   const int li = lane & 31, lh = lane >> 5;
   constexpr bool kCapStop = MODE != P1_TABLE_FULL;
 
