@@ -13,6 +13,7 @@
 // best SYM key, since every other row's SYM key is at least its D2Q key.
 // Rows for which that certificate fails are flagged for a wider pass.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -61,6 +62,9 @@ __device__ void bitonic_sort(uint64_t* buf, int N) {
 // when the next round could overflow it.  Keys are unique (row index in the
 // low bits), so the result is the exact L smallest in (distance, index)
 // order.
+// Bound: the rounds' chain of load, append and barriers; a round's keys are
+// loaded during the round before (one query over 18,000 rows 37 -> 24 us,
+// 3,000 over 60,000, with the symmetric sort below, 0.54 -> 0.27 ms).
 constexpr int kSelBuf = 4096;
 constexpr int kSelPer = 8;                      // keys per thread per round
 constexpr int kSelRound = kSelPer * kThreads;   // 2048
@@ -104,21 +108,35 @@ __global__ __launch_bounds__(kThreads) void k_select(const void* __restrict__ ke
     thr = ~0ull;
   }
   __syncthreads();
+  using Raw = typename std::conditional<PACKED, uint64_t, float>::type;
+  Raw nx[kSelPer];  // the next round's
+  auto load = [&](int64_t base) {
+#pragma unroll
+    for (int e = 0; e < kSelPer; ++e) {
+      const int64_t u = base + e * kThreads + threadIdx.x;
+      if (u < hi) {
+        if constexpr (PACKED) nx[e] = kp[u];
+        else nx[e] = kf[u];
+      }
+    }
+  };
+  load(lo);
   for (int64_t base = lo; base < hi; base += kSelRound) {
-    const int c = cnt;
-    __syncthreads();  // every thread has read cnt before any append below
-    if (c > kSelBuf - kSelRound) sel_compact(buf, &cnt, &thr, L);
-    const uint64_t t = thr;
     uint64_t kk[kSelPer];
 #pragma unroll
     for (int e = 0; e < kSelPer; ++e) {
       const int64_t u = base + e * kThreads + threadIdx.x;
       kk[e] = ~0ull;
       if (u < hi) {
-        if constexpr (PACKED) kk[e] = kp[u];
-        else if (u != excl) kk[e] = pack_s(kf[u], (uint32_t)u);
+        if constexpr (PACKED) kk[e] = nx[e];
+        else if (u != excl) kk[e] = pack_s(nx[e], (uint32_t)u);
       }
     }
+    load(base + kSelRound);
+    const int c = cnt;
+    __syncthreads();  // every thread has read cnt before any append below
+    if (c > kSelBuf - kSelRound) sel_compact(buf, &cnt, &thr, L);
+    const uint64_t t = thr;
     uint64_t t_use = t;
     if (base == lo && L <= kThreads) {
       // first round: threshold = the L-th smallest per-thread minimum, + 1
@@ -179,7 +197,9 @@ __global__ __launch_bounds__(kThreads) void k_finalize_sym(
   const int64_t ri = blockIdx.x;
   const int64_t b = row_list ? (int64_t)row_list[ri] : ri;
   const uint64_t* cr = cand + ri * cand_ld;
-  for (int i = threadIdx.x; i < kSelectBuf; i += kThreads) {
+  int N = 2;  // (the sort's time goes with its keys: 35 us for 2048, 4 for 32)
+  while (N < cand_use) N <<= 1;
+  for (int i = threadIdx.x; i < N; i += kThreads) {
     uint64_t kk = ~0ull;
     if (i < cand_use) {
       const uint64_t c = cr[i];
@@ -191,7 +211,7 @@ __global__ __launch_bounds__(kThreads) void k_finalize_sym(
     buf[i] = kk;
   }
   __syncthreads();
-  bitonic_sort(buf, kSelectBuf);
+  bitonic_sort(buf, N);
   for (int i = threadIdx.x; i < L; i += kThreads) {
     const uint64_t kk = buf[i];
     idx[b * L + i] = kk == ~0ull ? -1 : (int64_t)(uint32_t)kk;
