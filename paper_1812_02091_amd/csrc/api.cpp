@@ -575,41 +575,77 @@ int d2q_checked(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts*
 // that overflowed is run again, checked, one step deeper.  Phase 2 of an
 // overflowed tile reads incomplete tables, but its loops are bounded by the
 // list depth and the database records, and the rerun rewrites its rows.
-int run_d2q(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts* o, float* out, int64_t ld) {
+//
+// d2q_queue leaves the reading of the flags to the caller, who may queue work
+// on the distances first and read them with its own results: `nflags` ints of
+// the caller's, then (at tile_flags) one per tile.  ICT leaves no tiles.
+struct D2qRun {
+  int* flags = nullptr;
+  int64_t nflags = 0;
+  std::vector<std::pair<int64_t, int64_t>> tiles;
+  TileDepth d0{};
+  int* tile_flags() const { return flags + nflags; }
+};
+int d2q_queue(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts* o, float* out, int64_t ld,
+              int64_t nflags, D2qRun& run) {
   // ICT: the tables hold up to KT entries per row, but the lists of phase 1
   // stop at kIctList (a row needs a few entries before its capacities cover
   // the word's largest weight, Lemma 1); deeper rows are redone exactly
   const TileDepth d0{o->precision, table_depth(o, Q.hmax), o->method != LCEMD_ICT};
+  run.d0 = d0;
+  run.nflags = nflags;
   if (Q.B < 1) return LCEMD_OK;
-  int* ovf;
   int rc;
+  if ((rc = wsget(c, "ovf_tiles", (size_t)(nflags + Q.B), run.flags))) return rc;
   if (o->method == LCEMD_ICT) {
+    int* ovf;
     if ((rc = wsget(c, "ovf", 1, ovf))) return rc;
     return d2q_checked(c, db, Q, o, 0, Q.B, d0, ovf, out, ld);
   }
-  if ((rc = wsget(c, "ovf_tiles", (size_t)Q.B, ovf))) return rc;
-  HIPCHK(c, launch_zero_ints(ovf, (int)Q.B, c->stream));
-  std::vector<std::pair<int64_t, int64_t>> tiles;
+  HIPCHK(c, launch_zero_ints(run.tile_flags(), (int)Q.B, c->stream));
   for (int64_t q0 = 0; q0 < Q.B;) {
     const int64_t nq = std::min<int64_t>(d2q_tile_queries(c, db, d0.KT), Q.B - q0);
     float2* ZW;
-    if ((rc = d2q_tables(c, db, Q, o, q0, nq, d0.prec, d0.full, d0.KT, ovf + tiles.size(), &ZW))) return rc;
+    if ((rc = d2q_tables(c, db, Q, o, q0, nq, d0.prec, d0.full, d0.KT, run.tile_flags() + run.tiles.size(), &ZW)))
+      return rc;
     if ((rc = d2q_phase2(c, db, q0, nq, d0.KT, ZW, out, ld))) return rc;
-    tiles.emplace_back(q0, nq);
+    run.tiles.emplace_back(q0, nq);
     q0 += nq;
   }
-  std::vector<int> hf(tiles.size());
-  HIPCHK(c, hipMemcpyAsync(hf.data(), ovf, sizeof(int) * hf.size(), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  for (size_t t = 0; t < tiles.size(); ++t) {
+  return LCEMD_OK;
+}
+
+// Runs the tiles whose flag (hf, in host memory) is set again.
+int d2q_settle(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts* o, float* out, int64_t ld,
+               const D2qRun& run, const int* hf, bool* changed = nullptr) {
+  int rc;
+  for (size_t t = 0; t < run.tiles.size(); ++t) {
     if (!hf[t]) continue;
-    TileDepth d = d0;
+    if (changed) *changed = true;
+    const auto& tile = run.tiles[t];
+    TileDepth d = run.d0;
     if (!d.deeper(c, Q.hmax))
       return fail(c, LCEMD_E_CAPACITY, "a table row of queries [%lld, %lld) is deeper than its lists at full depth",
-                  (long long)tiles[t].first, (long long)(tiles[t].first + tiles[t].second));
-    if ((rc = d2q_checked(c, db, Q, o, tiles[t].first, tiles[t].first + tiles[t].second, d, ovf, out, ld))) return rc;
+                  (long long)tile.first, (long long)(tile.first + tile.second));
+    if ((rc = d2q_checked(c, db, Q, o, tile.first, tile.first + tile.second, d, run.tile_flags(), out, ld))) return rc;
   }
   return LCEMD_OK;
+}
+
+// ... the flags read first.
+int d2q_finish(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts* o, float* out, int64_t ld,
+               const D2qRun& run, bool* changed = nullptr) {
+  if (run.tiles.empty()) return LCEMD_OK;
+  std::vector<int> hf(run.tiles.size());
+  HIPCHK(c, hipMemcpyAsync(hf.data(), run.tile_flags(), sizeof(int) * hf.size(), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  return d2q_settle(c, db, Q, o, out, ld, run, hf.data(), changed);
+}
+
+int run_d2q(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts* o, float* out, int64_t ld) {
+  D2qRun run;
+  const int rc = d2q_queue(c, db, Q, o, out, ld, 0, run);
+  return rc ? rc : d2q_finish(c, db, Q, o, out, ld, run);
 }
 
 int run_d2q(lcemd_ctx* c, const QDev& Q, const lcemd_opts* o, float* out, int64_t ld) {
@@ -643,14 +679,13 @@ int run_pairs(lcemd_ctx* c, const QDev& Q, const lcemd_opts* o, P1Args a, float*
   if ((rc = prof_begin(c, "phase1_pair_q2d", (double)a.npairs))) return rc;
   if ((rc = p1_launch(c, a, P1_PAIR, o->precision, depth, c->db_hmax, Q.hmax))) return rc;
   if ((rc = prof_end(c))) return rc;
-  if ((o->method == LCEMD_ICT && depth < c->db_hmax) || o->precision != LCEMD_FP32) {
+  if (o->method == LCEMD_ICT && depth < c->db_hmax) {  // (other lists are as long as they need to be)
     int h_ovf = 0;
     HIPCHK(c, hipMemcpyAsync(&h_ovf, ovf, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (h_ovf) {
       ++c->fallbacks;
-      const int d2 = o->method == LCEMD_ICT ? c->db_hmax : depth;
-      if ((rc = p1_launch(c, a, P1_PAIR, LCEMD_FP32, d2, c->db_hmax, Q.hmax))) return rc;
+      if ((rc = p1_launch(c, a, P1_PAIR, LCEMD_FP32, c->db_hmax, c->db_hmax, Q.hmax))) return rc;
     }
   }
   HIPCHK(c, launch_pair_reduce(partial, a.npairs, a.rb_max, out, out_ld, per_row, c->stream));
@@ -1098,18 +1133,28 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
   const int64_t excl = o->exclude_self >= 0 ? o->exclude_self : -1;
   float* d2q;
   if ((rc = wsget(c, "d2q_full", (size_t)B * n, d2q))) return rc;
+  const DbView db = db_view(c);
+  D2qRun run;
   if (o->direction == LCEMD_Q2D) {
     if ((rc = run_q2d_lc(c, Q, o, d2q, n))) return rc;
   } else {
-    if ((rc = run_d2q(c, Q, o, d2q, n))) return rc;
+    // (its overflow flags are read with the first results: the selection is
+    // queued behind it, and runs again if a tile has to)
+    if ((rc = d2q_queue(c, db, Q, o, d2q, n, o->direction == LCEMD_SYM ? B : 0, run))) return rc;
   }
   if (o->direction != LCEMD_SYM) {
     uint64_t* cand;
     if ((rc = wsget(c, "cand", (size_t)B * l, cand))) return rc;
-    if ((rc = prof_begin(c, "select", (double)B * n))) return rc;
-    if ((rc = select_rows(c, d2q, n, n, B, l, nullptr, excl, cand))) return rc;
-    if ((rc = prof_end(c))) return rc;
-    HIPCHK(c, launch_unpack_topl(cand, l, B, nullptr, l, didx, ddist, c->stream));
+    bool again = false;
+    do {
+      if ((rc = prof_begin(c, "select", (double)B * n))) return rc;
+      if ((rc = select_rows(c, d2q, n, n, B, l, nullptr, excl, cand))) return rc;
+      if ((rc = prof_end(c))) return rc;
+      HIPCHK(c, launch_unpack_topl(cand, l, B, nullptr, l, didx, ddist, c->stream));
+      again = false;
+      if ((rc = d2q_finish(c, db, Q, o, d2q, n, run, &again))) return rc;
+      run.tiles.clear();
+    } while (again);
   } else {
     // exact symmetric top-l by lower-bound pruning (SYM >= D2Q)
     std::vector<int32_t> rows(B);
@@ -1120,8 +1165,8 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
     int64_t Lp = c->sym_candidates > 0 ? std::max<int64_t>(c->sym_candidates, l)
                                        : (int64_t)l + std::max<int64_t>(8, l / 2);
     int32_t* drows;
-    int* dflags;
-    if ((rc = wsget(c, "sym_rows", (size_t)B, drows)) || (rc = wsget(c, "sym_flags", (size_t)B, dflags))) return rc;
+    int* dflags = run.flags;
+    if ((rc = wsget(c, "sym_rows", (size_t)B, drows))) return rc;
     std::vector<int> hflags;
     bool first = true;
     while (!rows.empty()) {
@@ -1135,6 +1180,7 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
         // measures whose two directions differ widely, such as RWMD): the
         // whole Q2D matrix by the swapped-role linear method, SYM = max, and
         // the remaining rows selected from it
+        if ((rc = d2q_finish(c, db, Q, o, d2q, n, run))) return rc;
         float* q2 = nullptr;
         if ((rc = wsget(c, "q2d_full", (size_t)B * n, q2))) return rc;
         if ((rc = run_q2d_lc(c, Q, o, q2, n))) return rc;
@@ -1146,24 +1192,33 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
         HIPCHK(c, launch_unpack_topl(cand, l, R, drows, l, didx, ddist, c->stream));
         break;
       }
-      HIPCHK(c, hipMemcpyAsync(drows, rows.data(), sizeof(int32_t) * R, hipMemcpyHostToDevice, c->stream));
+      // (the first pass takes every row: no list)
+      const int32_t* list = R < B ? drows : nullptr;
+      if (list)
+        HIPCHK(c, hipMemcpyAsync(drows, rows.data(), sizeof(int32_t) * R, hipMemcpyHostToDevice, c->stream));
       uint64_t* cand;
       float* q2v;
       if ((rc = wsget(c, "cand", (size_t)R * cld, cand)) || (rc = wsget(c, "cand_q2d", (size_t)R * use, q2v))) return rc;
       if ((rc = prof_begin(c, "select", (double)R * n))) return rc;
-      if ((rc = select_rows(c, d2q, n, n, R, (int)cld, drows, excl, cand))) return rc;
+      if ((rc = select_rows(c, d2q, n, n, R, (int)cld, list, excl, cand))) return rc;
       if ((rc = prof_end(c))) return rc;
       P1Args a = base_args(c, Q, o);
       a.cand = cand;
       a.cand_ld = cld;
       a.cand_use = use;
-      a.qlist = drows;
+      a.qlist = list;
       a.npairs = R * use;
       if ((rc = run_pairs(c, Q, o, a, q2v, use, use))) return rc;
-      HIPCHK(c, launch_finalize_sym(cand, cld, use, q2v, R, drows, n, l, didx, ddist, dflags, c->stream));
-      hflags.resize(R);
-      HIPCHK(c, hipMemcpyAsync(hflags.data(), dflags, sizeof(int) * R, hipMemcpyDeviceToHost, c->stream));
+      HIPCHK(c, launch_finalize_sym(cand, cld, use, q2v, R, list, n, l, didx, ddist, dflags, c->stream));
+      // (tiles are left to check only in the first pass, where R = B: their
+      // flags follow the queries')
+      hflags.resize((size_t)R + run.tiles.size());
+      HIPCHK(c, hipMemcpyAsync(hflags.data(), dflags, sizeof(int) * hflags.size(), hipMemcpyDeviceToHost, c->stream));
       HIPCHK(c, hipStreamSynchronize(c->stream));
+      bool changed = false;
+      if ((rc = d2q_settle(c, db, Q, o, d2q, n, run, hflags.data() + R, &changed))) return rc;
+      run.tiles.clear();
+      if (changed) continue;  // the same pass on the right distances
       std::vector<int32_t> again;
       for (int64_t i = 0; i < R; ++i)
         if (hflags[i]) again.push_back(rows[i]);
