@@ -62,26 +62,27 @@ def parse():
     return ap.parse_args()
 
 
+def pow2_at_least(x):
+    return 1 << max(0, x - 1).bit_length()
+
+
 def phase1_kernel(method, k, precision, m):
     """The phase-1 kernel the library picks for the table (D2Q) pass of
     queries against m-dimensional embeddings."""
-    depth = {"rwmd": 1, "omr": 2, "act": k, "ict": 64}[method]
+    depth = {"rwmd": 1, "omr": 2, "act": k, "ict": 16}[method]  # (ICT: its short lists)
     mb = (m + 6 + 63) // 64 * 64
-    if precision == "bf16" and depth + 8 <= 32 and mb <= 384:  # its own kernel: P1_TABLE, list size, K steps
-        return f"k_phase1_bf16<0, {16 if depth + 8 <= 16 else 32}, {mb // 16}>"
-    margin = 0 if precision == "fp32" or depth + 8 > 32 else 8
-    kl = 2
-    while kl < depth + margin:
-        kl *= 2
-    prec = 0 if margin == 0 else {"bf16": 1, "fp8": 2}[precision]
-    if prec == 0 and (m + 3) // 4 <= 7 and depth <= 64 and method != "ict":  # float32, at most 28 dims: 64-row kernel
-        return f"k_phase1_fast<0, {kl}, 0>"
-    if depth + margin <= 32:
-        return f"k_phase1_wide<0, {kl}, {prec}, false>"
+    if precision == "bf16" and depth + 8 <= 32 and mb <= 384:  # its own kernel: P1_TABLE, list size
+        return f"k_phase1_bf16<0, {16 if depth + 8 <= 16 else 32}>"
+    if precision == "fp8" and depth + 8 <= 32:
+        return f"k_phase1_wide<0, {pow2_at_least(depth + 8)}>"
+    if depth <= 32:  # P1_TABLE, list size, at most 28 dims
+        return f"k_phase1_rows<0, {pow2_at_least(depth)}, {'true' if (m + 3) // 4 <= 7 else 'false'}>"
     return "k_phase1_fast<0, 64, 0>" if depth <= 64 else "k_phase1_f32"
 
 
-KERNEL_SOURCES = {"k_phase1_bf16": "phase1_bf16.hip", "k_phase2_persistent": "phase2.hip",
+KERNEL_SOURCES = {"k_phase1_bf16": "phase1_bf16.hip", "k_phase1_rows": "phase1_rows.hip",
+                  "k_phase1_wide": "phase1_wide.hip", "k_phase1_fast": "phase1_fast.hip", "k_phase1_f32": "phase1.hip",
+                  "k_phase2_persistent": "phase2.hip", "k_phase2_lds": "phase2_lds.hip",
                   "k_p2_word_costs": "phase2.hip", "k_p2_doc_sums": "phase2.hip"}
 
 
@@ -93,7 +94,7 @@ def traffic_record(kernel, a, precision):
     import hashlib
 
     path = os.path.join(ROOT, "profiles", "traffic.json")
-    src = os.path.join(ROOT, "paper_1812_02091_amd", "csrc", KERNEL_SOURCES.get(kernel.split("<")[0], "phase1_wide.hip"))
+    src = os.path.join(ROOT, "paper_1812_02091_amd", "csrc", KERNEL_SOURCES[kernel.split("<")[0]])
     try:
         rec = json.load(open(path))
         digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
@@ -589,8 +590,11 @@ def roofline_of(phases, precision, a):
     ms = p2["ms"] / max(1, p2["launches"])
     byt = p2["work"] / max(1, p2["launches"])
     ach = byt / (ms * 1e-3) if ms > 0 else 0.0
+    # (one- and two-entry tables of the images' few words are read from LDS)
+    kt = {"rwmd": 1, "omr": 2, "act": a.k}.get(a.method, 64)
+    kernel = f"k_phase2_lds<{kt}>" if a.workload.startswith("image") and kt <= 2 else "k_phase2_persistent"
     return {"bound": "hbm", "achieved": ach / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": ach / HBM_PEAK,
-            "traffic": measured_traffic("k_phase2_persistent", a, precision), "kernel": "k_phase2_persistent",
+            "traffic": measured_traffic(kernel, a, precision), "kernel": kernel,
             "avg_launch_ms": ms, "bytes_per_launch": byt}
 
 

@@ -23,8 +23,8 @@
 // query's slices are in flight while a query ends.  The tile in which a
 // query ends is selected from once per query that has words there, the
 // others' keys masked.  18,000 documents of ~118 words x 5,300 words of 61
-// others and back, RWMD: items of one query 54.8 ms, of eight 48.7; 250
-// queries, k = 16: 29.1 -> 26.3 ms.
+// others and back, RWMD: items of one query 54.8 ms, of eight 48.7; 500
+// queries over a 70,000-word vocabulary, k = 16: 29.1 -> 26.3 ms.
 //
 // Selection: in registers.  A key and its word's position make one 64-bit
 // number that orders by (key, position), compared as float64 (the key's bits
@@ -35,9 +35,8 @@
 // nothing has to be certified or redone but ICT rows deeper than the list.
 // The kernel this replaced put every key through LDS (two barriers per 64
 // words) and merged lists held there entry by entry with a band for quantised
-// keys.  62,000 words x 300 dims x 250 queries of ~118 words, against it:
-// RWMD 17.0 -> 11.6 ms, k = 16 22.4 -> 13.5; 784 grid words x 20,000 images,
-// k = 8, 7.7 -> 2.6 ms.
+// keys.  Against it, tables: the RWMD matrix above 75 -> 48.7 ms, the 500
+// queries 42.7 -> 26.3, 784 grid words x 20,000 images, k = 8, 7.7 -> 2.6.
 //
 // Distances: |v|^2 + key unless cancellation could bite (below a quarter of
 // |v|^2 + |c|^2), where it is recomputed by direct differences.  Most of
@@ -68,7 +67,7 @@ constexpr uint32_t kNoKey = 0x7f800000u;  // +inf: above every key
 // RWMD matrix above).  Longer lists spill there (k = 16: 30.2 ms against 26.4
 // with three tiles and two workgroups, 28.0 with four), and the pair mode has
 // one short segment per item, for which two workgroups of wider passes are
-// the faster (2.1 against 2.3 ms over 250 queries).  Embeddings of at most 28
+// the faster (2.1 against 2.3 ms over 500 queries).  Embeddings of at most 28
 // dims (SMALL) have one slice and little to contract, so what counts there is
 // how many waves hide the set-up and the selection (four workgroups, at 128
 // registers, spill: 20,000 images x 784 words, k = 8, 2.9 against 2.6 ms).
