@@ -631,20 +631,26 @@ __global__ __launch_bounds__(kBT, LK == 16 ? 4 : 2) void k_phase1_bf16(P1Args a,
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ int64_t s_item;
   const BfLds sm = bf_lds(smem_raw, hmax, LK);
+  // no more items than workgroups: one each, no counter (and none to clear)
+  const bool once = total <= (int64_t)gridDim.x;
   const int xcd = blockIdx.x & 7;
-  const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
+  const int64_t lo = total * xcd / 8, hi = once ? total : total * (xcd + 1) / 8;
   unsigned long long nxt = 0;
-  if (threadIdx.x == 0) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+  if (threadIdx.x == 0 && !once) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+  int64_t item = blockIdx.x;
   while (true) {
-    __syncthreads();  // the previous item is done with LDS and s_item
-    if (threadIdx.x == 0) {
-      s_item = lo + (int64_t)nxt;
-      if (lo + (int64_t)nxt < hi) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+    if (!once) {
+      __syncthreads();  // the previous item is done with LDS and s_item
+      if (threadIdx.x == 0) {
+        s_item = lo + (int64_t)nxt;
+        if (lo + (int64_t)nxt < hi) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+      }
+      __syncthreads();
+      item = s_item;
     }
-    __syncthreads();
-    const int64_t item = s_item;
     if (item >= hi) break;
     bf16_task<MODE, LK>(a, sm, item, glog);
+    if (once) break;
   }
 }
 
@@ -662,10 +668,12 @@ hipError_t launch_bf16_one(const P1Args& a, int hmax, hipStream_t s) {
   const int64_t total = ((a.nq + (int64_t(1) << glog) - 1) >> glog) * nsb << glog;
   if (total <= 0) return hipSuccess;
   if (!a.work_ctr) return hipErrorInvalidValue;
-  e = launch_zero_ints((int*)a.work_ctr, 16, s);
-  if (e != hipSuccess) return e;
   const int grid = persistent_grid(fn, kBT, shmem, total);
   if (grid <= 0) return hipErrorInvalidConfiguration;
+  if (total > grid) {
+    e = launch_zero_ints((int*)a.work_ctr, 16, s);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((k_phase1_bf16<MODE, LK>), dim3(grid), dim3(kBT), shmem, s, a, total, hmax, glog);
   return hipGetLastError();
 }

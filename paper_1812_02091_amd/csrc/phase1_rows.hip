@@ -622,20 +622,27 @@ __global__ __launch_bounds__(kThreads, (groups_per_cu<MODE, LK, SMALL>())) void 
                                                                                       int lg, int glog) {
   __shared__ F32Smem<MODE, LK, SMALL> sm;
   __shared__ int64_t s_item;
+  // no more items than workgroups: one each, no counter (and none to clear;
+  // the streams' registers are full, and large launches are what they are for)
+  const bool once = !streams<MODE, SMALL>() && total <= (int64_t)gridDim.x;
   const int xcd = blockIdx.x & 7;
-  const int64_t lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
+  const int64_t lo = total * xcd / 8, hi = once ? total : total * (xcd + 1) / 8;
   unsigned long long nxt = 0;
-  if (threadIdx.x == 0) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+  if (threadIdx.x == 0 && !once) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+  int64_t item = blockIdx.x;
   while (true) {
-    __syncthreads();  // the previous item is done with LDS and s_item
-    if (threadIdx.x == 0) {
-      s_item = lo + (int64_t)nxt;
-      if (lo + (int64_t)nxt < hi) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+    if (!once) {
+      __syncthreads();  // the previous item is done with LDS and s_item
+      if (threadIdx.x == 0) {
+        s_item = lo + (int64_t)nxt;
+        if (lo + (int64_t)nxt < hi) nxt = atomicAdd(&a.work_ctr[xcd], 1ull);
+      }
+      __syncthreads();
+      item = s_item;
     }
-    __syncthreads();
-    const int64_t item = s_item;
     if (item >= hi) break;
     f32_task<MODE, LK, SMALL>(a, sm, item, lg, glog);
+    if (once) break;
   }
 }
 
@@ -661,9 +668,12 @@ hipError_t launch_f32_one(const P1Args& a, hipStream_t s) {
   }
   if (total <= 0) return hipSuccess;
   if (!a.work_ctr) return hipErrorInvalidValue;
-  hipError_t e = launch_zero_ints((int*)a.work_ctr, 16, s);
-  if (e != hipSuccess) return e;
   const int grid = persistent_grid(fn, kThreads, 0, total);
+  if (grid <= 0) return hipErrorInvalidConfiguration;
+  if (streams<MODE, SMALL>() || total > grid) {
+    const hipError_t e = launch_zero_ints((int*)a.work_ctr, 16, s);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((k_phase1_rows<MODE, LK, SMALL>), dim3(grid), dim3(kThreads), 0, s, a, total, lg, glog);
   return hipGetLastError();
 }
