@@ -32,6 +32,47 @@ constexpr int kUnroll = 8;       // non-zeros whose table loads are in flight to
 constexpr int kItemSlots = 16;   // document slots per lane and work item
 static_assert(kItemSlots % 4 == 0, "results are stored four at a time");
 
+// doc_cost entry by entry and only while mass is left: no padding slot and no
+// entry past a walk's end is looked at.  doc_cost multiplies those by a mass of
+// 0, which is 0 unless the distance is infinite; it takes a document whose sum
+// came out without a number again here, so that an infinite distance reaches
+// only the documents that move mass to it, and the same ones whatever the batch
+// (k_phase2_small and the word-major walk step like this).  The second entry
+// of a row's first pair is the exception in all of them (phase2_step.h).
+// (Asked per document: asked per group, it was 2 % of the LDS kernel's time.)
+__device__ __forceinline__ float doc_by_steps(int64_t e0, int64_t e1, const int2* __restrict__ xcv,
+                                              const char* __restrict__ ZP, uint32_t lane, uint32_t rbytes,
+                                              uint32_t pbytes, int KP) {
+  float t = 0.f, comp = 0.f;
+#pragma unroll 1
+  for (int64_t e = e0; e < e1; e += kUnroll) {
+    float pair = 0.f, quad = 0.f, g = 0.f;  // doc_cost's tree over eight terms
+#pragma unroll 1
+    for (int k = 0; k < kUnroll; ++k) {
+      float rem = 0.f, acc = 0.f;
+      if (e + k < e1) {
+        const int2 r = xcv[e + k];
+        const char* base = ZP + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(r.x) * rbytes + lane;
+        rem = __int_as_float(r.y);
+#pragma unroll 1
+        for (int p = 0; p < KP && rem > 0.f; ++p) {
+          const float4 f = *(const float4*)(base + p * pbytes);
+          step(rem, acc, f.x, f.y);
+          if (p == 0 || rem > 0.f) step(rem, acc, f.z, f.w);
+        }
+      }
+      pair = k & 1 ? pair + acc : acc;
+      if (k & 1) quad = k & 2 ? quad + pair : pair;
+      if ((k & 3) == 3) g = k & 4 ? g + quad : quad;
+    }
+    const float y = g - comp;
+    const float tt = t + y;
+    comp = (tt - t) - y;
+    t = tt;
+  }
+  return t;
+}
+
 // Cost of document [e0, e1) against a lane's query (64 consecutive queries a
 // wave): the non-zeros in order, kUnroll at a time with their first table
 // pairs loaded together.  Every lane of the wave is on this document, so its
@@ -121,6 +162,7 @@ __device__ __forceinline__ float doc_cost(int64_t e0, int64_t e1, const int2* __
     comp = (tt - t) - y;
     t = tt;
   }
+  if (__any(t != t)) t = doc_by_steps(e0, e1, xcv, ZP, lane, rbytes, pbytes, KP);
   return t;
 }
 

@@ -84,7 +84,7 @@ __device__ __forceinline__ T lds_read(lds_u32 a) {
 // lane's query.  roff / wbits: the lane's own record (its word's row offset,
 // its weight); ta, tb: the lane's addresses of (z0, w0) (or z) and z1 in
 // table row 0.  All reads are issued before the first use.  Padding records
-// have weight 0: cost 0.
+// have weight 0: cost 0 (but see doc_by_records).
 template <int KT, int B>
 __device__ __forceinline__ float group_cost(lds_u32 ta, lds_u32 tb, int roff, int wbits) {
   float a[8];
@@ -136,6 +136,38 @@ __device__ __forceinline__ float group_cost(lds_u32 ta, lds_u32 tb, int roff, in
     a[7] = cost(row_bcast<B + 7>(wbits), zw[7], z1[7]);
   }
   return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+}
+
+// The document's sum again, from its records alone, where it came out without
+// a number: a padding record's mass of 0 times an infinite distance of word 0
+// has none.
+template <int KT>
+__device__ __forceinline__ Kahan doc_by_records(const int2* __restrict__ rp, int len, lds_u32 ta, lds_u32 tb) {
+  Kahan s;
+#pragma unroll 1
+  for (int e = 0; e < len; e += 8) {
+    float pair = 0.f, quad = 0.f, g = 0.f;  // group_cost's tree
+#pragma unroll 1
+    for (int k = 0; k < 8; ++k) {
+      float a = 0.f;
+      if (e + k < len) {
+        const int2 rec = rp[e + k];
+        const lds_u32 ro = rec.x * row_bytes<KT>();
+        if constexpr (KT == 1) {
+          a = fmaf(__int_as_float(rec.y), lds_read<float>(ro + ta), 0.f);
+        } else {
+          const floatx2 zw = lds_read<floatx2>(ro + ta);
+          const float r = __uint_as_float(min((uint32_t)rec.y, __float_as_uint(zw.y)));
+          a = fmaf(__int_as_float(rec.y) - r, lds_read<float>(ro + tb), fmaf(r, zw.x, 0.f));
+        }
+      }
+      pair = k & 1 ? pair + a : a;
+      if (k & 1) quad = k & 2 ? quad + pair : pair;
+      if ((k & 3) == 3) g = k & 4 ? g + quad : quad;
+    }
+    s.add(g);
+  }
+  return s;
 }
 
 template <int KT>
@@ -194,6 +226,7 @@ __global__ __launch_bounds__(kLT) void k_phase2_lds(const int64_t* __restrict__ 
           s.add(group_cost<KT, 0>(ta, tb, ro, wb));
           if (e + 8 < len) s.add(group_cost<KT, 8>(ta, tb, ro, wb));
         }
+        if (__any(s.t != s.t)) s = doc_by_records<KT>(rp, len, ta, tb);
         ob[l * kOutLd + (int)(u - w0)] = s.t;
       }
     }

@@ -12,9 +12,10 @@ namespace lcemd {
 // canonicalise both operands).  A step with rem = +0 changes nothing
 // (r = +0, acc + 0 z = acc for finite z >= 0): so the second entry of a
 // table row's first 16-byte pair, which is always written (as (0, 0) when
-// the row has one entry), is stepped without testing rem; later pairs are
-// read only while some mass remains (their entries past the row's sink are
-// never written).
+// the row has one entry), is stepped without testing rem; later pairs count
+// only while some mass remains (their entries past the row's sink are never
+// written).  For z = +inf, 0 z has no number: a walk that ends at a row's first
+// entry has none either where the second is infinitely far.
 __device__ __forceinline__ void step(float& rem, float& acc, float z, float w) {
   const float r = __uint_as_float(min(__float_as_uint(rem), __float_as_uint(w)));
   rem -= r;

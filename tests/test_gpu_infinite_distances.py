@@ -1,0 +1,106 @@
+"""Finite embeddings whose squared norm is beyond float32: distances to such a
+word are +inf, which must reach the sums of the documents that hold it and no
+others, and must not be taken for a missing list entry."""
+import numpy as np
+import pytest
+
+from oracle import emd_oracle as O
+from synth.generators import CSR
+import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1812_02091_amd import lcemd
+
+    lcemd.load_library()
+    return lcemd
+
+
+def _csr(rows):
+    ptr = np.concatenate([[0], np.cumsum([len(c) for c, _ in rows])]).astype(np.int64)
+    return CSR(ptr, np.concatenate([c for c, _ in rows]).astype(np.int32),
+               np.concatenate([w for _, w in rows]).astype(np.float32))
+
+
+def _rows(rng, lo, v, lengths):
+    """Rows of the given lengths: distinct words of [lo, v), weights 1 - U[0,1)."""
+    out = []
+    for n in lengths:
+        w = 1.0 - rng.random(n)
+        out.append((np.sort(lo + rng.choice(v - lo, n, replace=False)), w / w.sum()))
+    return out
+
+
+# a group of eight non-zeros and its edges, two groups and theirs
+LENGTHS = [1, 2, 7, 8, 9, 15, 16, 17, 31, 33]
+
+
+def _far_word(L, method, k, m, precision):
+    """The lowest-numbered used word is infinitely far from everything: the
+    documents without it have the oracle's distances whatever their length and
+    the batch, those with it +inf."""
+    rng = np.random.default_rng(51)
+    v = 400
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    V[0, 0] = 1e20
+    rows = _rows(rng, 1, v, LENGTHS)
+    db = _csr(rows + [(np.array([0, 9]), np.array([0.5, 0.5])), (np.array([0]), np.array([1.0]))])
+    q = _csr(_rows(rng, 1, v, [int(x) for x in rng.integers(6, 60, 70)]))
+    near = _csr(rows)
+    want = O.Oracle(V, near.rowptr, near.col, near.val).matrix(q.rowptr, q.col, q.val, method, k, "d2q")
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    for B in (1, 8, 33, 64, 70):
+        print(f"[gpu] far word {method} k={k} m={m} {precision} B={B}", flush=True)
+        s = q.take(range(B))
+        got = ctx.distances(s.rowptr, s.col, s.val, method=method, k=k, direction="d2q", precision=precision)
+        P.assert_distances(got[:, :len(rows)], want[:B], f"B={B}")
+        assert np.all(np.isposinf(got[:, len(rows):])), B
+    ctx.close()
+
+
+MEASURES = [("rwmd", 1), ("act", 2), ("act", 5), ("ict", 1)]
+
+
+@pytest.mark.parametrize("method,k", MEASURES)
+def test_a_far_word_is_in_its_own_documents_only(L, method, k):
+    """Phase 2: batches per document, of 64 queries and (up to two entries a
+    row) from LDS."""
+    _far_word(L, method, k, 40, "fp32")
+
+
+@pytest.mark.parametrize("B", [1, 64])
+def test_a_far_entry_past_a_word_s_mass(L, B):
+    """Walks that end before an infinite entry of their table row, at every
+    entry of its second and third pair: lists of up to eight near words, then
+    two far ones (each word is a document of its own too, so that its list goes
+    on to them)."""
+    rng = np.random.default_rng(52)
+    v, m = 64, 4
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    far, near = [10, 20], [1, 3, 5, 7, 11, 13, 15, 17]
+    V[far, 0] = 1e20
+    words = np.arange(40, 49)
+    rows = [(words[:2], np.array([x, 1 - x])) for x in (0.95, 0.9, 0.8, 0.7, 0.6, 0.5)]
+    rows += [(words, np.full(9, 1.0 / 9)), (words[:7], np.full(7, 1.0 / 7))]
+    rows += [(np.array([w]), np.array([1.0])) for w in words]
+    db = _csr(rows)
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    for used in range(3, 9):  # near words of weight 0.96 / used each, the far ones hold the rest
+        c = np.array(sorted(near[:used] + far))
+        q = _csr([(c, np.where(np.isin(c, far), 0.02, 0.96 / used))] * B)
+        print(f"[gpu] far entry, {used} near words, B={B}", flush=True)
+        got = ctx.distances(q.rowptr, q.col, q.val, method="act", k=c.size, direction="d2q")
+        want = O.Oracle(V, db.rowptr, db.col, db.val).matrix(q.rowptr, q.col, q.val, "act", c.size, "d2q")
+        for u, (_, x) in enumerate(rows):
+            if x.max() > 0.96:  # some mass goes to the far words
+                assert np.all(np.isposinf(got[:, u])), (used, u)
+            else:
+                P.assert_distances(got[:, u:u + 1], want[:, u:u + 1], f"{used} near words, document {u}")
+    ctx.close()
