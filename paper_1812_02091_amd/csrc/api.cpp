@@ -291,6 +291,7 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
     if (rc) return rc;
   }
   const int margin = prec == LCEMD_FP32 ? 0 : kMargin;
+  a.zero_word = (int)c->v;
   a.Vb = c->Vb;
   a.Vbq = c->Vbq;
   a.vres = c->vres;
@@ -876,7 +877,7 @@ int lcemd_load_embeddings(lcemd_ctx* c, const float* V, int64_t v, int32_t m, ui
   free_emb(c);
   const int m_pad = ((m + 63) / 64) * 64;  // one 128-byte bf16 slice = 64 dims
   int rc;
-  if ((rc = dalloc(c, c->V, (size_t)v * m_pad, "embeddings"))) return rc;
+  if ((rc = dalloc(c, c->V, ((size_t)v + 1) * m_pad, "embeddings"))) return rc;
   if ((rc = dalloc(c, c->vnorm, (size_t)v, "row norms"))) return rc;
   const float* src = V;
   float* tmp = nullptr;

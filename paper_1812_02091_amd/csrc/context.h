@@ -42,7 +42,7 @@ struct lcemd_ctx {
   // embeddings (Sec. 4: V)
   int64_t v = 0;
   int m = 0, m_pad = 0;
-  float* V = nullptr;
+  float* V = nullptr;       // [v + 1][m_pad], the last row zeros
   float* vnorm = nullptr;
   uint16_t* Vb = nullptr;   // bfloat16 rows of mb dims (see P1Args::Vb)
   uint16_t* Vbq = nullptr;  // their query form (see P1Args::Vbq)

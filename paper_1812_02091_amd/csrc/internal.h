@@ -52,7 +52,8 @@ enum P1Prec : int { PREC_F32 = 0, PREC_BF16 = 1, PREC_FP8 = 2 };
 
 struct P1Args {
   // embeddings
-  const float* V;         // [v][m_pad] float32, zero padded
+  const float* V;         // [v + 1][m_pad] float32, zero padded
+  int zero_word;          // the row of zeros behind the words' rows
   const float* vnorm;     // [v] |v|^2 (float64 accumulation, stored float32)
   const uint16_t* Vb;     // [v][mb] bfloat16 rows: -2 v, then 1, 1, 1 and a three-piece
                           // split of |v|^2 in the six dims after the m real ones

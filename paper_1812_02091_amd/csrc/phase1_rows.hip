@@ -58,7 +58,11 @@ constexpr int kFR = 128;        // rows per workgroup
 constexpr int kFStride = 144;   // bytes per staged word slice (128 + 16 pad: conflict-free 16-byte reads)
 constexpr int kFCat = 2 * LCEMD_MAX_HIST;  // words of an item's queries in LDS at a time
 constexpr float kFGuard = 0.25f;
-constexpr uint32_t kNoKey = 0x7f800000u;  // +inf: above every key
+// No key: above every key, also +inf (a word whose squared norm is beyond
+// float32 is the farthest word, not a missing one) and the NaN that arithmetic
+// gives (0x7fc00000, between two such words); itself a quiet NaN, which a sum
+// hands on as it is, but not yet one as the high half of a float64.
+constexpr uint32_t kNoKey = 0x7fe00000u;
 
 // Tiles per pass at most, and workgroups per CU.  Two tiles let a wave of
 // lists of up to 8 entries fit 168 registers, three workgroups per CU, which
@@ -80,9 +84,9 @@ template <int MODE, int LK, bool SMALL>
 struct F32Smem {
   unsigned char st[SMALL ? 1 : 2][32 * max_tiles<MODE, LK, SMALL>() * kFStride];  // word slices, double-buffered
   float rcost[kFR];       // pair mode: the rows' costs
-  int cid[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];   // word 0 past the queries' words, up to a pass's end
+  int cid[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];   // zero_word past the queries' words, up to a pass's end
   float cap[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];
-  float qn[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];  // +inf there: those keys are above every key
+  float qn[kFCat + 32 * max_tiles<MODE, LK, SMALL>()];  // kNoKey there, and with a zero dot product the key too
 };
 
 // queries per item group: 8, or 32 over vocabularies of at least 2^18 used
@@ -543,10 +547,10 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<MODE, LK, SMAL
     const int64_t s0 = a.xptr[u];
     const int h = (int)(a.xptr[u + 1] - s0);
     for (int c = tid; c < h + kPad; c += kThreads) {
-      const int w = c < h ? a.xcol[s0 + c] : 0;
+      const int w = c < h ? a.xcol[s0 + c] : a.zero_word;
       sm.cid[c] = w;
       sm.cap[c] = c < h ? __int_as_float(a.xcv[s0 + c].y) : 0.f;
-      sm.qn[c] = c < h ? a.vnorm[w] : INFINITY;
+      sm.qn[c] = c < h ? a.vnorm[w] : __uint_as_float(kNoKey);
     }
     row.vn = a.vnorm[row.id];
     __syncthreads();
@@ -599,10 +603,10 @@ __device__ __forceinline__ void f32_task(const P1Args& a, F32Smem<MODE, LK, SMAL
       if (n > 0) {
         __syncthreads();  // the words before are done with
         for (int c = tid; c < n + kPad; c += kThreads) {
-          const int w = c < n ? a.qcol[s0 + c] : 0;
+          const int w = c < n ? a.qcol[s0 + c] : a.zero_word;
           sm.cid[c] = w;
           sm.cap[c] = c < n ? a.qval[s0 + c] : 0.f;
-          sm.qn[c] = c < n ? a.vnorm[w] : INFINITY;
+          sm.qn[c] = c < n ? a.vnorm[w] : __uint_as_float(kNoKey);
         }
         __syncthreads();
         f32_words<MODE, LK, SMALL>(a, sm, lst, row, n, qs, qe, s0, tid);

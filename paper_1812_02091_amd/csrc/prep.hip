@@ -5,7 +5,8 @@
 // (zero padding leaves dot products and distances unchanged).  Row norms
 // |v|^2 are accumulated in float64 and stored as float32; with
 // L2 normalisation (Sec. 5: word vectors are L2-normalised) the scale is
-// also computed in float64 and each value is rounded once.
+// also computed in float64 and each value is rounded once.  A row of zeros
+// follows the last word's (P1Args::zero_word).
 #include "internal.h"
 
 namespace lcemd {
@@ -16,6 +17,8 @@ __global__ __launch_bounds__(kThreads) void k_prep_embeddings(const float* __res
                                                               float* __restrict__ vnorm) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (r == v)
+    for (int d = lane; d < m_pad; d += 64) Vpad[r * (int64_t)m_pad + d] = 0.f;
   if (r >= v) return;
   const float* src = Vin + r * (int64_t)m;
   float* dst = Vpad + r * (int64_t)m_pad;
@@ -40,7 +43,7 @@ __global__ __launch_bounds__(kThreads) void k_prep_embeddings(const float* __res
 
 hipError_t launch_prep_embeddings(const float* Vin, int64_t v, int m, int m_pad, int l2norm,
                                   float* Vpad, float* vnorm, hipStream_t s) {
-  const int64_t g = (v + 3) / 4;
+  const int64_t g = (v + 1 + 3) / 4;
   hipLaunchKernelGGL(k_prep_embeddings, dim3((unsigned)g), dim3(kThreads), 0, s, Vin, v, m, m_pad,
                      l2norm, Vpad, vnorm);
   return hipGetLastError();

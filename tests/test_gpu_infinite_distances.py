@@ -104,3 +104,55 @@ def test_a_far_entry_past_a_word_s_mass(L, B):
             else:
                 P.assert_distances(got[:, u:u + 1], want[:, u:u + 1], f"{used} near words, document {u}")
     ctx.close()
+
+
+@pytest.mark.parametrize("method,k", MEASURES)
+def test_float32_tables_of_a_far_row(L, method, k):
+    """At most 28 dims: positions past the query's words, which stand for word
+    0, are no candidates."""
+    _far_word(L, method, k, 3, "fp32")
+
+
+@pytest.mark.parametrize("m", [3, 40])
+def test_far_query_words_need_no_redo(L, monkeypatch, m):
+    """A query word infinitely far from every row is a list entry like any
+    other: no row has to be redone for it, so a redo list of one row is
+    enough."""
+    rng = np.random.default_rng(53)
+    v = 300
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    V[7, 0] = 1e20
+    db = _csr(_rows(rng, 8, v, LENGTHS) + [(np.array([9]), np.array([1.0]))])
+    q = _csr([(np.array([1, 4, 7]), np.array([0.5, 0.4, 0.1])), (np.array([7]), np.array([1.0])),
+              (np.array([2, 7, 100]), np.array([0.2, 0.3, 0.5]))])
+    monkeypatch.setenv("LCEMD_FIX_CAP", "1")
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    for method, k in (("rwmd", 1), ("act", 2), ("act", 3)):
+        print(f"[gpu] far query word {method} k={k} m={m}", flush=True)
+        got = ctx.distances(q.rowptr, q.col, q.val, method=method, k=k, direction="d2q")
+        # (over several groups of eight the sum's compensation is inf - inf)
+        assert not np.any(np.isfinite(got[1])), (method, k)
+        if method == "rwmd":
+            want = O.Oracle(V, db.rowptr, db.col, db.val).matrix(q.rowptr, q.col, q.val, method, k, "d2q")
+            P.assert_distances(got[[0, 2]], want[[0, 2]])
+    S, Z, _ = ctx.tables(q.rowptr, q.col, q.val, 3)
+    assert np.all(S[1] == [0, -1, -1]) and np.all(np.isposinf(Z[1, :, 0]))
+    for b, far in ((0, 2), (2, 1)):
+        assert np.all(S[b, :, 2] == far) and np.all(np.isposinf(Z[b, :, 2])) and np.all(np.isfinite(Z[b, :, :2]))
+    ctx.close()
+
+
+@pytest.mark.parametrize("m", [3, 40])
+def test_candidate_pairs_with_a_far_word(L, m):
+    """A document of the far word alone, which the query holds too: nothing to
+    move one way, an infinite way for the query's other word."""
+    V = np.random.default_rng(54).standard_normal((50, m)).astype(np.float32)
+    V[3, 0] = 1e20
+    one = np.array([1.0])
+    db = _csr([(np.array([3]), one)] + [(np.array([10 + i]), one) for i in range(30)])
+    q = _csr([(np.array([2, 3]), np.array([0.5, 0.5]))])
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    print(f"[gpu] far pair m={m}", flush=True)
+    idx, dist = ctx.topl(q.rowptr, q.col, q.val, db.n, method="rwmd", direction="sym")
+    assert np.all(np.isposinf(dist)), (idx, dist)
+    ctx.close()
