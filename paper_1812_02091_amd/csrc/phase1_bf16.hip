@@ -83,7 +83,9 @@ constexpr uint32_t kPosMask = 511u;   // 9 position bits (words < 512)
 // twice the largest relative rounding of a packed key: 2 * 2^(9 - 23)
 constexpr float kQuant = 1.f / 8192.f;
 constexpr float kGuard = 0.25f;       // cancellation guard of the float32 form
-constexpr uint32_t kNoD2 = 0x7f800000u;
+// no listed word: above every squared distance, also +inf and the NaN that
+// arithmetic gives, and not a float64 NaN as the high half of one
+constexpr uint32_t kNoD2 = 0x7fe00000u;
 
 // LDS of a workgroup: a union of the contraction's word slice, the lists
 // on their way to the recompute's lanes and its staged float32 words; then

@@ -156,3 +156,33 @@ def test_candidate_pairs_with_a_far_word(L, m):
     idx, dist = ctx.topl(q.rowptr, q.col, q.val, db.n, method="rwmd", direction="sym")
     assert np.all(np.isposinf(dist)), (idx, dist)
     ctx.close()
+
+
+@pytest.mark.parametrize("m", [3, 40])
+@pytest.mark.parametrize("method,k", MEASURES)
+def test_bf16_tables_of_a_far_row(L, method, k, m):
+    """The exact re-sort keeps a listed word at an infinite distance."""
+    _far_word(L, method, k, m, "bf16")
+
+
+@pytest.mark.parametrize("m", [3, 40])
+def test_bf16_tables_of_a_far_query_word(L, m):
+    """Its listed entries are those of float32 keys."""
+    rng = np.random.default_rng(55)
+    v = 300
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    V[7, 0] = 1e20
+    db = _csr(_rows(rng, 8, v, LENGTHS))
+    q = _csr([(np.array([1, 4, 7]), np.array([0.5, 0.4, 0.1])), (np.array([7]), np.array([1.0])),
+              (np.array([20, 30]), np.array([0.5, 0.5]))])
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    print(f"[gpu] bf16, far query word m={m}", flush=True)
+    for k in (1, 2, 3):
+        a = ctx.tables(q.rowptr, q.col, q.val, k)
+        b = ctx.tables(q.rowptr, q.col, q.val, k, precision="bf16")
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[2], b[2]) and np.allclose(a[1], b[1], rtol=1e-6), k
+    want = O.Oracle(V, db.rowptr, db.col, db.val).matrix(q.rowptr, q.col, q.val, "rwmd", 1, "d2q")
+    got = ctx.distances(q.rowptr, q.col, q.val, method="rwmd", direction="d2q", precision="bf16")
+    P.assert_distances(got[[0, 2]], want[[0, 2]])
+    assert not np.any(np.isfinite(got[1]))
+    ctx.close()
