@@ -581,7 +581,8 @@ __device__ __forceinline__ void bf16_task(const P1Args& a, const BfLds& sm, int6
   // the merge cut this list (k_eff or capacity reached in key order); a
   // shortfall after the exact re-sort is a rounding residue of the
   // capacity sum, which the last entry absorbs
-  if (!covered && sm.rflag[xr]) covered = true;
+  // (a row without entries, whose band has no number, is written by the redo)
+  if (!covered && sm.rflag[xr]) covered = D > 0;
   const int64_t r = r0 + xr;
   if (sub == 0) {
     bool redo = !covered && D < h;

@@ -186,3 +186,21 @@ def test_bf16_tables_of_a_far_query_word(L, m):
     P.assert_distances(got[[0, 2]], want[[0, 2]])
     assert not np.any(np.isfinite(got[1]))
     ctx.close()
+
+
+def test_bf16_tables_of_a_row_of_zeros_and_a_far_query_word(L):
+    """The row's error band has no number (0 times infinity), so nothing is
+    listed: its table row is written all the same."""
+    V = np.random.default_rng(56).standard_normal((60, 40)).astype(np.float32)
+    V[7, 0] = 1e20
+    V[9] = 0.0
+    db = _csr([(np.array([9]), np.array([1.0])), (np.array([8, 9, 12]), np.array([0.5, 0.25, 0.25]))])
+    q = _csr([(np.array([1, 7]), np.array([0.5, 0.5]))])
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    print("[gpu] bf16, row of zeros, far query word", flush=True)
+    S, Z, W = ctx.tables(q.rowptr, q.col, q.val, 2, precision="bf16")
+    assert np.all(S[0] == [0, 1]) and np.all(W[0] == 0.5) and np.all(np.isposinf(Z[0, :, 1]))
+    assert np.allclose(Z[0, 1, 0], np.linalg.norm(V[1].astype(np.float64)), rtol=1e-6)  # (the used words: 8, 9, 12)
+    got = ctx.distances(q.rowptr, q.col, q.val, method="rwmd", direction="d2q", precision="bf16")
+    P.assert_distances(got, O.Oracle(V, db.rowptr, db.col, db.val).matrix(q.rowptr, q.col, q.val, "rwmd", 1, "d2q"))
+    ctx.close()
