@@ -1126,9 +1126,13 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
   const int64_t B = Q.B;
   if (o->exclude_self >= 0 && o->exclude_self + B > n)
     return fail(c, LCEMD_E_INVALID_ARG, "exclude_self + B exceeds the database size");
+  // the caller's device arrays are written once nothing but a device error can
+  // fail the call: symmetric results, which an early pass may leave to a later
+  // one, collect in scratch, one-way results are unpacked after the last check
+  const bool sym = o->direction == LCEMD_SYM;
   int64_t* didx = idx;
   float* ddist = dist;
-  if (!Q.device) {
+  if (!Q.device || sym) {
     if ((rc = wsget(c, "topl_idx", (size_t)B * l, didx)) || (rc = wsget(c, "topl_dist", (size_t)B * l, ddist))) return rc;
   }
   const int64_t excl = o->exclude_self >= 0 ? o->exclude_self : -1;
@@ -1141,9 +1145,9 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
   } else {
     // (its overflow flags are read with the first results: the selection is
     // queued behind it, and runs again if a tile has to)
-    if ((rc = d2q_queue(c, db, Q, o, d2q, n, o->direction == LCEMD_SYM ? B : 0, run))) return rc;
+    if ((rc = d2q_queue(c, db, Q, o, d2q, n, sym ? B : 0, run))) return rc;
   }
-  if (o->direction != LCEMD_SYM) {
+  if (!sym) {
     uint64_t* cand;
     if ((rc = wsget(c, "cand", (size_t)B * l, cand))) return rc;
     bool again = false;
@@ -1151,11 +1155,12 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
       if ((rc = prof_begin(c, "select", (double)B * n))) return rc;
       if ((rc = select_rows(c, d2q, n, n, B, l, nullptr, excl, cand))) return rc;
       if ((rc = prof_end(c))) return rc;
-      HIPCHK(c, launch_unpack_topl(cand, l, B, nullptr, l, didx, ddist, c->stream));
+      if (!Q.device) HIPCHK(c, launch_unpack_topl(cand, l, B, nullptr, l, didx, ddist, c->stream));
       again = false;
       if ((rc = d2q_finish(c, db, Q, o, d2q, n, run, &again))) return rc;
       run.tiles.clear();
     } while (again);
+    if (Q.device) HIPCHK(c, launch_unpack_topl(cand, l, B, nullptr, l, didx, ddist, c->stream));
   } else {
     // exact symmetric top-l by lower-bound pruning (SYM >= D2Q)
     std::vector<int32_t> rows(B);
@@ -1227,6 +1232,7 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
       Lp *= 4;
       first = false;
     }
+    if (Q.device) HIPCHK(c, launch_copy_topl(didx, ddist, B * l, idx, dist, c->stream));
   }
   if (!Q.device) {
     HIPCHK(c, hipMemcpyAsync(idx, didx, sizeof(int64_t) * B * l, hipMemcpyDeviceToHost, c->stream));

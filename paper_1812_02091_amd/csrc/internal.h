@@ -188,6 +188,8 @@ hipError_t launch_finalize_sym(const uint64_t* cand, int64_t cand_ld, int64_t ca
 hipError_t launch_unpack_topl(const uint64_t* cand, int64_t cand_ld, int64_t rows,
                               const int32_t* row_list, int L, int64_t* idx, float* dist,
                               hipStream_t s);
+hipError_t launch_copy_topl(const int64_t* idx_from, const float* dist_from, int64_t count, int64_t* idx, float* dist,
+                            hipStream_t s);
 hipError_t launch_max_inplace(float* a, const float* b, int64_t count, hipStream_t s);
 hipError_t launch_record_weights(const int2* xcv, int64_t nnz, float* val, hipStream_t s);
 // Records of a query batch as the set phase 2 walks (reverse.hip): scratch

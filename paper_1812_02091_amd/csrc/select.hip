@@ -262,6 +262,24 @@ hipError_t launch_unpack_topl(const uint64_t* cand, int64_t cand_ld, int64_t row
   return hipGetLastError();
 }
 
+// Finished lists to the caller's arrays.
+__global__ __launch_bounds__(kThreads) void k_copy_topl(const int64_t* __restrict__ idx_from,
+                                                        const float* __restrict__ dist_from, int64_t count,
+                                                        int64_t* __restrict__ idx, float* __restrict__ dist) {
+  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (t >= count) return;
+  idx[t] = idx_from[t];
+  dist[t] = dist_from[t];
+}
+
+hipError_t launch_copy_topl(const int64_t* idx_from, const float* dist_from, int64_t count, int64_t* idx, float* dist,
+                            hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_copy_topl, dim3((unsigned)((count + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, idx_from,
+                     dist_from, count, idx, dist);
+  return hipGetLastError();
+}
+
 // The database weights (the second word of each 8-byte record).
 __global__ __launch_bounds__(kThreads) void k_record_weights(const int2* __restrict__ xcv, int64_t nnz,
                                                              float* __restrict__ val) {
