@@ -62,6 +62,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "launch_sizes.h"
 
 namespace lcemd {
 
@@ -658,10 +659,11 @@ __global__ __launch_bounds__(kBT, LK == 16 ? 4 : 2) void k_phase1_bf16(P1Args a,
 }
 
 template <int MODE, int LK>
-hipError_t launch_bf16_one(const P1Args& a, int hmax, hipStream_t s) {
+hipError_t launch_bf16_one(const P1Args& a, int seg_hmax, hipStream_t s) {
+  const int hmax = bf16_layout_words(seg_hmax, kBSeg);
   const size_t shmem = bf_bytes(hmax, LK);
   const void* fn = (const void*)k_phase1_bf16<MODE, LK>;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bf_bytes(kBSeg, LK));
   if (e != hipSuccess) return e;
   const int64_t nsb = (a.v_used + kBR - 1) / kBR;
   // (a smaller batch has smaller groups: every empty item costs its workgroup a

@@ -37,6 +37,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "launch_sizes.h"
 #include "phase2_step.h"
 
 namespace lcemd {
@@ -247,8 +248,8 @@ template <int KT>
 hipError_t launch_lds(const int64_t* xptr, const int2* xcv, int64_t n, const int32_t* perm, int64_t v_used,
                       const float2* ZW, int64_t zw_nq, int64_t nq, float* out, int64_t ld, hipStream_t s) {
   const void* fn = (const void*)k_phase2_lds<KT>;
-  const size_t sh = lds_bytes(v_used, KT);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+  const size_t sh = lds_launch_bytes(lds_bytes(v_used, KT), kLdsMax);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
   if (e != hipSuccess) return e;
   const int64_t units = (nq + kG - 1) / kG * ((n + kWin - 1) / kWin);
   const int grid = persistent_grid(fn, kLT, sh, units);
