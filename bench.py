@@ -77,7 +77,7 @@ def phase1_kernel(method, k, precision, m):
         return f"k_phase1_wide<0, {pow2_at_least(depth + 8)}>"
     if depth <= 32:  # P1_TABLE, list size, at most 28 dims
         return f"k_phase1_rows<0, {pow2_at_least(depth)}, {'true' if (m + 3) // 4 <= 7 else 'false'}>"
-    return "k_phase1_fast<0, 64, 0>" if depth <= 64 else "k_phase1_f32"
+    return "k_phase1_fast<0>" if depth <= 64 else "k_phase1_f32"
 
 
 KERNEL_SOURCES = {"k_phase1_bf16": "phase1_bf16.hip", "k_phase1_rows": "phase1_rows.hip",

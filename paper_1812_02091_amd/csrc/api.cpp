@@ -290,7 +290,6 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
     int rc = wsget(c, "p1_counters", 8, a.work_ctr);
     if (rc) return rc;
   }
-  const int margin = prec == LCEMD_FP32 ? 0 : kMargin;
   a.zero_word = (int)c->v;
   a.Vb = c->Vb;
   a.Vbq = c->Vbq;
@@ -301,7 +300,6 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
   a.vscale = c->vscale;
   a.m8 = c->m8;
   if (prec == LCEMD_BF16) {
-    a.KT_margin = margin;
     a.rb_max = 0;
     // per-call row and query-word records (callers that capture graphs
     // bring their own buffers; a.qnnz covers the batch's query non-zeros)
@@ -321,27 +319,22 @@ int p1_launch(lcemd_ctx* c, P1Args& a, int mode, int prec, int depth, int seg_hm
     return LCEMD_OK;
   }
   if (prec == LCEMD_FP32 && depth <= 32 && !c->force_kernel) {
-    a.KT_margin = 0;
     a.rb_max = phase1_rows_partials(a, row_hmax);
     HIPCHK(c, launch_phase1_rows(a, mode, depth, c->stream));
   } else if (prec == LCEMD_FP8) {  // tables, lists of up to 32 entries
-    const int KL = pow2ceil(depth + margin);
-    a.KT_margin = margin;
+    const int KL = pow2ceil(depth + kMargin);
     a.rb_max = 0;
     HIPCHK(c, launch_phase1_wide(a, mode, KL, c->stream));
   } else if (depth <= 64 && c->force_kernel != 2) {
-    const int KL = pow2ceil(std::min(depth + margin, 64));
-    a.KT_margin = margin;
     a.rb_max = (row_hmax + kRows - 1) / kRows;
-    HIPCHK(c, launch_phase1_fast(a, mode, KL, prec, c->stream));
+    HIPCHK(c, launch_phase1_fast(a, mode, c->stream));
   } else {
-    a.KT_margin = 0;
     a.rb_max = (row_hmax + kRows - 1) / kRows;
     if (seg_hmax > kSegShort && !a.deep_keys) {
       int rc = wsget(c, "deep_keys", (size_t)(kDeepSlots * kDeepSlotFloats), a.deep_keys);
       if (rc) return rc;
     }
-    HIPCHK(c, launch_phase1_deep(a, mode, seg_hmax, PREC_F32, c->stream));
+    HIPCHK(c, launch_phase1_deep(a, mode, seg_hmax, c->stream));
   }
   return LCEMD_OK;
 }

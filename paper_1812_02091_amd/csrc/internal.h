@@ -48,8 +48,6 @@ enum P1Mode : int {
                       // emits the summed per-row transfer cost (Q2D)
 };
 
-enum P1Prec : int { PREC_F32 = 0, PREC_BF16 = 1, PREC_FP8 = 2 };
-
 struct P1Args {
   // embeddings
   const float* V;         // [v + 1][m_pad] float32, zero padded
@@ -65,7 +63,7 @@ struct P1Args {
   int64_t qnnz;           // query non-zeros (qptr[B]) the records cover
   int mb;                 // dims per bfloat16 row (bf16_row_dims(m))
   int m;                  // real dims
-  const uint8_t* V8;      // [v][m8] fp8 (OCP e4m3) codes of V / vscale (PREC_FP8)
+  const uint8_t* V8;      // [v][m8] fp8 (OCP e4m3) codes of V / vscale
   const float* vscale;    // [v] fp8 row scales
   int m8;                 // bytes per fp8 row: m_pad rounded up to 128
   int m_pad;
@@ -74,7 +72,6 @@ struct P1Args {
   int method;             // LCEMD_RWMD / OMR / ACT / ICT
   int k;                  // ACT k
   int KT;                 // table stride (entries per table row)
-  int KT_margin;          // extra candidates kept for the exact re-sort (bf16/fp8 keys)
   // database
   int64_t n;
   const int64_t* xptr;    // [n+1]
@@ -148,8 +145,9 @@ __device__ __forceinline__ void zw_write_row(float2* ZW, int64_t zw_nq, int KT, 
 }
 
 // kernel launchers (each in the translation unit of its kernel)
-hipError_t launch_phase1_deep(const P1Args& a, int mode, int hmax, int prec, hipStream_t s);
-hipError_t launch_phase1_fast(const P1Args& a, int mode, int KT, int prec, hipStream_t s);
+hipError_t launch_phase1_deep(const P1Args& a, int mode, int hmax, hipStream_t s);
+// float32 keys, lists of up to 64 entries
+hipError_t launch_phase1_fast(const P1Args& a, int mode, hipStream_t s);
 // fp8 table modes (lists of up to 32 entries, segments <= kSegShort words)
 hipError_t launch_phase1_wide(const P1Args& a, int mode, int KL, hipStream_t s);
 // float32 keys, lists of up to 32 entries, segments of up to LCEMD_MAX_HIST

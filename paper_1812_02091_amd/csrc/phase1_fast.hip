@@ -13,14 +13,12 @@
 // (see internal.h).  Keys: |c|^2 - 2 <v_r, c>, ranking a row's columns like
 // the squared distance; ties go to the lower column position.
 //
-// Precision of the contraction:
-//   float32  (32x32x2 f32 MFMA): list distances use the contraction value
-//            |v|^2 + key unless that value is below a quarter of
-//            |v|^2 + |c|^2 (cancellation), where they are recomputed exactly;
-//   bfloat16 (32x32x16 bf16 MFMA, float32 accumulation): the list is
-//            over-selected by the host-given margin, every entry is
-//            recomputed exactly in float32, re-sorted by the exact value,
-//            and only then cut to k_eff / capacity.
+// Float32 contraction (32x32x2 f32 MFMA): list distances use the contraction
+// value |v|^2 + key unless that value is below a quarter of |v|^2 + |c|^2
+// (cancellation), where they are recomputed exactly.
+//
+// Runs lists of 33 to 64 entries (shorter ones: phase1_rows.hip, whose register
+// lists end at 32; there because of the test hook only).
 //
 // Work order: table-mode workgroups are mapped so that each of the eight
 // XCDs walks a contiguous range of (query group, row block, query) tiles,
@@ -31,7 +29,6 @@
 namespace lcemd {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 namespace {
 
@@ -57,9 +54,9 @@ constexpr int kStageStride = 144;  // bytes per staged row (128 data + 16 pad)
 constexpr int kCKS = 68;           // floats per row of a pass's keys; 68 % 64 == 4
 constexpr int kSeg = LCEMD_MAX_HIST;
 constexpr int kGroup = 8;          // queries per tile group (table modes)
-constexpr float kGuard = 0.25f;    // float32 path: recompute below this cancellation ratio
+constexpr float kGuard = 0.25f;    // recompute below this cancellation ratio
+constexpr int KL = 64;             // list capacity
 
-template <int KL>
 struct FastSmem {
   union {
     unsigned char st[2 * kRows * kStageStride];  // staged row / column slices
@@ -105,10 +102,9 @@ __device__ __forceinline__ float exact_d2(const float* __restrict__ V, int m_pad
 
 // One work item: (query, 64-row block) in the table modes, (pair, row
 // block) in pair mode.  Returns early (uniformly) for empty items.
-template <int MODE, int KL, int PREC>
+template <int MODE>
 __device__ __forceinline__ void fast_task(const P1Args& a, unsigned char* smem_raw, int64_t item) {
-  using Sm = FastSmem<KL>;
-  Sm& sm = *reinterpret_cast<Sm*>(smem_raw);
+  FastSmem& sm = *reinterpret_cast<FastSmem*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
   // ---------------- task decode ----------------
@@ -193,18 +189,15 @@ __device__ __forceinline__ void fast_task(const P1Args& a, unsigned char* smem_r
     else if (a.method == LCEMD_RWMD) kef = 1;
     else kef = min(a.k, h);
   }
-  // list length during selection: exact path keeps k_eff, approximate keys
-  // keep a margin of extra candidates for the exact re-sort
-  const int sel_limit = PREC == PREC_F32 ? min(KL, kef) : min(KL, min(h, kef + a.KT_margin));
-  constexpr bool kCapStop = PREC == PREC_F32 && MODE != P1_TABLE_FULL;
+  const int sel_limit = min(KL, kef);  // list length during selection
+  constexpr bool kCapStop = MODE != P1_TABLE_FULL;
 
   // ---------------- contraction, pass by pass ----------------
-  const unsigned char* base = PREC == PREC_F32 ? (const unsigned char*)a.V : (const unsigned char*)a.Vb;
-  const size_t rowbytes = (size_t)a.m_pad * (PREC == PREC_F32 ? 4 : 2);
+  const unsigned char* base = (const unsigned char*)a.V;
+  const size_t rowbytes = (size_t)a.m_pad * 4;
   // 128-byte slices that hold real dims (the zero padding past them would
   // add exact zeros)
-  const int realbytes = 4 * a.m4 * (PREC == PREC_F32 ? 4 : 2);
-  const int nsl = min((int)(rowbytes / 128), (realbytes + 127) / 128);
+  const int nsl = min((int)(rowbytes / 128), (16 * a.m4 + 127) / 128);
   unsigned char* stV = sm.u.st;
   unsigned char* stQ = sm.u.st + kRows * kStageStride;
   const int wr = (wave & 1) * 32, wc = (wave >> 1) * 32;
@@ -248,29 +241,17 @@ __device__ __forceinline__ void fast_task(const P1Args& a, unsigned char* smem_r
       __syncthreads();
       if (sl + 1 < nsl) gload(c0, sl + 1);
       else if (c0 + kColChunk < h) gload(c0 + kColChunk, 0);
-      if constexpr (PREC == PREC_F32) {
-        // lane half lh supplies dims [16*lh, 16*lh+16) of the 32-dim slice
-        const float* ap = (const float*)(stV + (wr + li) * kStageStride) + 16 * lh;
-        const float* bp = (const float*)(stQ + (wc + li) * kStageStride) + 16 * lh;
+      // lane half lh supplies dims [16*lh, 16*lh+16) of the 32-dim slice
+      const float* ap = (const float*)(stV + (wr + li) * kStageStride) + 16 * lh;
+      const float* bp = (const float*)(stQ + (wc + li) * kStageStride) + 16 * lh;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float4 av = *(const float4*)(ap + 4 * j);
-          const float4 bv = *(const float4*)(bp + 4 * j);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv.w, acc, 0, 0, 0);
-        }
-      } else {
-        // 64-dim slice: step s, lane half lh supplies dims [16s + 8lh, +8)
-        const __bf16* ap = (const __bf16*)(stV + (wr + li) * kStageStride) + 8 * lh;
-        const __bf16* bp = (const __bf16*)(stQ + (wc + li) * kStageStride) + 8 * lh;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const bf16x8 av = *(const bf16x8*)(ap + 16 * s);
-          const bf16x8 bv = *(const bf16x8*)(bp + 16 * s);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
-        }
+      for (int j = 0; j < 4; ++j) {
+        const float4 av = *(const float4*)(ap + 4 * j);
+        const float4 bv = *(const float4*)(bp + 4 * j);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv.w, acc, 0, 0, 0);
       }
     }
     __syncthreads();
@@ -342,7 +323,7 @@ __device__ __forceinline__ void fast_task(const P1Args& a, unsigned char* smem_r
     const uint64_t e = lst[l];
     const int pos = (int)(uint32_t)e;
     float d2 = sm.rvn[row] + f_unpack(e);
-    bool need = PREC != PREC_F32 || !(d2 >= kGuard * (sm.rvn[row] + sm.qn[pos]));
+    bool need = !(d2 >= kGuard * (sm.rvn[row] + sm.qn[pos]));
     if (MODE != P1_TABLE_FULL && a.method == LCEMD_OMR && l == 0) need = true;
     if (need) d2 = exact_d2(a.V, a.m_pad, a.m4, sm.rid[row], sm.cid[pos], sm.rvn[row]);
     sm.u.zb[row * KL + l] = d2;
@@ -352,20 +333,6 @@ __device__ __forceinline__ void fast_task(const P1Args& a, unsigned char* smem_r
   if (sub == 0 && row_ok) {
     uint64_t* L = &sm.lst[par][row * KL];
     float* Z2 = &sm.u.zb[row * KL];
-    if constexpr (PREC != PREC_F32) {
-      // re-sort by the exact squared distance (position breaks ties)
-      for (int i = 1; i < len; ++i) {
-        const uint64_t e = f_pack(Z2[i], (uint32_t)L[i]);
-        int j = i - 1;
-        while (j >= 0 && f_pack(Z2[j], (uint32_t)L[j]) > e) {
-          L[j + 1] = L[j];
-          Z2[j + 1] = Z2[j];
-          --j;
-        }
-        L[j + 1] = e;
-        Z2[j + 1] = f_unpack(e);
-      }
-    }
     // depth actually used by the row
     int D = 0;
     bool covered = false;
@@ -423,8 +390,8 @@ __device__ __forceinline__ void fast_task(const P1Args& a, unsigned char* smem_r
   }
 }
 
-// Persistent grid fed by per-XCD counters (as the 128-row kernel).
-template <int MODE, int KL, int PREC>
+// Persistent grid fed by per-XCD counters (as k_phase1_wide).
+template <int MODE>
 __global__ __launch_bounds__(kThreads, 2) void k_phase1_fast(P1Args a, int64_t total) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ int64_t s_item;
@@ -436,14 +403,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_phase1_fast(P1Args a, int64_t t
     __syncthreads();
     const int64_t item = s_item;
     if (item >= hi) break;
-    fast_task<MODE, KL, PREC>(a, smem_raw, item);
+    fast_task<MODE>(a, smem_raw, item);
   }
 }
 
-template <int MODE, int KL, int PREC>
+template <int MODE>
 static hipError_t launch_fast_one(const P1Args& a, hipStream_t s) {
-  const size_t shmem = sizeof(FastSmem<KL>);
-  const void* fn = (const void*)k_phase1_fast<MODE, KL, PREC>;
+  const size_t shmem = sizeof(FastSmem);
+  const void* fn = (const void*)k_phase1_fast<MODE>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
   int64_t total;
@@ -459,34 +426,16 @@ static hipError_t launch_fast_one(const P1Args& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int grid = persistent_grid(fn, kThreads, shmem, total);
   if (grid <= 0) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_phase1_fast<MODE, KL, PREC>), dim3(grid), dim3(kThreads), shmem, s, a, total);
+  hipLaunchKernelGGL((k_phase1_fast<MODE>), dim3(grid), dim3(kThreads), shmem, s, a, total);
   return hipGetLastError();
 }
 
-template <int MODE, int PREC>
-static hipError_t launch_fast_mode(const P1Args& a, int KL, hipStream_t s) {
-  if (KL <= 2) return launch_fast_one<MODE, 2, PREC>(a, s);
-  if (KL <= 4) return launch_fast_one<MODE, 4, PREC>(a, s);
-  if (KL <= 8) return launch_fast_one<MODE, 8, PREC>(a, s);
-  if (KL <= 16) return launch_fast_one<MODE, 16, PREC>(a, s);
-  if (KL <= 32) return launch_fast_one<MODE, 32, PREC>(a, s);
-  if (KL <= 64) return launch_fast_one<MODE, 64, PREC>(a, s);
-  return hipErrorInvalidValue;
-}
-
-template <int PREC>
-static hipError_t launch_fast_prec(const P1Args& a, int mode, int KL, hipStream_t s) {
+hipError_t launch_phase1_fast(const P1Args& a, int mode, hipStream_t s) {
   switch (mode) {
-    case P1_TABLE: return launch_fast_mode<P1_TABLE, PREC>(a, KL, s);
-    case P1_TABLE_FULL: return launch_fast_mode<P1_TABLE_FULL, PREC>(a, KL, s);
-    case P1_PAIR: return launch_fast_mode<P1_PAIR, PREC>(a, KL, s);
+    case P1_TABLE: return launch_fast_one<P1_TABLE>(a, s);
+    case P1_TABLE_FULL: return launch_fast_one<P1_TABLE_FULL>(a, s);
+    case P1_PAIR: return launch_fast_one<P1_PAIR>(a, s);
   }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_phase1_fast(const P1Args& a, int mode, int KL, int prec, hipStream_t s) {
-  if (prec == PREC_F32) return launch_fast_prec<PREC_F32>(a, mode, KL, s);
-  if (prec == PREC_BF16) return hipErrorInvalidValue;  // bf16 keys: launch_phase1_bf16
   return hipErrorInvalidValue;
 }
 
