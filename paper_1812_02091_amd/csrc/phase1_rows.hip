@@ -366,15 +366,22 @@ __device__ __forceinline__ void f32_store(const P1Args& a, const F32Smem<MODE, L
   const Cut<MODE, LK, SMALL> c(a, sm, lst, row, h);
   if (!row.ok) return;
   // an ICT row deeper than the list: redone exactly by k_fix_rows while the
-  // redo list has room, else the launch reports overflow
-  if (!c.covered && c.D < h && lh == 0) {
+  // redo list has room, else the launch reports overflow.  So is a row with keys
+  // that are no numbers (+inf - inf: words whose squared norms are beyond float32,
+  // against the row of one),
+  // which come first in the list, by position; where the redo list is full it
+  // keeps that order.
+  const bool deeper = !c.covered && c.D < h;
+  const uint32_t first = (uint32_t)__double2hiint(lst[0]);
+  const bool unordered = (first << 1) > 0xff000000u && first != kNoKey;
+  if ((deeper || unordered) && lh == 0) {
+    bool listed = false;
     if (a.fix_list) {
       const int slot = atomicAdd(a.fix_count, 1);
-      if (slot < a.fix_cap) a.fix_list[slot] = qi * a.v_used + row.r;
-      else if (a.overflow) a.overflow[0] = 1;
-    } else if (a.overflow) {
-      a.overflow[0] = 1;
+      listed = slot < a.fix_cap;
+      if (listed) a.fix_list[slot] = qi * a.v_used + row.r;
     }
+    if (!listed && deeper && a.overflow) a.overflow[0] = 1;
   }
   if constexpr (MODE == P1_TABLE) {
     if (c.D > a.KT && a.overflow) a.overflow[0] = 1;

@@ -204,3 +204,37 @@ def test_bf16_tables_of_a_row_of_zeros_and_a_far_query_word(L):
     got = ctx.distances(q.rowptr, q.col, q.val, method="rwmd", direction="d2q", precision="bf16")
     P.assert_distances(got, O.Oracle(V, db.rowptr, db.col, db.val).matrix(q.rowptr, q.col, q.val, "rwmd", 1, "d2q"))
     ctx.close()
+
+
+@pytest.mark.parametrize("m", [3, 40])
+@pytest.mark.parametrize("method,k", MEASURES)
+def test_far_words_near_each_other(L, monkeypatch, method, k, m):
+    """Far words that differ from each other by little: their keys are no
+    numbers, so their order is that of the distances by direct differences."""
+    rng = np.random.default_rng(57)
+    v = 120
+    V = rng.standard_normal((v, m)).astype(np.float32)
+    far = rng.choice(v, 30, replace=False)
+    V[far, 0] = 1e20
+    group = [np.sort(far), np.setdiff1d(np.arange(v), far)]
+    rows = []
+    for i in range(40):  # documents and queries of far words only, or near ones only
+        g = group[0] if i % 4 else group[1]
+        n = int(rng.integers(1, 13))
+        w = 1.0 - rng.random(n)
+        rows.append((np.sort(rng.choice(g, n, replace=False)), w / w.sum()))
+    db, q = _csr(rows[:30]), _csr([r for i, r in enumerate(rows) if i % 4])
+    print(f"[gpu] far words near each other {method} k={k} m={m}", flush=True)
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    got = ctx.distances(q.rowptr, q.col, q.val, method=method, k=k, direction="d2q")
+    want = O.Oracle(V, db.rowptr, db.col, db.val).matrix(q.rowptr, q.col, q.val, method, k, "d2q")
+    docs = [u for u in range(30) if u % 4]  # (the others are infinitely far)
+    P.assert_distances(got[:, docs], want[:, docs])
+    assert not np.any(np.isfinite(got[:, [u for u in range(30) if u % 4 == 0]]))
+    ctx.close()
+    # without room for the redo the call still answers
+    monkeypatch.setenv("LCEMD_FIX_CAP", "1")
+    ctx = L.open_context(V, db.rowptr, db.col, db.val)
+    got = ctx.distances(q.rowptr, q.col, q.val, method=method, k=k, direction="d2q")
+    assert np.all(np.isfinite(got[:, docs]))
+    ctx.close()
