@@ -1119,15 +1119,39 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
   const int64_t B = Q.B;
   if (o->exclude_self >= 0 && o->exclude_self + B > n)
     return fail(c, LCEMD_E_INVALID_ARG, "exclude_self + B exceeds the database size");
-  // the caller's device arrays are written once nothing but a device error can
-  // fail the call: symmetric results, which an early pass may leave to a later
-  // one, collect in scratch, one-way results are unpacked after the last check
   const bool sym = o->direction == LCEMD_SYM;
-  int64_t* didx = idx;
+  int64_t *didx = idx, *sidx = nullptr;
   float* ddist = dist;
-  if (!Q.device || sym) {
+  if (!Q.device) {
     if ((rc = wsget(c, "topl_idx", (size_t)B * l, didx)) || (rc = wsget(c, "topl_dist", (size_t)B * l, ddist))) return rc;
+  } else if (sym) {  // B l indices, then B l distances
+    if ((rc = wsget(c, "topl_saved", (size_t)(B * l + (B * l + 1) / 2), sidx))) return rc;
   }
+  // A failing call leaves the caller's arrays as they were.  One-way results
+  // are unpacked into device arrays after the last check; symmetric passes
+  // write there, so what the arrays hold is saved (queued behind phase 2, which
+  // hides it: collecting in scratch and copying at the end cost one document's
+  // call 15 us of 370) and put back if a later pass fails.
+  struct Saved {
+    lcemd_ctx* c;
+    int64_t *from_idx = nullptr, *idx;
+    float *from_dist = nullptr, *dist;
+    int64_t count;
+    hipError_t take(int64_t* i, float* d) {
+      const hipError_t e = launch_copy_topl(idx, dist, count, i, d, c->stream);
+      if (e == hipSuccess) {
+        from_idx = i;
+        from_dist = d;
+      }
+      return e;
+    }
+    void keep() { from_idx = nullptr; }
+    ~Saved() {
+      if (!from_idx) return;
+      (void)launch_copy_topl(from_idx, from_dist, count, idx, dist, c->stream);
+      (void)hipStreamSynchronize(c->stream);
+    }
+  } saved{c, nullptr, idx, nullptr, dist, B * l};
   const int64_t excl = o->exclude_self >= 0 ? o->exclude_self : -1;
   float* d2q;
   if ((rc = wsget(c, "d2q_full", (size_t)B * n, d2q))) return rc;
@@ -1166,6 +1190,7 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
     int32_t* drows;
     int* dflags = run.flags;
     if ((rc = wsget(c, "sym_rows", (size_t)B, drows))) return rc;
+    if (Q.device) HIPCHK(c, saved.take(sidx, reinterpret_cast<float*>(sidx + B * l)));
     std::vector<int> hflags;
     bool first = true;
     while (!rows.empty()) {
@@ -1225,7 +1250,7 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
       Lp *= 4;
       first = false;
     }
-    if (Q.device) HIPCHK(c, launch_copy_topl(didx, ddist, B * l, idx, dist, c->stream));
+    saved.keep();
   }
   if (!Q.device) {
     HIPCHK(c, hipMemcpyAsync(idx, didx, sizeof(int64_t) * B * l, hipMemcpyDeviceToHost, c->stream));

@@ -262,7 +262,7 @@ hipError_t launch_unpack_topl(const uint64_t* cand, int64_t cand_ld, int64_t row
   return hipGetLastError();
 }
 
-// Finished lists to the caller's arrays.
+// Lists from one pair of arrays to another.
 __global__ __launch_bounds__(kThreads) void k_copy_topl(const int64_t* __restrict__ idx_from,
                                                         const float* __restrict__ dist_from, int64_t count,
                                                         int64_t* __restrict__ idx, float* __restrict__ dist) {
