@@ -136,7 +136,8 @@ int lcemd_version(void);
  * LCEMD_E_NO_DEVICE if the device does not exist or is not gfx950,
  * LCEMD_E_INVALID_ARG if out is NULL, LCEMD_E_OOM if its 8-byte device
  * counter cannot be allocated.  Test hooks, read from the environment here:
- * LCEMD_FORCE_KERNEL (1: skip the 128-row phase-1 kernel, 2: deep kernel),
+ * LCEMD_FORCE_KERNEL (1: float32 keys, the 64-row phase-1 kernel up to lists
+ * of 64; 2: the deep kernel),
  * LCEMD_SYM_CANDIDATES (first candidate count of the symmetric top-l),
  * LCEMD_PHASE2 (1: word-major phase 2 where possible, 2: per document),
  * LCEMD_TABLE_BUDGET (bytes of phase-1 tables per tile; default 12 GiB),

@@ -463,9 +463,9 @@ int d2q_tables(lcemd_ctx* c, const DbView& db, const QDev& Q, const lcemd_opts* 
   a.ZW = ZW;
   a.zw_nq = zw_pitch(nq);
   a.overflow = ovf;
-  // rows whose quantised selection is not certified are listed for an
-  // exact redo (every precision on the 128-row kernel); the redo kernel
-  // reads the listed count on the device
+  // rows that a kernel cannot settle (bf16 and fp8: a selection that is not
+  // certified; ICT: more entries than the list) are listed for an exact redo;
+  // the redo kernel reads the listed count on the device
   int* fixc = nullptr;
   int fixcap = c->arena.base ? kFixCapNoAlloc : kFixCap;
   if (c->fix_cap > 0) fixcap = std::min(fixcap, c->fix_cap);

@@ -71,7 +71,7 @@ struct lcemd_ctx {
   // scratch, grow-only
   std::map<std::string, DevBuf> ws;
   size_t table_budget = size_t(12) << 30;  // test hook LCEMD_TABLE_BUDGET (bytes) sets it at creation
-  int force_kernel = 0;   // test hook (LCEMD_FORCE_KERNEL): 1 = skip the 128-row kernel, 2 = deep kernel
+  int force_kernel = 0;   // test hook (LCEMD_FORCE_KERNEL): 1 = the 64-row kernel for lists of up to 64 entries, 2 = deep kernel
   int sym_candidates = 0; // test hook (LCEMD_SYM_CANDIDATES): first candidate count of the SYM top-l
   int p2_mode = 0;        // test hook (LCEMD_PHASE2): 0 = by table size, 1 = word-major when possible, 2 = per document
   int fix_cap = 0;        // test hook (LCEMD_FIX_CAP): rows per table tile that may be redone exactly (0 = default)

@@ -28,8 +28,11 @@ constexpr int kSegShort = 512;
 // capacities do not yet cover the word's largest weight are redone exactly.
 constexpr int kIctList = 16;
 // bfloat16 phase-1 rows: the real dims plus six folded-in terms, rounded up
-// to 64 dims; the bf16 kernel holds rows of up to this many dims in
-// registers (wider embeddings select with float32 keys).
+// to 64 dims.  Wider rows than this select with float32 keys.  The line is that
+// of a kernel that held its rows in registers; the present one streams 64-dim
+// slices and was the faster one beyond it too in a trial (32 queries, 18,000
+// documents, 30,000 words, k = 8: 500 dims 1.79 -> 1.36 ms a call, 768 dims
+// 2.50 -> 1.82), but has no tests there.
 constexpr int kBf16MaxDims = 384;
 __host__ __device__ inline int bf16_row_dims(int m) { return (m + 6 + 63) / 64 * 64; }
 // The keys kernel for segments longer than kSegShort keeps its rows of keys
@@ -218,10 +221,10 @@ hipError_t launch_phase2_wordmajor(const int64_t* xptr, int64_t n, const int64_t
                                    const uint32_t* winv, int64_t nnz, int64_t v_used, const float2* ZW,
                                    int64_t zw_nq, int KT, float* cost, float* out, int64_t ld,
                                    unsigned long long* counters, hipStream_t s);
-// Phase 2 with the tables of 8 or 16 queries in LDS (phase2_lds.hip): small
-// vocabularies, batches of more than 32 queries with enough windows of 128
-// documents to fill the chip.  perm: the documents in order of length within
-// windows of 128.
+// Phase 2 with the tables of 16 queries in LDS (phase2_lds.hip): small
+// vocabularies, one or two entries a row, batches of more than 32 queries or
+// enough documents.  perm: the documents in order of length within windows of
+// 128.
 bool phase2_lds_fits(int64_t n, int64_t v_used, int KT, int64_t nq);
 hipError_t launch_phase2_lds(const int64_t* xptr, const int2* xcv, int64_t n, const int32_t* perm, int64_t v_used,
                              const float2* ZW, int64_t zw_nq, int KT, int64_t nq, float* out, int64_t ld,

@@ -58,7 +58,8 @@
 // dims all in registers and a tile of 32 words at a time: 68 ms.
 // What is computed from the thread's index is kept from being hoisted out of
 // the item and stage loops (fresh): 46 registers spilled, and a reload waits
-// for every load in flight before it, the next stage's words (55 -> 44 ms).
+// for every load in flight before it, the next stage's words (55 -> 44 ms;
+// lists of 16 still spill 3).
 #include <algorithm>
 
 #include "internal.h"

@@ -64,14 +64,18 @@ constexpr float kFGuard = 0.25f;
 // hands on as it is, but not yet one as the high half of a float64.
 constexpr uint32_t kNoKey = 0x7fe00000u;
 
-// Tiles per pass at most, and workgroups per CU.  Two tiles let a wave of
-// lists of up to 8 entries fit 168 registers, three workgroups per CU, which
-// hide each other's latencies: lists of 1, items of eight queries, two tiles
-// and three workgroups 48.7 ms, three and two 50.3, four and two 52.0 (the
-// RWMD matrix above).  Longer lists spill there (k = 16: 30.2 ms against 26.4
-// with three tiles and two workgroups, 28.0 with four), and the pair mode has
-// one short segment per item, for which two workgroups of wider passes are
-// the faster (2.1 against 2.3 ms over 500 queries).  Embeddings of at most 28
+// Tiles per pass at most, and workgroups per CU.  Two tiles bring a wave of
+// lists of up to 8 entries near 168 registers (tables of 1, 2, 4 and 8 spill
+// 8, 9, 11 and 22), three workgroups per CU, which hide each other's
+// latencies: lists of 1, items of eight queries, two tiles and three
+// workgroups 48.7 ms, three and two 50.3, four and two 52.0 (the RWMD matrix
+// above).  Longer lists spill too much there (k = 16: 30.2 ms against 26.4 with
+// three tiles and two workgroups, 28.0 with four).  Lists of 32 spill 116
+// registers at two workgroups and are still the faster way: 64 queries against
+// 18,000 documents of a 70,000-word vocabulary, k = 17 / 24 / 32, 6.2 / 6.2 /
+// 6.2 ms a call, 11.8 / 12.2 / 12.3 on the kernel this replaced.  The pair mode
+// has one short segment per item, for which two workgroups of wider passes are
+// the faster (2.1 against 2.3 ms over 500 queries; lists of 16 spill 14).  Embeddings of at most 28
 // dims (SMALL) have one slice and little to contract, so what counts there is
 // how many waves hide the set-up and the selection (four workgroups, at 128
 // registers, spill: 20,000 images x 784 words, k = 8, 2.9 against 2.6 ms).

@@ -6,18 +6,18 @@
 // valid entry carries w = +inf, so the walk below is Eq. (6)-(8) followed by
 // Eq. (9) (the rest of the mass at the last distance) and always ends.
 //
-// Layout and mapping: a wave's 64 lanes are QL consecutive queries times
-// 64/QL documents.  A lane walks its document's non-zeros in order, so the
-// QL lanes of a document read one contiguous run of the table (QL entries of
-// 16 bytes per non-zero, the interleaved layout) and every (query, document)
-// sum has one fixed order: groups of eight consecutive non-zeros summed as a
-// binary tree, the groups accumulated in order with Kahan compensation (the
-// error stays a few ulps for rows of any length) -- the same bits whatever
-// QL, the batch or the launch.  QL = 64 for batches of more
-// than 32 queries (then a wave works on one document at a time); smaller
-// batches put several documents in a wave, taken in order of length within
-// windows of 128 documents (a permutation made when the database is loaded)
-// so that the lanes of a wave finish together while its outputs stay close.
+// Layout and mapping: batches of more than 32 queries take 64 consecutive
+// queries in a wave's lanes and one document at a time (k_phase2_persistent);
+// smaller ones QL queries (a power of two) beside several lanes that share a
+// document's non-zeros and, below 8 queries, several documents in order of
+// length within windows of 128 (a permutation made when the database is
+// loaded), so that the lanes of a wave finish together while its outputs stay
+// close (k_phase2_small).  A non-zero's table row is one contiguous run for the
+// queries of a wave (16 bytes each, the interleaved layout), and every (query,
+// document) sum has one fixed order: groups of eight consecutive non-zeros
+// summed as a binary tree, the groups accumulated in order with Kahan
+// compensation (the error stays a few ulps for rows of any length) -- the same
+// bits whatever the split, the batch or the launch.
 #include <algorithm>
 #include <climits>
 #include <mutex>
