@@ -1120,12 +1120,10 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
   if (o->exclude_self >= 0 && o->exclude_self + B > n)
     return fail(c, LCEMD_E_INVALID_ARG, "exclude_self + B exceeds the database size");
   const bool sym = o->direction == LCEMD_SYM;
-  int64_t *didx = idx, *sidx = nullptr;
+  int64_t* didx = idx;
   float* ddist = dist;
   if (!Q.device) {
     if ((rc = wsget(c, "topl_idx", (size_t)B * l, didx)) || (rc = wsget(c, "topl_dist", (size_t)B * l, ddist))) return rc;
-  } else if (sym) {  // B l indices, then B l distances
-    if ((rc = wsget(c, "topl_saved", (size_t)(B * l + (B * l + 1) / 2), sidx))) return rc;
   }
   // A failing call leaves the caller's arrays as they were.  One-way results
   // are unpacked into device arrays after the last check; symmetric passes
@@ -1153,8 +1151,9 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
     }
   } saved{c, nullptr, idx, nullptr, dist, B * l};
   const int64_t excl = o->exclude_self >= 0 ? o->exclude_self : -1;
-  float* d2q;
-  if ((rc = wsget(c, "d2q_full", (size_t)B * n, d2q))) return rc;
+  float* d2q;  // (then the saved lists: B l indices, 8-byte aligned, and B l distances)
+  const int64_t after = (B * n + 1) / 2 * 2;
+  if ((rc = wsget(c, "d2q_full", (size_t)(after + (sym && Q.device ? 3 * B * l : 0)), d2q))) return rc;
   const DbView db = db_view(c);
   D2qRun run;
   if (o->direction == LCEMD_Q2D) {
@@ -1190,7 +1189,7 @@ int lcemd_topl(lcemd_ctx* c, const lcemd_query* q, const lcemd_opts* o, int32_t 
     int32_t* drows;
     int* dflags = run.flags;
     if ((rc = wsget(c, "sym_rows", (size_t)B, drows))) return rc;
-    if (Q.device) HIPCHK(c, saved.take(sidx, reinterpret_cast<float*>(sidx + B * l)));
+    if (Q.device) HIPCHK(c, saved.take(reinterpret_cast<int64_t*>(d2q + after), d2q + after + 2 * B * l));
     std::vector<int> hflags;
     bool first = true;
     while (!rows.empty()) {
